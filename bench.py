@@ -38,28 +38,26 @@ BYTES_PER_EVENT_COMPUTED_BINS = 33
 HBM_PEAK_GBS = 8000.0
 SETTLE_S = 0.1   # untimed load before the warm-up steps (clock settle)
 # Algorithmic FP64 flops per event of the formulation the kernel follows
-# (an FMA counts two, a reciprocal estimate one): matter term and amplitude
-# inputs 9, cubic coefficients 12 (the trigonometric seeds are FP32), one
-# Halley step with its third-order correction on two roots 54, third root 2,
-# differences, 1/(E Q) and the phase scale 16, coefficients of the
-# projectors X1 and X2 6, two sin and cos - 1 of the phase differences 52
-# (the phase products sit inside their reduction FMAs), numerators of X1
-# and X2 16, amplitude sum 15, |S|^2 3, weighted add 2 (w * P and the add
-# into the histogram).  Computing the bin per call adds 4 (scale, offset,
-# quotient, floor).  A wave in which two eigenvalues lie within ~0.85 % of
-# their spread adds a Newton step (31); no wave of the benchmark workloads
-# does.
-FLOPS_PER_EVENT = 187
-FLOPS_PER_EVENT_COMPUTED_BINS = 191
-# Layered path, per layer: matter term 1, cubic coefficients 9 and its
-# solution 59 (as above: p 3, corrected Halley 54, third root 2),
-# differences and 1/Q 12, phase scale 1, two sin and cos - 1 52, cos 2,
+# (an FMA counts two, an inverse square root estimate one): matter term and
+# amplitude inputs 9, coefficients of the cubic and its discriminant 13 (the
+# seed of the isolated root is FP32), two chord steps 14, sum and product of
+# the other two roots and f' 6, 1/E, 1/f', del and 1/del from one inverse
+# square root 23, root difference and phase scale 3, the projector element X
+# 8 and Y 7, two sines and cosines of the phases 52 (the phase products sit
+# inside their reduction FMAs), amplitude sum and |S|^2 17, weighted add 2
+# (w * P and the add into the histogram).  Computing the bin per call adds 4
+# (scale, offset, quotient, floor).
+FLOPS_PER_EVENT = 154
+FLOPS_PER_EVENT_COMPUTED_BINS = 158
+# Layered path, per layer: matter term 1, the isolated root and the
+# discriminant 33 (as above), del 15, the three roots 5, differences and 1/Q
+# 12, phase scale 1, two sines and cosines 52,
 # c_k 7, eigenvalue sums and products 6, polynomial coefficients a2, a1, a0
-# 19, y = M v 74, z = M y 74, v = a2 z + a1 y + a0 v 66: 382.  The first
+# 19, y = M v 74, z = M y 74, v = a2 z + a1 y + a0 v 66: 365.  The first
 # layer forms y as column alpha of M (2 instead of 74), the last only
 # component beta of z and v (26 + 22 instead of 74 + 66); per event 1/E 7,
 # |v_beta|^2 3 and the weighted add 2.
-LAYER_FLOPS = 382
+LAYER_FLOPS = 365
 
 
 def layered_flops_per_event(n_layers):
@@ -81,17 +79,17 @@ KERNEL_SOURCES = ("paper_1311_7579_amd/csrc/osc_device.h",
                   "paper_1311_7579_amd/csrc/osc_kernels.hip",
                   "paper_1311_7579_amd/build.py")
 COUNTER_TRAFFIC = {
-    "fetch_kib": 92836.0, "fetch_scale": 2.0,     # copy of 512 MiB: FETCH_SIZE 262157 KiB
-    "write_kib": 82562.4, "write_scale": 1.0,     # copy of 512 MiB: WRITE_SIZE 524288 KiB
-    "valu_per_event": 170.0,
-    "classes_per_event": {"fp64": 119.5, "fp64_trans": 2.0, "fp32": 15.0, "fp32_trans": 4.0,
-                          "cvt": 5.0, "int32": 6.69, "int64": 0.375, "other": 17.44},
-    "source_sha256": "bda247f22a1b7708bb86df22b451d9748abe6d2a1e6e26a4b6f78e769d704574",
+    "fetch_kib": 92843.9, "fetch_scale": 2.0,     # copy of 512 MiB: FETCH_SIZE 262157 KiB
+    "write_kib": 82424.3, "write_scale": 1.0,     # copy of 512 MiB: WRITE_SIZE 524288 KiB
+    "valu_per_event": 144.9,
+    "classes_per_event": {"fp64": 95.9, "fp64_trans": 1.0, "fp32": 19.0, "fp32_trans": 2.0,
+                          "cvt": 3.0, "int32": 6.38, "int64": 0.375, "other": 17.25},
+    "source_sha256": "73a9e42ec6fbc40ac5f3d96abf886bfdd0acf4ecf7df17e2a872a7baf655b239",
 }
 # Issue time of one wave instruction on one SIMD, measured on the box with
 # probe kernels of independent chains (ns): FP64 FMA/MUL/ADD 2.08, FP32
-# 1.06, v_rcp_f64 6.75, v_cos_f32 3.38 and v_sqrt_f32 about 4 (3.7 for the
-# FP32 transcendentals, two cos and a sqrt and an rsq per event).
+# 1.06, v_rcp_f64 6.75 (v_rsq_f64 taken as that), v_cos_f32 3.38 and
+# v_sqrt_f32 about 4 (3.7 for the FP32 transcendentals).
 # Conversions and 64-bit integer operations are taken at the FP64 rate and
 # the unclassified remainder (moves, selects) at the FP32 rate: assumed,
 # not measured.  2.08 ns for a 4-cycle FP64 instruction is an engine clock

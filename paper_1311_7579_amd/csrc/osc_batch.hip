@@ -142,7 +142,7 @@ void batch_kernel(BatchArgs a, SinCosTable sctab, const BatchSampleDev* __restri
         for (int set = int(g) * a.sets_per_item; set < set_end; ++set) {
             const SetConsts& sc = sets[set];
             __syncthreads();   // the previous set's table and histogram are read
-            load_tab<MIXED>(sc, tabs, lane);
+            load_tab(sc, tabs, lane);
             hist_zero(hist, lane, nbt);
             __syncthreads();
             const ConstDensityProb<MIXED> prob{&sc, &tabs, S.pc.kA, S.pc.kL};

@@ -21,8 +21,8 @@ constexpr int kGroup = 1;
 static_assert(kLaneEvents % kGroup == 0, "the group size divides the events per lane");
 
 // ---------------------------------------------------------------------------
-// FP64 sine and cosine - 1 of a phase given in units of pi/32 as the
-// product a b (|a b| < 2^50).  The nearest integer n to the exact product
+// FP64 sine and cosine of a phase given in units of pi/32 as the product
+// a b (|a b| < 2^50).  The nearest integer n to the exact product
 // comes out of one FMA against 1.5 * 2^52 (n lands in the low mantissa
 // bits), u = a b - n (|u| <= 1/2) out of a second one, so the reduction is
 // exact up to the final rounding of u.  With r = u pi/32 (|r| <= pi/64):
@@ -32,7 +32,7 @@ static_assert(kLaneEvents % kGroup == 0, "the group size divides the events per 
 //                error fit on |u| <= 1/2, error below 8e-18),
 // and the angle-addition formulas with the anchor k = n mod 64 from LDS:
 //   sin = s_k + s_k (cos r - 1) + c_k sin r,
-//   cos - 1 = (c_k - 1) + c_k (cos r - 1) - s_k sin r.
+//   cos = c_k + c_k (cos r - 1) - s_k sin r.
 // ---------------------------------------------------------------------------
 constexpr double kRoundMagic = 6755399441055744.0;        // 1.5 * 2^52
 constexpr double kStep = 0.09817477042468103;             // fl(pi / 32)
@@ -51,29 +51,25 @@ __device__ __forceinline__ double flip_sign(double v, uint32_t sign_bit)
 // p7 and q6 are kP7 and kQ6; a caller that evaluates many phases passes
 // them from VGPRs (see PolyRegs), so that each polynomial step reads at most
 // one constant from an SGPR pair (the VALU reads one per instruction).
-__device__ __forceinline__ void phase_sincos(double a, double b, const SinCosL* __restrict__ table,
-                                             double& sn, double& cm1, double p7 = kP7,
+__device__ __forceinline__ void phase_sincos(double a, double b, const SinCos* __restrict__ table,
+                                             double& sn, double& cs, double p7 = kP7,
                                              double q6 = kQ6)
 {
     const double t = __builtin_fma(a, b, kRoundMagic);
     const double n = t - kRoundMagic;
     const double u = __builtin_fma(a, b, -n);
-    const SinCosL k = table[__double2loint(t) & 63];
+    const SinCos k = table[__double2loint(t) & 63];
     const double z = u * u;
     const double s = u * __builtin_fma(z, __builtin_fma(z, __builtin_fma(z, p7, kP5), kP3), kStep);
     const double cm = z * __builtin_fma(z, __builtin_fma(z, q6, kQ4), kQ2);
     sn = __builtin_fma(k.s, cm, __builtin_fma(k.c, s, k.s));
-    cm1 = __builtin_fma(k.c, cm, __builtin_fma(-k.s, s, k.cm1));
+    cs = __builtin_fma(k.c, cm, __builtin_fma(-k.s, s, k.c));
 }
 
-// Copy the sin/cos anchors into LDS (the 64 lanes of a wave, one each);
-// c - 1 is exact for c >= 1/2 and within half an ulp of 1 below.
+// Copy the sin/cos anchors into LDS (the 64 lanes of a wave, one each).
 __device__ __forceinline__ void load_sincos(const SinCosTable& t, TileTables& T, int lane)
 {
-    if (lane < 64) {
-        const SinCos e = t.e[lane];
-        T.sct[lane] = SinCosL{e.s, e.c, e.c - 1.0};
-    }
+    if (lane < 64) T.sct[lane] = t.e[lane];
 }
 
 // Mixed tier: the phase (a b in units of pi/32, so a b / 64 in revolutions)
@@ -96,6 +92,16 @@ __device__ __forceinline__ double recip(double y)
     const double r = __builtin_amdgcn_rcp(y);
     const double e = fma(-y, r, 1.0);
     return fma(r, fma(e, e, e), r);
+}
+
+// y^-1/2 of a positive y: the hardware estimate r (relative error e/2 ~
+// 3e-7) corrected with the third-order series r (1 + e/2 + 3/8 e^2), e = 1 -
+// y r^2.
+__device__ __forceinline__ double rsqrt_refined(double y)
+{
+    const double r = __builtin_amdgcn_rsq(y);
+    const double e = fma(-(y * r), r, 1.0);
+    return fma(r * e, fma(e, 0.375, 0.5), r);
 }
 
 // 1/y with one Newton-Raphson correction (relative error ~1e-13): enough
@@ -133,9 +139,9 @@ __device__ __forceinline__ double sgpr_value(double v)
     return v;
 }
 
-// The same, kept in a VGPR: loop-invariant operands that would otherwise
-// be the second SGPR operand of an instruction (and be copied into a VGPR
-// on every use).
+// The same, kept in a VGPR: loop-invariant
+// operands that would otherwise be the second SGPR operand of an instruction
+// (and be copied into a VGPR on every use).
 __device__ __forceinline__ double vgpr_value(double v)
 {
     asm("" : "+v"(v));
@@ -152,44 +158,185 @@ struct PolyRegs {
     }
 };
 
-// Roots of f(x) = x^3 - tr x^2 + c1 x - det (three real roots: the matrix
-// is Hermitian).  Two roots are seeded in FP32 from the trigonometric
-// solution x = tr/3 + (2/3) sqrt(p) cos(theta - 2 pi k / 3),
-// theta = acos(q / (2 p^1.5)) / 3 (p = tr^2 - 3 c1; qh = q / 2 with
-// q = 2 tr^3 - 9 tr c1 + 27 det is passed in), each refined in FP64 by one
-// Halley step on f with its third-order error term added back; the third
-// root follows from the trace.  The two roots' divisions of each step
-// share one reciprocal: 1/a = b / (a b), 1/b = a / (a b).
-// The seeds err by about 1e-4 of the roots' spread, so relative to the
-// smallest root distance they worsen as two roots close in.  With
-// r = q / (2 p^1.5) = cos 3 theta, that distance over the spread is about
-// sqrt((1 - |r|) / 3.4), and a wave where some lane has 1 - |r| below
-// kNearDegenerate (distance under ~0.85 % of the spread: near a level
-// crossing, or a matter term far above the vacuum splittings) adds one
-// Newton step.  Elsewhere the corrected Halley step leaves the roots within
-// ~1e-14 of their smallest distance, as Halley and Newton together do.
-// HALLEY_ONLY (the FP32-mixed tier): a wave skips the Newton step when
-// every lane's Halley corrections were at most 2^-12 of its smallest root
-// distance.  Halley converges cubically, so the roots are then within about
-// (2^-12)^3 ~ 1.5e-11 of that distance, far below what the FP32 amplitude
-// assembly resolves, and the phases stay within ~1e-8 rad up to 1e3 rad.
-constexpr double kHalleyOnly = 0x1p-12;
-constexpr float kNearDegenerate = 0x1p-12f;
-// Two roots closer than about 7e-4 of the spread (1 - |r| below this, near
-// an exact level crossing, which needs a zero mixing angle) round r to
-// within a few ulp of +-1 in FP32: both seeds then start from the pair's
-// midpoint, where f' vanishes, and no refinement separates them.  Such a
-// lane's P is undefined and comes out NaN (every such lane takes the
-// Newton step, where this is applied).
+// The eigenvalues of M in the FP64 tier come from one root of the characteristic cubic f(x) =
+// x^3 - tr x^2 + c1 x - det and the cubic's discriminant.  Of three real
+// roots one, x, is isolated: at least half the spread away from both
+// others (the top one where q > 0, the bottom one where q < 0).  It is
+// x = tr/3 + sign(q) sqrt(p) (2/3) cos(acos(|r|) / 3), r = q / (2 p^1.5),
+// and (2/3) cos(acos(|r|) / 3) is smooth on [0, 1] (no arccos near its end
+// points, no cosine): a polynomial of degree 6 gives it to 5e-8.  With a =
+// A + A0 (A0 the minimum of p over A) p = a^2 + pm and q/2 = a^3 + k1 a + k0
+// have no cancellation, so all of the seed runs in FP32 from fl32(a); it
+// errs by at most ~3e-6 of the spread, typically 1e-7.  Each chord step
+// x -= f(x) / f'(seed), with FP64 f and an FP32 1/f', squares that error and
+// then multiplies it by it again: two steps reach FP64 rounding.
+// The other two roots are not solved for: their sum is tr - x = -e, their
+// product g = c1 - x (tr - x), f'(x) = (x - l1)(x - l2), and half their
+// distance is del = sqrt(disc) / f'(x) with disc a quarter of the
+// discriminant, a quartic in A with host coefficients.  That keeps del
+// accurate to a few ulp of itself also where the two are close (a solution
+// of the cubic for both roots leaves an ulp of the largest root there).
+struct Levels {
+    double x;     // the isolated eigenvalue
+    double e;     // x - tr: minus the sum of the other two
+    double g;     // their product
+    double fp;    // f'(x) > 0
+    double disc;  // discriminant / 4 = (fp del)^2
+};
+
+// Two eigenvalues closer than about 7e-4 of the spread (1 - |r| below this,
+// near an exact level crossing, which needs a zero mixing angle) are not
+// resolved by the characteristic cubic; such an event's P comes out NaN.
 constexpr float kUnresolved = 0x1p-19f;
-// FP32-mixed tier: waves with a matter term above this (eV^2, about 4
-// times the largest vacuum splitting) assemble the amplitude in FP64.
+
+// q / (2 p^1.5) = cos 3 theta of the cubic, in FP32 (also gives the seed's
+// a, p^-1/2 and p).
+struct SeedAngle {
+    float a, p, rs, r;
+};
+
+__device__ __forceinline__ SeedAngle seed_angle(const SetConsts& sc, double A)
+{
+    SeedAngle s;
+    s.a = float(A + sc.A0);
+    const float a2 = s.a * s.a;
+    s.p = a2 + sc.pm;
+    const float qh = __builtin_fmaf(s.a, a2 + sc.k1, sc.k0);     // q / 2
+    s.rs = __builtin_amdgcn_rsqf(s.p);
+    s.r = qh * s.rs * (s.rs * s.rs);
+    return s;
+}
+
+__device__ __forceinline__ Levels matter_levels(const SetConsts& sc, double A)
+{
+    Levels v;
+    const double tr = sc.T0 + A, c1 = fma(A, sc.CA, sc.C0), det = A * sc.DA;
+    v.disc = fma(A, fma(A, fma(A, fma(A, sc.D4, sc.D3), sc.D2), sc.D1), sc.D0);
+    // the seed, in FP32
+    const SeedAngle sa = seed_angle(sc, A);
+    const float ar = __builtin_fabsf(sa.r);
+    float G = -0.0006958966f;
+    G = __builtin_fmaf(G, ar, 0.003408973f);
+    G = __builtin_fmaf(G, ar, -0.008384795f);
+    G = __builtin_fmaf(G, ar, 0.015869704f);
+    G = __builtin_fmaf(G, ar, -0.031987853f);
+    G = __builtin_fmaf(G, ar, 0.11110617f);
+    G = __builtin_fmaf(G, ar, 0.57735032f);
+    const float kf = __builtin_copysignf(sa.p * sa.rs, sa.r);
+    float xf = __builtin_fmaf(kf, G, __builtin_fmaf(sa.a, 1.0f / 3.0f, sc.t3));
+    if (ar > 1.0f - kUnresolved) xf = __builtin_nanf("");
+    // f'(seed) = p (3 G^2 - 1/3)
+    const double inv = double(__builtin_amdgcn_rcpf(sa.p * __builtin_fmaf(3.0f * G, G, -1.0f / 3.0f)));
+    double x = double(xf);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) x = fma(-fma(fma(x - tr, x, c1), x, -det), inv, x);
+    v.x = x;
+    v.e = x - tr;
+    v.g = fma(v.e, x, c1);
+    v.fp = fma(x, x + v.e, v.g);
+    return v;
+}
+
+// The entry of flag byte f in one of the LDS channel arrays.
+template <class Part>
+__device__ __forceinline__ Part channel_part(const Part* table, uint32_t f)
+{
+    static_assert(sizeof(Part) == 16, "entries are 16-byte parts");
+    const uint32_t ci = min(f, uint32_t(kFlagEntries - 1));
+    return *reinterpret_cast<const Part*>(reinterpret_cast<const unsigned char*>(table) +
+                                          ((ci << 4) + (ci & 16u)));
+}
+
+// +kA E for neutrinos, -kA E for antineutrinos (bit 4 of the flag byte,
+// moved to the sign bit; one shift and one bit-field insert).
+__device__ __forceinline__ double matter_term(double kA, double E, uint32_t f)
+{
+    return __builtin_copysign(kA * E, __hiloint2double(int(f << 27), 0));
+}
+
+// P(alpha -> beta) of one event.  With the isolated eigenvalue x, the mean mu
+// and half-distance del of the other two, b = x - mu, and the phases theta =
+// b L/2E and psi = del L/2E, the evolution operator is, up to the common
+// phase exp(-i mu L/2E),
+//   (1 - X) cos psi - i (sin psi / del) Y + exp(-i theta) X,
+//   X = (M^2 + e M + g) / f'(x)     (the spectral projector of x),
+//   Y = (M - mu)(1 - X) = M - mu - b X.
+// sin psi / del has no singularity as the two eigenvalues close in.  Only
+// the element (beta, alpha) is formed.  1/E, 1/f', del and 1/del share one
+// inverse square root, of disc (E f')^2.
+// Bound by VALU issue: about 125 FP64 issue slots per event and wave (the
+// benchmark step's loop, an FP32 instruction counted as half), against 158
+// with two roots from trigonometric seeds, a Halley step each and the
+// projectors of two roots.  1e7 events: P alone 59.5 -> 49.7 us, the step on
+// binned events with P written 71.1 -> 59.9 us; the error against
+// 64-bit references fell (1.1e-15 -> 6.5e-16 relative on uniform energies)
+// or stayed.
+__device__ __forceinline__ double event_prob(const SetConsts& sc, const TileTables& T, double kA,
+                                             double kL, double E, uint32_t f,
+                                             const PolyRegs& pr = PolyRegs{})
+{
+    // flag byte (alpha bits 0-1, beta bits 2-3, antineutrino bit 4) -> the
+    // channel entry (conjugated for antineutrinos) and the sign of A
+    const Pair m = channel_part(T.m, f), m2 = channel_part(T.m2, f), g = channel_part(T.g, f),
+               d = channel_part(T.d, f);
+    const double A = matter_term(kA, E, f);
+    const double dba = d.b;   // [alpha = beta]; NaN for an invalid flag byte
+
+    // amplitude inputs: M_ba and (M^2)_ba
+    const double mre = fma(A, d.a, m.a), mim = m.b;
+    const double m2re = fma(A, fma(A, d.a, g.a), m2.a);
+    const double m2im = fma(A, g.b, m2.b);
+
+    const Levels v = matter_levels(sc, A);
+    const double u = E * v.fp;
+    const double y = rsqrt_refined(v.disc * (u * u));   // 1 / (sqrt(disc) u)
+    const double yu = y * u;                            // 1 / sqrt(disc)
+    const double sd = v.disc * yu;                      // sqrt(disc)
+    const double iu = y * sd;                           // 1 / u
+    const double inv_fp = E * iu;
+    double invE = v.fp * iu;
+    invE = fma(invE, fma(-E, invE, 1.0), invE);         // the phases take its last bits
+    const double del = sd * inv_fp, inv_del = v.fp * yu;
+    const double b = fma(0.5, v.e, v.x);
+    const double ph = kL * invE;                        // phase per eV^2 in units of pi/32
+
+    const double Xr = fma(v.g, dba, fma(v.e, mre, m2re)) * inv_fp;
+    const double Xi = fma(v.e, mim, m2im) * inv_fp;
+    const double Yr = fma(-b, Xr, fma(v.e, 0.5 * dba, mre));
+    const double Yi = fma(-b, Xi, mim);
+    double s1, c1, s2, c2;
+    phase_sincos(b, ph, T.sct, s1, c1, pr.p7, pr.q6);     // theta
+    phase_sincos(del, ph, T.sct, s2, c2, pr.p7, pr.q6);   // psi
+    const double sg = s2 * inv_del, w = c1 - c2;
+    const double zr = fma(sg, Yi, fma(s1, Xi, fma(w, Xr, dba * c2)));
+    const double zi = fma(-sg, Yr, fma(-s1, Xr, w * Xi));
+    return fma(zi, zi, zr * zr);
+}
+
+// The eigenvalues in the FP32-mixed tier: roots of f(x) = x^3 - tr x^2 +
+// c1 x - det.  Two roots are seeded in FP32 from the trigonometric
+// solution x = tr/3 + (2/3) sqrt(p) cos(theta - 2 pi k / 3),
+// theta = acos(q / (2 p^1.5)) / 3 (p = tr^2 - 3 c1, q = 2 tr^3 - 9 tr c1 +
+// 27 det, qh = q / 2), each refined in FP64 by one
+// Halley step on f; the third root follows from the trace.  The two roots'
+// divisions of each step share one reciprocal: 1/a = b / (a b), 1/b = a /
+// (a b).  A wave skips the Newton step when every lane's Halley corrections
+// were at most 2^-12 of its smallest root distance.  Halley converges
+// cubically, so the roots are then within about (2^-12)^3 ~ 1.5e-11 of that
+// distance, far below what the FP32 amplitude assembly resolves, and the
+// phases stay within ~1e-8 rad up to 1e3 rad.  (The FP64 tier's isolated
+// root would be cheaper here too, but every P of this tier would change in
+// its FP32 roundings.)
+constexpr double kHalleyOnly = 0x1p-12;
+// Waves with a matter term above this (eV^2, about 4 times the largest
+// vacuum splitting) assemble the amplitude in FP64.
 constexpr double kMixedWideA = 0.01;
 
-template <bool HALLEY_ONLY = false>
-__device__ __forceinline__ void cubic_roots(double tr, double c1, double det, double qh,
-                                            double& l0, double& l1, double& l2)
+__device__ __forceinline__ void cubic_roots_mixed(const SetConsts& sc, double A, double& l0,
+                                                  double& l1, double& l2)
 {
+    const double tr = sc.T0 + A, c1 = fma(A, sc.CA, sc.C0), det = A * sc.DA;
+    const double qh = fma(fma(A + sc.QH2, A, sc.QH1), A, sc.QH0);
     const double p = fma(tr, tr, -3.0 * c1);
     const float pf = float(p), qf = float(qh);
     const float rs = __builtin_amdgcn_rsqf(pf);                 // p^-1/2
@@ -215,40 +362,20 @@ __device__ __forceinline__ void cubic_roots(double tr, double c1, double det, do
         const double d0 = fma(g0, g0, f0 * m0);
         const double d1 = fma(g1, g1, f1 * m1);
         const double r = recip_coarse(d0 * d1);
-        if constexpr (!HALLEY_ONLY) {
-            // the Halley step h and its leading error term: for this cubic
-            // the root lies C h^3 beyond x - h, C = (f' - (3x - tr)^2) / f'^2
-            // (to leading order; h is then the seed's error), so that term
-            // is added; 1/f'^2 comes from the shared reciprocal, since
-            // d = f'^2 (1 + O(h)).
-            const double q0 = d1 * r, q1 = d0 * r;
-            const double h0 = (f0 * g0) * q0, h1 = (f1 * g1) * q1;
-            const double e0 = fma(-m0, m0, g0) * q0, e1 = fma(-m1, m1, g1) * q1;
-            // x - h + e h^3 = x - h (1 - e h^2)
-            x0 = fma(-h0, fma(-(e0 * h0), h0, 1.0), x0);
-            x1 = fma(-h1, fma(-(e1 * h1), h1, 1.0), x1);
-            if (!__any(__builtin_fabsf(rf) > 1.0f - kNearDegenerate)) {
-                l0 = x0;
-                l1 = x1;
-                l2 = (tr - l0) - l1;
-                return;
-            }
-        } else {
-            const double h0 = (f0 * g0) * (d1 * r), h1 = (f1 * g1) * (d0 * r);
-            x0 -= h0;
-            x1 -= h1;
-            // x0 > x1 > x2 = tr - x0 - x1: the smallest root distance is
-            // x0 - x1 or x1 - x2 = 2 x1 + x0 - tr
-            const double dmin = __builtin_fmin(__builtin_fabs(x0 - x1),
-                                               __builtin_fabs(fma(2.0, x1, x0) - tr));
-            const bool done = __builtin_fmax(__builtin_fabs(h0), __builtin_fabs(h1)) <=
-                              kHalleyOnly * dmin;
-            if (__all(done)) {
-                l0 = x0;
-                l1 = x1;
-                l2 = (tr - l0) - l1;
-                return;
-            }
+        const double h0 = (f0 * g0) * (d1 * r), h1 = (f1 * g1) * (d0 * r);
+        x0 -= h0;
+        x1 -= h1;
+        // x0 > x1 > x2 = tr - x0 - x1: the smallest root distance is
+        // x0 - x1 or x1 - x2 = 2 x1 + x0 - tr
+        const double dmin = __builtin_fmin(__builtin_fabs(x0 - x1),
+                                           __builtin_fabs(fma(2.0, x1, x0) - tr));
+        const bool done = __builtin_fmax(__builtin_fabs(h0), __builtin_fabs(h1)) <=
+                          kHalleyOnly * dmin;
+        if (__builtin_expect(__all(done), 1)) {
+            l0 = x0;
+            l1 = x1;
+            l2 = (tr - l0) - l1;
+            return;
         }
     }
     // Newton: x -= f / f'
@@ -261,118 +388,84 @@ __device__ __forceinline__ void cubic_roots(double tr, double c1, double det, do
         const double r = recip_coarse(g0 * g1);
         x0 -= f0 * (g1 * r);
         x1 -= f1 * (g0 * r);
-        if (__builtin_fabsf(rf) > 1.0f - kUnresolved) x0 = __builtin_nan("");
+        // the FP64 tier's rule, so that both give NaN on the same events
+        // (every such lane's Halley step is large, so its wave comes here)
+        if (__builtin_fabsf(seed_angle(sc, A).r) > 1.0f - kUnresolved) x0 = __builtin_nan("");
     }
     l0 = x0;
     l1 = x1;
     l2 = (tr - l0) - l1;
 }
 
-// P(alpha -> beta) of one event.  The evolution operator over L is
-// sum_k exp(-i phi_k) X_k with the spectral projectors
-// X_k = (M - l_j)(M - l_l) / ((l_k - l_j)(l_k - l_l)); the common phase
-// exp(-i phi_0) drops out of |.|^2, so only the differences phi_k - phi_0
-// are formed.
-template <bool MIXED>
-__device__ __forceinline__ double event_prob(const SetConsts& sc, const Tables<MIXED>& T,
-                                             double kA, double kL, double E, uint32_t f,
-                                             const PolyRegs& pr = PolyRegs{})
+// P of one event in the FP32-mixed tier.  The evolution operator is sum_k
+// exp(-i phi_k) X_k with the spectral projectors X_k = (M - l_j)(M - l_l) /
+// ((l_k - l_j)(l_k - l_l)); the common phase exp(-i phi_0) drops out, and
+// the projectors sum to the identity, so S' = [a = b] + (exp(-i dphi1) - 1)
+// X1 + (exp(-i dphi2) - 1) X2.  Eigenvalues and phase differences are FP64,
+// the rest FP32.
+__device__ __forceinline__ double event_prob_mixed(const SetConsts& sc, const TileTablesMixed& T,
+                                                   double kA, double kL, double E, uint32_t f)
 {
-    using Entry = std::conditional_t<MIXED, ChanF, ChanL>;
-    using Real = std::conditional_t<MIXED, float, double>;
-    // flag byte (alpha bits 0-1, beta bits 2-3, antineutrino bit 4) -> the
-    // channel entry (conjugated for antineutrinos) and the sign of A
-    const FlagInfo fl = T.flag[min(f, uint32_t(kFlagEntries - 1))];
-    const Entry c = *reinterpret_cast<const Entry*>(
+    const FlagInfo fl = T.flag[min(f, uint32_t(kMixedFlags - 1))];
+    const ChanF c = *reinterpret_cast<const ChanF*>(
         reinterpret_cast<const unsigned char*>(T.ch) + fl.ch_off);
     const double A = flip_sign(kA * E, fl.sign);
-    const Real dba = c.dba;   // [alpha = beta]; NaN for an invalid flag byte
 
-    // amplitude inputs: M_ba and (M^2)_ba (FP32 in the mixed tier)
-    const auto mad = [](Real a, Real b, Real d) -> Real {
-        if constexpr (MIXED)
-            return __builtin_fmaf(a, b, d);
-        else
-            return __builtin_fma(a, b, d);
-    };
-    const Real Ar = Real(A);
-    const Real mre = mad(Ar, c.dee, c.m_re);
-    const Real mim = c.m_im;
-    const Real m2re = mad(Ar, mad(Ar, c.dee, c.g_re), c.m2_re);
-    const Real m2im = mad(Ar, c.g_im, c.m2_im);
+    // amplitude inputs: M_ba and (M^2)_ba
+    const float Ar = float(A);
+    const float mre = __builtin_fmaf(Ar, c.dee, c.m_re), mim = c.m_im;
+    const float m2re = __builtin_fmaf(Ar, __builtin_fmaf(Ar, c.dee, c.g_re), c.m2_re);
+    const float m2im = __builtin_fmaf(Ar, c.g_im, c.m2_im);
 
-    // matter eigenvalues (FP64 in every tier)
     double l0, l1, l2;
-    cubic_roots<MIXED>(sc.T0 + A, fma(A, sc.CA, sc.C0), A * sc.DA,
-                       fma(fma(A + sc.QH2, A, sc.QH1), A, sc.QH0), l0, l1, l2);
+    cubic_roots_mixed(sc, A, l0, l1, l2);
 
     const double d01 = l0 - l1, d02 = l0 - l2, d12 = l1 - l2;
     const double Q = d01 * d02 * d12;
     const double R = recip(E * Q);
     const double invE = Q * R, invQ = E * R;
-    // phase per eV^2 in units of pi/32 (FP64 tier) or of 2 pi (mixed tier)
-    const double ph = (MIXED ? kL * (1.0 / 64.0) : kL) * invE;
+    const double ph = kL * (1.0 / 64.0) * invE;   // phase per eV^2 in units of 2 pi
     // numerator coefficients: N_k = (M^2)_ba - (l_j + l_l) M_ba + l_j l_l [a = b]
-    // for k = 1, 2.  The projectors sum to the identity, so X0 = [a = b] -
-    // X1 - X2 and S' = [a = b] + (exp(-i dphi1) - 1) X1 + (exp(-i dphi2) - 1) X2;
-    // the projectors of a Hermitian matrix have entries of modulus <= 1, so
-    // forming cos - 1 costs nothing in absolute accuracy.
     const double u1 = l0 + l2, v1 = l0 * l2;
     const double u2 = l0 + l1, v2 = l0 * l1;
     const double iD1 = -d02 * invQ, iD2 = d01 * invQ;
 
-    double P;
-    if constexpr (!MIXED) {
-        double s1, e1, s2, e2;                        // sin and cos - 1
-        phase_sincos(-d01, ph, T.sct, s1, e1, pr.p7, pr.q6);   // phi_1 - phi_0
-        phase_sincos(-d02, ph, T.sct, s2, e2, pr.p7, pr.q6);   // phi_2 - phi_0
-        const double x1r = fma(v1, dba, fma(-u1, mre, m2re)) * iD1;
-        const double x1i = fma(-u1, mim, m2im) * iD1;
-        const double x2r = fma(v2, dba, fma(-u2, mre, m2re)) * iD2;
-        const double x2i = fma(-u2, mim, m2im) * iD2;
-        const double sr = dba + e1 * x1r + s1 * x1i + e2 * x2r + s2 * x2i;
-        const double si = e1 * x1i - s1 * x1r + e2 * x2i - s2 * x2r;
-        P = sr * sr + si * si;
-    } else {
-        float s1, c1, s2, c2;
-        phase_sincos_mixed(-d01, ph, s1, c1);
-        phase_sincos_mixed(-d02, ph, s2, c2);
-        if (__any(__builtin_fabs(A) > kMixedWideA)) {
-            // Matter terms well above the vacuum splittings: the projector
-            // numerators cancel over about |A| / dm^2_31, beyond what FP32
-            // resolves, so such waves form them and the sum in FP64 (from
-            // the same FP32 channel entries and FP32 phases).
-            const double d_dee = c.dee, d_dba = c.dba;
-            const double d_mre = fma(A, d_dee, double(c.m_re));
-            const double d_mim = c.m_im;
-            const double d_m2re = fma(A, fma(A, d_dee, double(c.g_re)), double(c.m2_re));
-            const double d_m2im = fma(A, double(c.g_im), double(c.m2_im));
-            const double x1r = fma(v1, d_dba, fma(-u1, d_mre, d_m2re)) * iD1;
-            const double x1i = fma(-u1, d_mim, d_m2im) * iD1;
-            const double x2r = fma(v2, d_dba, fma(-u2, d_mre, d_m2re)) * iD2;
-            const double x2i = fma(-u2, d_mim, d_m2im) * iD2;
-            const double e1 = double(c1) - 1.0, e2 = double(c2) - 1.0;
-            const double ds1 = s1, ds2 = s2;
-            const double sr = d_dba + e1 * x1r + ds1 * x1i + e2 * x2r + ds2 * x2i;
-            const double si = e1 * x1i - ds1 * x1r + e2 * x2i - ds2 * x2r;
-            return sr * sr + si * si;
-        }
-        // amplitude assembly in FP32 from FP32-rounded inputs
-        const float fmre = mre, fmim = mim, fm2re = m2re, fm2im = m2im;
-        const float fdba = dba;
-        const float fu1 = float(u1), fu2 = float(u2);
-        const float fv1 = float(v1), fv2 = float(v2);
-        const float fi1 = float(iD1), fi2 = float(iD2);
-        const float x1r = __builtin_fmaf(fv1, fdba, __builtin_fmaf(-fu1, fmre, fm2re)) * fi1;
-        const float x1i = __builtin_fmaf(-fu1, fmim, fm2im) * fi1;
-        const float x2r = __builtin_fmaf(fv2, fdba, __builtin_fmaf(-fu2, fmre, fm2re)) * fi2;
-        const float x2i = __builtin_fmaf(-fu2, fmim, fm2im) * fi2;
-        const float e1 = c1 - 1.0f, e2 = c2 - 1.0f;
-        const float sr = fdba + e1 * x1r + s1 * x1i + e2 * x2r + s2 * x2i;
-        const float si = e1 * x1i - s1 * x1r + e2 * x2i - s2 * x2r;
-        P = double(sr * sr + si * si);
+    float s1, c1, s2, c2;
+    phase_sincos_mixed(-d01, ph, s1, c1);
+    phase_sincos_mixed(-d02, ph, s2, c2);
+    if (__any(__builtin_fabs(A) > kMixedWideA)) {
+        // Matter terms well above the vacuum splittings: the projector
+        // numerators cancel over about |A| / dm^2_31, beyond what FP32
+        // resolves, so such waves form them and the sum in FP64 (from
+        // the same FP32 channel entries and FP32 phases).
+        const double d_dee = c.dee, d_dba = c.dba;
+        const double d_mre = fma(A, d_dee, double(c.m_re));
+        const double d_mim = c.m_im;
+        const double d_m2re = fma(A, fma(A, d_dee, double(c.g_re)), double(c.m2_re));
+        const double d_m2im = fma(A, double(c.g_im), double(c.m2_im));
+        const double x1r = fma(v1, d_dba, fma(-u1, d_mre, d_m2re)) * iD1;
+        const double x1i = fma(-u1, d_mim, d_m2im) * iD1;
+        const double x2r = fma(v2, d_dba, fma(-u2, d_mre, d_m2re)) * iD2;
+        const double x2i = fma(-u2, d_mim, d_m2im) * iD2;
+        const double e1 = double(c1) - 1.0, e2 = double(c2) - 1.0;
+        const double ds1 = s1, ds2 = s2;
+        const double sr = d_dba + e1 * x1r + ds1 * x1i + e2 * x2r + ds2 * x2i;
+        const double si = e1 * x1i - ds1 * x1r + e2 * x2i - ds2 * x2r;
+        return sr * sr + si * si;
     }
-    return P;
+    // amplitude assembly in FP32 from FP32-rounded inputs
+    const float fdba = c.dba;
+    const float fu1 = float(u1), fu2 = float(u2);
+    const float fv1 = float(v1), fv2 = float(v2);
+    const float fi1 = float(iD1), fi2 = float(iD2);
+    const float x1r = __builtin_fmaf(fv1, fdba, __builtin_fmaf(-fu1, mre, m2re)) * fi1;
+    const float x1i = __builtin_fmaf(-fu1, mim, m2im) * fi1;
+    const float x2r = __builtin_fmaf(fv2, fdba, __builtin_fmaf(-fu2, mre, m2re)) * fi2;
+    const float x2i = __builtin_fmaf(-fu2, mim, m2im) * fi2;
+    const float e1 = c1 - 1.0f, e2 = c2 - 1.0f;
+    const float sr = fdba + e1 * x1r + s1 * x1i + e2 * x2r + s2 * x2i;
+    const float si = e1 * x1i - s1 * x1r + e2 * x2i - s2 * x2r;
+    return double(sr * sr + si * si);
 }
 
 // P of one event through one constant-density layer: the policy the tile
@@ -385,7 +478,10 @@ struct ConstDensityProb {
     PolyRegs pr;
     __device__ __forceinline__ double operator()(double E, uint32_t f) const
     {
-        return event_prob<MIXED>(*sc, *tabs, kA, kL, E, f, pr);
+        if constexpr (MIXED)
+            return event_prob_mixed(*sc, *tabs, kA, kL, E, f);
+        else
+            return event_prob(*sc, *tabs, kA, kL, E, f, pr);
     }
 };
 
@@ -418,8 +514,8 @@ __device__ __forceinline__ double event_prob_layered(const SetConsts& sc, const 
     for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            hr[i][j] = T.ch[3 * i + j].m_re;
-            hi[i][j] = flip_sign(T.ch[3 * i + j].m_im, anti);
+            hr[i][j] = sc.ch[3 * i + j].m_re;
+            hi[i][j] = flip_sign(sc.ch[3 * i + j].m_im, anti);
         }
     double vr[3] = {a == 0u ? 1.0 : 0.0, a == 1u ? 1.0 : 0.0, a == 2u ? 1.0 : 0.0};
     double vi[3] = {0.0, 0.0, 0.0};
@@ -427,17 +523,17 @@ __device__ __forceinline__ double event_prob_layered(const SetConsts& sc, const 
     for (int layer = 0; layer < lp.n; ++layer) {
         const PathConsts pc = lp.layer[layer];
         const double A = flip_sign(pc.kA * E, anti);
-        double l0, l1, l2;
-        cubic_roots(sc.T0 + A, fma(A, sc.CA, sc.C0), A * sc.DA,
-                    fma(fma(A + sc.QH2, A, sc.QH1), A, sc.QH0), l0, l1, l2);
-        const double d01 = l0 - l1, d02 = l0 - l2, d12 = l1 - l2;
+        const Levels lv = matter_levels(sc, A);
+        const double rs = rsqrt_refined(lv.disc * (lv.fp * lv.fp));   // 1 / (sqrt(disc) f')
+        const double del = lv.disc * (rs * lv.fp) * (lv.disc * (rs * lv.fp) * rs);
+        const double b_ = fma(0.5, lv.e, lv.x), mu = -0.5 * lv.e;
+        const double l0 = lv.x, l1 = mu + del, l2 = mu - del;
+        const double d01 = b_ - del, d02 = b_ + del, d12 = 2.0 * del;
         const double invQ = recip(d01 * d02 * d12);
         const double ph = pc.kL * invE;
         double s1, c1, s2, c2;
-        phase_sincos(-d01, ph, T.sct, s1, c1);   // phi_1 - phi_0: sin, cos - 1
+        phase_sincos(-d01, ph, T.sct, s1, c1);   // phi_1 - phi_0
         phase_sincos(-d02, ph, T.sct, s2, c2);   // phi_2 - phi_0
-        c1 += 1.0;
-        c2 += 1.0;
         // c_k = exp(-i dphi_k) / D_k (c_0 real)
         const double iD0 = d12 * invQ, iD1 = -d02 * invQ, iD2 = d01 * invQ;
         const double k1r = c1 * iD1, k1i = -s1 * iD1;
@@ -871,45 +967,53 @@ __device__ __forceinline__ TileArrays tile_arrays(int64_t tile, int64_t n, const
     return a;
 }
 
-// Build the channel and flag tables of a parameter set in LDS (lanes 0-31
-// of the block's first wave; the caller's barrier publishes them).  The
-// mixed tier's tables hold the entries rounded to FP32.
-template <bool MIXED = false>
-__device__ __forceinline__ void load_tab(const SetConsts& sc, Tables<MIXED>& T, int lane)
+// Build the channel (and flag) tables of a parameter set in LDS (lanes 0-31
+// of the block's first wave; the caller's barrier publishes them).
+__device__ __forceinline__ void load_tab(const SetConsts& sc, TileTables& T, int lane)
 {
-    using Entry = std::conditional_t<MIXED, ChanF, ChanL>;
-    if (lane < kLdsChannels) {
-        ChanL e;
+    if (lane >= kFlagEntries) return;
+    const uint32_t f = uint32_t(lane);
+    const bool valid = (kValidFlags >> f) & 1u;
+    const uint32_t a = f & 3u, b = (f >> 2) & 3u;
+    const Chan c = sc.ch[valid ? 3u * b + a : 0u];
+    const double re = valid ? 1.0 : 0.0, im = (f & 16u) ? -re : re;
+    const int slot = lane + (lane >> 4);
+    T.m[slot] = {re * c.m_re, im * c.m_im};
+    T.m2[slot] = {re * c.m2_re, im * c.m2_im};
+    T.g[slot] = {re * c.g_re, im * c.g_im};
+    T.d[slot] = {re * c.dee, valid ? (a == b ? 1.0 : 0.0) : __builtin_nan("")};
+}
+
+__device__ __forceinline__ void load_tab(const SetConsts& sc, TileTablesMixed& T, int lane)
+{
+    if (lane < kMixedChannels) {
+        ChanF e;
         if (lane < kInvalidChannel) {
             const int k = lane % kChannels;
             const Chan c = sc.ch[k];
             const bool conj = lane >= kChannels;
-            e.m_re = c.m_re;
-            e.m_im = conj ? -c.m_im : c.m_im;
-            e.m2_re = c.m2_re;
-            e.m2_im = conj ? -c.m2_im : c.m2_im;
-            e.g_re = c.g_re;
-            e.g_im = conj ? -c.g_im : c.g_im;
-            e.dee = c.dee;
-            e.dba = (k % 3 == k / 3) ? 1.0 : 0.0;
+            e.m_re = float(c.m_re);
+            e.m_im = float(conj ? -c.m_im : c.m_im);
+            e.m2_re = float(c.m2_re);
+            e.m2_im = float(conj ? -c.m2_im : c.m2_im);
+            e.g_re = float(c.g_re);
+            e.g_im = float(conj ? -c.g_im : c.g_im);
+            e.dee = float(c.dee);
+            e.dba = (k % 3 == k / 3) ? 1.0f : 0.0f;
         } else {
-            e.m_re = e.m_im = e.m2_re = e.m2_im = e.g_re = e.g_im = e.dee = 0.0;
-            e.dba = __builtin_nan("");
+            e.m_re = e.m_im = e.m2_re = e.m2_im = e.g_re = e.g_im = e.dee = 0.0f;
+            e.dba = __builtin_nanf("");
         }
-        if constexpr (MIXED)
-            T.ch[lane] = ChanF{float(e.m_re), float(e.m_im), float(e.m2_re), float(e.m2_im),
-                               float(e.g_re), float(e.g_im), float(e.dee), float(e.dba)};
-        else
-            T.ch[lane] = e;
+        T.ch[lane] = e;
     }
-    if (lane < kFlagEntries) {
+    if (lane < kMixedFlags) {
         const uint32_t f = uint32_t(lane);
         const bool valid = (kValidFlags >> f) & 1u;
         const uint32_t anti = (f >> 4) & 1u;
         const uint32_t entry =
             valid ? (f & 3u) + 3u * ((f >> 2) & 3u) + anti * uint32_t(kChannels)
                   : uint32_t(kInvalidChannel);
-        T.flag[lane] = FlagInfo{entry * uint32_t(sizeof(Entry)), valid && anti ? 0x80000000u : 0u};
+        T.flag[lane] = FlagInfo{entry * uint32_t(sizeof(ChanF)), valid && anti ? 0x80000000u : 0u};
     }
 }
 

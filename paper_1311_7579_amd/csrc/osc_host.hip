@@ -75,6 +75,37 @@ void mixing_matrix(const osc_params& p, cplx U[3][3])
     U[2][2] = c23 * c13;
 }
 
+// The eigenvalue solver's constants (see SetConsts) from T0, C0, CA and DA,
+// in extended precision: their sums cancel.
+void seed_consts(osc::SetConsts& sc)
+{
+    typedef long double R;
+    const R T = sc.T0, C = sc.C0, a = sc.CA, d = sc.DA;
+    // p = tr^2 - 3 c1 = A^2 + p1 A + p0 about its minimum at A = -A0
+    const R p1 = 2.0L * T - 3.0L * a, p0 = T * T - 3.0L * C;
+    sc.A0 = static_cast<double>(0.5L * p1);
+    const R A0 = sc.A0;
+    sc.pm = static_cast<float>(p0 + A0 * (A0 - p1));
+    // q/2 = tr^3 - 4.5 tr c1 + 13.5 det = A^3 + q2 A^2 + q1 A + q0
+    const R q2 = 3.0L * T - 4.5L * a;
+    const R q1 = 3.0L * T * T - 4.5L * (C + T * a) + 13.5L * d;
+    const R q0 = T * (T * T - 4.5L * C);
+    sc.k1 = static_cast<float>(q1 + A0 * (3.0L * A0 - 2.0L * q2));
+    sc.k0 = static_cast<float>(q0 + A0 * (-q1 + A0 * (q2 - A0)));
+    sc.t3 = static_cast<float>((T - A0) / 3.0L);
+    // the discriminant tr^2 c1^2 - 4 c1^3 - 4 tr^3 det + 18 tr c1 det -
+    // 27 det^2 by powers of A, over 4
+    sc.D0 = static_cast<double>(0.25L * C * C * (T * T - 4.0L * C));
+    sc.D1 = static_cast<double>(0.25L * (2.0L * T * C * (C + T * a) - 12.0L * C * C * a -
+                                         4.0L * T * T * T * d + 18.0L * T * C * d));
+    sc.D2 = static_cast<double>(0.25L * (C * C + 4.0L * T * C * a + T * T * a * a -
+                                         12.0L * C * a * a - 12.0L * T * T * d +
+                                         18.0L * d * (C + T * a) - 27.0L * d * d));
+    sc.D3 = static_cast<double>(0.25L * (2.0L * C * a + 2.0L * T * a * a - 4.0L * a * a * a -
+                                         12.0L * T * d + 18.0L * a * d));
+    sc.D4 = static_cast<double>(0.25L * (a * a - 4.0L * d));
+}
+
 }  // namespace
 
 // Parameter-only quantities of one set for the kernels.
@@ -107,6 +138,7 @@ osc::SetConsts osc::host::set_consts(const osc_params& p)
     sc.QH2 = 3.0 * sc.T0 - 4.5 * sc.CA;
     sc.QH1 = 3.0 * sc.T0 * sc.T0 - 4.5 * (sc.C0 + sc.T0 * sc.CA) + 13.5 * sc.DA;
     sc.QH0 = sc.T0 * (sc.T0 * sc.T0 - 4.5 * sc.C0);
+    seed_consts(sc);
     for (int b = 0; b < 3; ++b)
         for (int a = 0; a < 3; ++a) {
             cplx g = 0.0;

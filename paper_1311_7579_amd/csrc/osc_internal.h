@@ -104,12 +104,20 @@ constexpr int kChannels = 9;   // index 3 beta + alpha
 
 // Parameter-only quantities of one oscillation parameter set.
 // Characteristic polynomial of M: x^3 - tr x^2 + c1 x - det with
-//   tr = T0 + A,  c1 = C0 + A CA,  det = A DA.
-// The trigonometric seed of its roots uses q/2 with q = 2 tr^3 - 9 tr c1 +
-// 27 det, expanded in A as q/2 = ((A + QH2) A + QH1) A + QH0.
+//   tr = T0 + A,  c1 = C0 + A CA,  det = A DA;
+// a quarter of its discriminant is the quartic (((D4 A + D3) A + D2) A +
+// D1) A + D0.  The FP32-mixed tier's seeds take q/2, q = 2 tr^3 - 9 tr c1 +
+// 27 det, as ((A + QH2) A + QH1) A + QH0; the FP64 tier's seed of the
+// isolated root works in FP32 in a = A + A0:
+//   p = tr^2 - 3 c1 = a^2 + pm,  q/2 = a^3 + k1 a + k0,  tr/3 = a/3 + t3
+// (A0 is minus the A of the smallest p, pm that p; the a^2 term of q/2
+// vanishes there).
 struct SetConsts {
     double T0, C0, CA, DA;
     double QH0, QH1, QH2;
+    double D0, D1, D2, D3, D4;
+    double A0;
+    float pm, k1, k0, t3;
     Chan ch[kChannels];
 };
 
@@ -120,11 +128,6 @@ struct SinCos {
 };
 struct SinCosTable {
     SinCos e[64];
-};
-// The LDS form of an anchor adds cm1 = c - 1, so that cos(phase) - 1 is
-// formed without cancellation.
-struct SinCosL {
-    double s, c, cm1;
 };
 
 // Path constants of one sample.
@@ -161,51 +164,57 @@ constexpr uint32_t kValidFlags = 0x07770777u;
 
 // Tables a per-event kernel keeps in LDS, built by each block from a
 // SetConsts and the SinCosTable:
-//  * ch: the channel table per (alpha, beta, antineutrino): entries
-//    3 beta + alpha for neutrinos, 9 + 3 beta + alpha for antineutrinos
-//    (complex conjugates: m_im, m2_im and g_im negated), each with
-//    dba = [alpha = beta]; entry 18 (invalid flag bytes) is zero with
-//    dba = NaN, so P comes out NaN;
-//  * flag: for each flag byte f < 32 the byte offset of its ch entry and
-//    the sign bit of A (set for antineutrinos); bytes >= 32 use entry 31,
-//    which is invalid;
-//  * sct: the phase sine/cosine anchors (24 B each: the table grows the
-//    per-wave LDS by 512 B, which still leaves room for the six waves per
-//    SIMD of a 50-bin histogram).
-// The per-event decode of a flag byte is then one min, one LDS read and one
-// XOR.
-struct ChanL {
-    double m_re, m_im;
-    double m2_re, m2_im;
-    double g_re, g_im;
-    double dee, dba;
-};
-constexpr int kLdsChannels = 2 * kChannels + 1;
-constexpr int kInvalidChannel = 2 * kChannels;
-constexpr int kFlagEntries = 32;
-struct FlagInfo {
-    uint32_t ch_off;   // byte offset into the table's ch array
-    uint32_t sign;     // 0 or 0x80000000: the sign bit of A
+//  * the channel entry of each flag byte below 28 (complex conjugates for
+//    antineutrinos: the imaginary parts negated), with dba = [alpha = beta];
+//    invalid flag bytes have a zero entry with dba = NaN, so P comes out
+//    NaN, and bytes >= 28 use entry 27, which is invalid.  An entry is cut
+//    into 16-byte parts, one array each; entry f sits at f + (f >> 4), so
+//    that the same channel of neutrinos and antineutrinos lies in different
+//    LDS banks (with entries 16 apart the benchmark step took 65.3 instead
+//    of 61.8 us);
+//  * sct: the phase sine/cosine anchors.
+// The decode of a flag byte is then one min, the entry's offset and, for
+// the sign of A, bit 4 moved to the sign bit.
+constexpr int kFlagEntries = 28;
+constexpr int kEntrySlots = kFlagEntries + 1;
+struct alignas(16) Pair {
+    double a, b;
 };
 struct TileTables {
-    ChanL ch[kLdsChannels];
-    FlagInfo flag[kFlagEntries];
-    SinCosL sct[64];
+    Pair m[kEntrySlots];    // M_ba of H0, real and imaginary part
+    Pair m2[kEntrySlots];   // (H0^2)_ba
+    Pair g[kEntrySlots];    // d(M^2)_ba / dA
+    Pair d[kEntrySlots];    // [a = b = e], [a = b]
+    SinCos sct[64];
 };
 
 // The FP32-mixed tier assembles the amplitude in FP32 from the same channel
 // entries rounded to FP32 (M_ba and (M^2)_ba are then formed from them in
 // FP32), and its phases use the hardware sine and cosine, so its tables
-// hold FP32 channel entries and no sin/cos anchors.
+// hold FP32 channel entries and no sin/cos anchors:
+//  * ch: entries 3 beta + alpha for neutrinos, 9 + 3 beta + alpha for
+//    antineutrinos; entry 18 (invalid flag bytes) is zero with dba = NaN;
+//  * flag: for each flag byte f < 32 the byte offset of its ch entry and
+//    the sign bit of A (set for antineutrinos); bytes >= 32 use entry 31,
+//    which is invalid.
+// (The FP64 tier's indexing by flag byte ran the mixed kernel 2 % slower:
+// its two 16-byte reads per event leave less to save.)
 struct ChanF {
     float m_re, m_im;
     float m2_re, m2_im;
     float g_re, g_im;
     float dee, dba;
 };
+constexpr int kMixedChannels = 2 * kChannels + 1;
+constexpr int kInvalidChannel = 2 * kChannels;
+constexpr int kMixedFlags = 32;
+struct FlagInfo {
+    uint32_t ch_off;   // byte offset into the table's ch array
+    uint32_t sign;     // 0 or 0x80000000: the sign bit of A
+};
 struct TileTablesMixed {
-    ChanF ch[kLdsChannels];
-    FlagInfo flag[kFlagEntries];
+    ChanF ch[kMixedChannels];
+    FlagInfo flag[kMixedFlags];
 };
 template <bool MIXED>
 struct TablesOf {

@@ -45,7 +45,7 @@ void tile_kernel(
     const int nbt = bc.nb + 2;
 
     if (MODE != kHist) {
-        load_tab<MIXED>(sc, tabs, lane);
+        load_tab(sc, tabs, lane);
         if constexpr (!MIXED) load_sincos(sctab, tabs, lane);
     }
     if (MODE != kReweight) hist_zero(hist, lane, nbt);

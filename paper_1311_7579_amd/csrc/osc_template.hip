@@ -131,7 +131,7 @@ __global__ __launch_bounds__(64) void centre_probs_kernel(SetConsts sc, SinCosTa
         E = tb.lo + off;
     }
     const uint32_t f = (c % 3u) | (((c / 3u) % 3u) << 2) | ((c / 9u) << 4);
-    P[k] = event_prob<false>(sc, tabs, pc.kA, pc.kL, E, f);
+    P[k] = event_prob(sc, tabs, pc.kA, pc.kL, E, f);
 }
 
 // hist[r] for one reconstructed bin per wave: lane l adds the terms

@@ -133,6 +133,46 @@ def test_near_level_crossings_within_bound(osc, ctx):
     assert checked == len(sets)
 
 
+@pytest.mark.parametrize("ordering", [1, -1], ids=["normal", "inverted"])
+def test_equally_spaced_eigenvalues(osc, ctx, ordering):
+    """Where the middle eigenvalue lies halfway between the others, the
+    eigenvalue that the solver treats as isolated changes from the highest to
+    the lowest.  Events at matter terms within 1e-12..1e-1 relative of such
+    points, on both sides, stay within the FP64 bound in every channel."""
+    p = dict(workload.TABLE1, dm2_32=ordering * workload.TABLE1["dm2_32"], delta_cp=0.7)
+    rho, ye = 3.0, 0.5
+    U = oracle.pmns(p)
+    H = (U * np.array([0.0, p["dm2_21"], p["dm2_21"] + p["dm2_32"]])) @ U.conj().T
+    lopsided = lambda A: np.dot(np.linalg.eigvalsh(H + np.diag([A, 0, 0])), [1.0, -2.0, 1.0])
+    grid = np.concatenate([-np.geomspace(1e-1, 1e-6, 2001), np.geomspace(1e-6, 1e-1, 2001)])
+    f = np.array([lopsided(A) for A in grid])
+    roots = []
+    for k in np.nonzero(np.sign(f[1:]) != np.sign(f[:-1]))[0]:
+        lo, hi = grid[k], grid[k + 1]
+        if lo * hi < 0:
+            continue
+        for _ in range(60):
+            mid = 0.5 * (lo + hi)
+            lo, hi = (mid, hi) if np.sign(lopsided(mid)) == np.sign(lopsided(lo)) else (lo, mid)
+        roots.append(lo)
+    assert roots
+    rng = np.random.default_rng(17)
+    n = 4000
+    ctx.osc_set_params([p])
+    for a0 in roots:
+        A = a0 * (1 + 10 ** rng.uniform(-12, -1, n) * np.where(rng.random(n) < 0.5, -1, 1))
+        e = np.abs(A) / (oracle.k_matter() * ye * rho)
+        fl = workload.make_flags(rng.integers(0, 3, n), rng.integers(0, 3, n), A < 0)
+        for L in (295.0, 2500.0):
+            ds = osc.DeviceSample.from_host(
+                workload.Sample(e, fl, np.ones(n), e.copy(), L_km=L, rho_gcc=rho, Ye=ye))
+            out = torch.empty(n, dtype=torch.float64, device="cuda")
+            ctx.osc_reweight(ds, 0, out)
+            want = oracle.prob_batch(p, L, rho, ye, e, fl)
+            ratio = np.abs(out.cpu().numpy() - want) / fp64_bound(p, L, rho, ye, e, fl)
+            assert ratio.max() <= 1.0, (a0, L, float(ratio.max()))
+
+
 def brute_force_prob(p, L, rho, ye, e, f):
     """P from an eigendecomposition of the flavour-basis matrix (numpy
     eigh, accurate however close the eigenvalues are)."""
