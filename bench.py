@@ -49,19 +49,19 @@ SETTLE_S = 0.1   # untimed load before the warm-up steps (clock settle)
 # (scale, offset, quotient, floor).
 FLOPS_PER_EVENT = 154
 FLOPS_PER_EVENT_COMPUTED_BINS = 158
-# Layered path, per layer: matter term 1, the isolated root and the
-# discriminant 33 (as above), del 15, the three roots 5, differences and 1/Q
-# 12, phase scale 1, two sines and cosines 52,
-# c_k 7, eigenvalue sums and products 6, polynomial coefficients a2, a1, a0
-# 19, y = M v 74, z = M y 74, v = a2 z + a1 y + a0 v 66: 365.  The first
-# layer forms y as column alpha of M (2 instead of 74), the last only
-# component beta of z and v (26 + 22 instead of 74 + 66); per event 1/E 7,
-# |v_beta|^2 3 and the weighted add 2.
-LAYER_FLOPS = 365
+# Layered path, per layer solved: matter term 1, the isolated root and the
+# discriminant 33 (as above), 1/f', del and 1/del 15, root difference and
+# phase scale 3, two sines and cosines 52, the operator's coefficients 18;
+# per vector taken through a layer: y = N v 22, t = kappa y - i s v 30, c0 v
+# 18, N t 28; per event 1/E 7, u . v 24, |S|^2 3 and the weighted add 2.  A
+# path that reads the same from both ends solves its first half only.
+LAYER_SOLVE_FLOPS = 122
+LAYER_VECTOR_FLOPS = 98
 
 
-def layered_flops_per_event(n_layers):
-    return LAYER_FLOPS * n_layers - 72 - 92 + 12
+def layered_flops_per_event(n_layers, mirrored):
+    solved = (n_layers + 1) // 2 if mirrored else n_layers
+    return LAYER_SOLVE_FLOPS * solved + LAYER_VECTOR_FLOPS * n_layers + 36
 
 
 # FP64 vector peak: 256 CUs x 4 SIMDs x 16 lanes x 2 flop (FMA) x 2.4 GHz.
@@ -79,12 +79,12 @@ KERNEL_SOURCES = ("paper_1311_7579_amd/csrc/osc_device.h",
                   "paper_1311_7579_amd/csrc/osc_kernels.hip",
                   "paper_1311_7579_amd/build.py")
 COUNTER_TRAFFIC = {
-    "fetch_kib": 92843.9, "fetch_scale": 2.0,     # copy of 512 MiB: FETCH_SIZE 262157 KiB
-    "write_kib": 82424.3, "write_scale": 1.0,     # copy of 512 MiB: WRITE_SIZE 524288 KiB
+    "fetch_kib": 92854.8, "fetch_scale": 2.0,     # copy of 512 MiB: FETCH_SIZE 262157 KiB
+    "write_kib": 82418.1, "write_scale": 1.0,     # copy of 512 MiB: WRITE_SIZE 524288 KiB
     "valu_per_event": 144.9,
     "classes_per_event": {"fp64": 95.9, "fp64_trans": 1.0, "fp32": 19.0, "fp32_trans": 2.0,
                           "cvt": 3.0, "int32": 6.38, "int64": 0.375, "other": 17.25},
-    "source_sha256": "73a9e42ec6fbc40ac5f3d96abf886bfdd0acf4ecf7df17e2a872a7baf655b239",
+    "source_sha256": "b0b905f07309da22babf394a4edafffa2783884e3fa351c48f0a421079ce9c1a",
 }
 # Issue time of one wave instruction on one SIMD, measured on the box with
 # probe kernels of independent chains (ns): FP64 FMA/MUL/ADD 2.08, FP32
@@ -432,7 +432,7 @@ def layered_form(osc, ctx, n=10_000_000, reps=20):
     ev_ms, ev_n, _, _ = ctx.osc_profile_read()
     ctx.osc_profile_enable(False)
     kernel_ms = ev_ms / max(ev_n, 1)
-    flops = layered_flops_per_event(len(earth))
+    flops = layered_flops_per_event(len(earth), earth == earth[::-1])
     tflops = flops * n / (kernel_ms * 1e-3) / 1e12
     return {"config": "5-layer Earth path (11600 km), 1e7 events, E log-uniform 0.5-20 GeV, "
                       "all channels, FP64, 50 bins",

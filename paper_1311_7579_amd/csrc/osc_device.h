@@ -67,7 +67,8 @@ __device__ __forceinline__ void phase_sincos(double a, double b, const SinCos* _
 }
 
 // Copy the sin/cos anchors into LDS (the 64 lanes of a wave, one each).
-__device__ __forceinline__ void load_sincos(const SinCosTable& t, TileTables& T, int lane)
+template <class Tab>
+__device__ __forceinline__ void load_sincos(const SinCosTable& t, Tab& T, int lane)
 {
     if (lane < 64) T.sct[lane] = t.e[lane];
 }
@@ -487,134 +488,117 @@ struct ConstDensityProb {
 
 // P(alpha -> beta) of one event through layers of constant density.  The
 // evolution operator of the path is the product of the layers' operators,
-// so only column alpha of it is needed: v = e_alpha is propagated layer by
-// layer.  Within a layer, exp(-i M L / 2E) (common phase dropped) is the
-// polynomial a2 M^2 + a1 M + a0 of its Lagrange form over the eigenvalues,
-//   sum_k c_k (M - l_j)(M - l_l),  c_k = exp(-i dphi_k) / D_k,
-// so v becomes a2 (M M v) + a1 (M v) + a0 v.  M is the flavour-basis mass
-// matrix of the layer (H0 + A e_e e_e^T, conjugated with A -> -A for
-// antineutrinos); its entries come from the channel table.  In the first
-// layer v = e_alpha, so M v is column alpha of M; in the last layer only
-// component beta of the new v is formed.  Both give the same roundings as
-// the full products.
-__device__ __forceinline__ double pick3(uint32_t k, double x0, double x1, double x2)
+// so only column alpha of it is needed: v = <basis|alpha> is propagated layer
+// by layer, in the basis where M is real and tridiagonal (Tridiagonal).
+// Antineutrinos: the operators are the complex conjugates of those of H0 -
+// |A| e_e e_e^T with the phases reversed, and |S|^2 is that of the conjugate.
+//
+// With N = M - mu, the operator of one layer is, up to a phase (notation of
+// event_prob; its eigenvalues on N are b and +-del),
+//   cos psi - i (sin psi / del) N + kappa (N^2 - del^2)
+//     = c0 + N (kappa N - i s),   s = sin psi / del,
+//   kappa = (exp(-i theta) - cos psi + i s b) / f'(x),  c0 = cos psi - kappa del^2,
+// two products with a real tridiagonal matrix per vector.
+//
+// M is symmetric, so every layer's operator is, and a path that reads the
+// same from both ends gives S = T^T T or T^T S_mid T with T the first
+// half's operator: S_beta,alpha = (T beta) . (S_mid T alpha).  Both vectors go
+// through each layer of the first half with one set of coefficients.
+//
+// Bound by VALU issue: about 95 FP64 issue slots for a layer's coefficients
+// and 58 for each vector through it.  With complex 3x3 products in the
+// flavour basis and every layer solved, 1e7 events took 424 us through the
+// five-layer Earth path (now 229) and 3e6 events 300 us through 12 layers
+// (now 137).
+struct Vec3 {
+    double r[3], i[3];
+};
+
+struct LayerOp {
+    double p0, p1, p2, b0, b1;   // N
+    double c0r, c0i, s, kr, ki;
+};
+
+// N u + start, component by component (real part or imaginary part).
+__device__ __forceinline__ void add_times(const LayerOp& o, const double (&u)[3], double (&d)[3])
 {
-    return k == 0u ? x0 : (k == 1u ? x1 : x2);
+    d[0] = fma(o.p0, u[0], fma(o.b0, u[1], d[0]));
+    d[1] = fma(o.p1, u[1], fma(o.b0, u[0], fma(o.b1, u[2], d[1])));
+    d[2] = fma(o.p2, u[2], fma(o.b1, u[1], d[2]));
 }
 
-__device__ __forceinline__ double event_prob_layered(const SetConsts& sc, const TileTables& T,
+__device__ __forceinline__ void propagate(const LayerOp& o, Vec3& v)
+{
+    Vec3 y, t;
+    y.r[0] = fma(o.p0, v.r[0], o.b0 * v.r[1]);
+    y.i[0] = fma(o.p0, v.i[0], o.b0 * v.i[1]);
+    y.r[1] = fma(o.p1, v.r[1], fma(o.b0, v.r[0], o.b1 * v.r[2]));
+    y.i[1] = fma(o.p1, v.i[1], fma(o.b0, v.i[0], o.b1 * v.i[2]));
+    y.r[2] = fma(o.p2, v.r[2], o.b1 * v.r[1]);
+    y.i[2] = fma(o.p2, v.i[2], o.b1 * v.i[1]);
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        t.r[j] = fma(o.s, v.i[j], fma(o.kr, y.r[j], -(o.ki * y.i[j])));
+        t.i[j] = fma(-o.s, v.r[j], fma(o.kr, y.i[j], o.ki * y.r[j]));
+        const double r = fma(o.c0r, v.r[j], -(o.c0i * v.i[j]));
+        v.i[j] = fma(o.c0r, v.i[j], o.c0i * v.r[j]);
+        v.r[j] = r;
+    }
+    add_times(o, t.r, v.r);
+    add_times(o, t.i, v.i);
+}
+
+__device__ __forceinline__ double event_prob_layered(const SetConsts& sc, const LayeredTables& T,
                                                      const LayerPath& lp, double E, uint32_t f)
 {
-    const bool valid = (f < 32u) && ((kValidFlags >> (f & 31u)) & 1u);
-    const uint32_t a = min(f & 3u, 2u), b = min((f >> 2) & 3u, 2u);
-    const uint32_t anti = (f << 27) & 0x80000000u;
-    // H0 (conjugated for antineutrinos), row-major; the diagonal is real
-    double hr[3][3], hi[3][3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            hr[i][j] = sc.ch[3 * i + j].m_re;
-            hi[i][j] = flip_sign(sc.ch[3 * i + j].m_im, anti);
-        }
-    double vr[3] = {a == 0u ? 1.0 : 0.0, a == 1u ? 1.0 : 0.0, a == 2u ? 1.0 : 0.0};
-    double vi[3] = {0.0, 0.0, 0.0};
-    const double invE = recip(E);
-    for (int layer = 0; layer < lp.n; ++layer) {
-        const PathConsts pc = lp.layer[layer];
-        const double A = flip_sign(pc.kA * E, anti);
+    const uint32_t fv = f < 32u ? f : 3u;   // invalid bytes take the NaN row
+    const double(&wa)[5] = T.w[fv & 3u];
+    const double(&wb)[5] = T.w[(fv >> 2) & 3u];
+    Vec3 v{{wa[0], wa[1], wa[3]}, {0.0, -wa[2], -wa[4]}};
+    Vec3 u{{wb[0], wb[1], wb[3]}, {0.0, wb[2], wb[4]}};
+    const double invE = matter_term(1.0, recip(E), f);   // negative for antineutrinos
+    for (int k = 0; k < lp.n; ++k) {
+        const PathConsts pc = lp.layer[k];
+        const double A = matter_term(pc.kA, E, f);
         const Levels lv = matter_levels(sc, A);
-        const double rs = rsqrt_refined(lv.disc * (lv.fp * lv.fp));   // 1 / (sqrt(disc) f')
-        const double del = lv.disc * (rs * lv.fp) * (lv.disc * (rs * lv.fp) * rs);
-        const double b_ = fma(0.5, lv.e, lv.x), mu = -0.5 * lv.e;
-        const double l0 = lv.x, l1 = mu + del, l2 = mu - del;
-        const double d01 = b_ - del, d02 = b_ + del, d12 = 2.0 * del;
-        const double invQ = recip(d01 * d02 * d12);
+        const double y = rsqrt_refined(lv.disc * (lv.fp * lv.fp));   // 1 / (sqrt(disc) f')
+        const double yf = y * lv.fp;                                 // 1 / sqrt(disc)
+        const double sd = lv.disc * yf;
+        const double inv_fp = y * sd;
+        const double del = sd * inv_fp;
+        const double b = fma(0.5, lv.e, lv.x);
         const double ph = pc.kL * invE;
         double s1, c1, s2, c2;
-        phase_sincos(-d01, ph, T.sct, s1, c1);   // phi_1 - phi_0
-        phase_sincos(-d02, ph, T.sct, s2, c2);   // phi_2 - phi_0
-        // c_k = exp(-i dphi_k) / D_k (c_0 real)
-        const double iD0 = d12 * invQ, iD1 = -d02 * invQ, iD2 = d01 * invQ;
-        const double k1r = c1 * iD1, k1i = -s1 * iD1;
-        const double k2r = c2 * iD2, k2i = -s2 * iD2;
-        const double u0 = l1 + l2, u1 = l0 + l2, u2 = l0 + l1;
-        const double w0 = l1 * l2, w1 = l0 * l2, w2 = l0 * l1;
-        const double a2r = iD0 + k1r + k2r, a2i = k1i + k2i;
-        const double a1r = -(iD0 * u0 + k1r * u1 + k2r * u2), a1i = -(k1i * u1 + k2i * u2);
-        const double a0r = iD0 * w0 + k1r * w1 + k2r * w2, a0i = k1i * w1 + k2i * w2;
-        // y = M v
-        double yr[3], yi[3], zr[3], zi[3];
-        if (layer == 0) {
-            // v = e_alpha: column alpha of H0, plus A on the (e, e) entry
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                yr[i] = pick3(a, hr[i][0], hr[i][1], hr[i][2]);
-                yi[i] = pick3(a, hi[i][0], hi[i][1], hi[i][2]);
-            }
-            yr[0] = fma(A, vr[0], yr[0]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                double sr = (i == 0) ? A * vr[0] : 0.0, si = (i == 0) ? A * vi[0] : 0.0;
-#pragma unroll
-                for (int j = 0; j < 3; ++j) {
-                    sr = fma(hr[i][j], vr[j], fma(-hi[i][j], vi[j], sr));
-                    si = fma(hr[i][j], vi[j], fma(hi[i][j], vr[j], si));
-                }
-                yr[i] = sr;
-                yi[i] = si;
-            }
-        }
-        if (layer == lp.n - 1) {
-            // component beta of a2 (M y) + a1 y + a0 v: row beta of M
-            double sr = (b == 0u) ? A * yr[0] : 0.0, si = (b == 0u) ? A * yi[0] : 0.0;
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                const double mr = pick3(b, hr[0][j], hr[1][j], hr[2][j]);
-                const double mi = pick3(b, hi[0][j], hi[1][j], hi[2][j]);
-                sr = fma(mr, yr[j], fma(-mi, yi[j], sr));
-                si = fma(mr, yi[j], fma(mi, yr[j], si));
-            }
-            const double ybr = pick3(b, yr[0], yr[1], yr[2]), ybi = pick3(b, yi[0], yi[1], yi[2]);
-            const double vbr = pick3(b, vr[0], vr[1], vr[2]), vbi = pick3(b, vi[0], vi[1], vi[2]);
-            const double nr = a2r * sr - a2i * si + a1r * ybr - a1i * ybi + a0r * vbr - a0i * vbi;
-            const double ni = a2r * si + a2i * sr + a1r * ybi + a1i * ybr + a0r * vbi + a0i * vbr;
-            vr[0] = nr;
-            vi[0] = ni;
-            break;
-        }
-        // z = M y
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            double sr = (i == 0) ? A * yr[0] : 0.0, si = (i == 0) ? A * yi[0] : 0.0;
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                sr = fma(hr[i][j], yr[j], fma(-hi[i][j], yi[j], sr));
-                si = fma(hr[i][j], yi[j], fma(hi[i][j], yr[j], si));
-            }
-            zr[i] = sr;
-            zi[i] = si;
-        }
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const double nr = a2r * zr[i] - a2i * zi[i] + a1r * yr[i] - a1i * yi[i] +
-                              a0r * vr[i] - a0i * vi[i];
-            const double ni = a2r * zi[i] + a2i * zr[i] + a1r * yi[i] + a1i * yr[i] +
-                              a0r * vi[i] + a0i * vr[i];
-            vr[i] = nr;
-            vi[i] = ni;
-        }
+        phase_sincos(b, ph, T.sct, s1, c1);     // theta
+        phase_sincos(del, ph, T.sct, s2, c2);   // psi
+        LayerOp o;
+        o.s = s2 * (lv.fp * yf);
+        o.kr = (c1 - c2) * inv_fp;
+        o.ki = fma(o.s, b, -s1) * inv_fp;
+        const double del2 = del * del;
+        o.c0r = fma(-o.kr, del2, c2);
+        o.c0i = -(o.ki * del2);
+        o.p0 = fma(0.5, lv.e, lp.tri.a0 + A);
+        o.p1 = fma(0.5, lv.e, lp.tri.a1);
+        o.p2 = fma(0.5, lv.e, lp.tri.a2);
+        o.b0 = lp.tri.b0;
+        o.b1 = lp.tri.b1;
+        propagate(o, v);
+        if (k < lp.pairs) propagate(o, u);
     }
-    // the last layer left component beta in vr[0], vi[0]
-    const double P = vr[0] * vr[0] + vi[0] * vi[0];
-    return __hiloint2double(valid ? __double2hiint(P) : 0x7ff80000, __double2loint(P));
+    double zr = 0.0, zi = 0.0;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        zr = fma(u.r[j], v.r[j], fma(-u.i[j], v.i[j], zr));
+        zi = fma(u.r[j], v.i[j], fma(u.i[j], v.r[j], zi));
+    }
+    return fma(zi, zi, zr * zr);
 }
 
 // P of one event through a layered path (FP64).
 struct LayeredProb {
     const SetConsts* sc;
-    const TileTables* tabs;
+    const LayeredTables* tabs;
     const LayerPath* lp;
     __device__ __forceinline__ double operator()(double E, uint32_t f) const
     {
@@ -982,6 +966,14 @@ __device__ __forceinline__ void load_tab(const SetConsts& sc, TileTables& T, int
     T.m2[slot] = {re * c.m2_re, im * c.m2_im};
     T.g[slot] = {re * c.g_re, im * c.g_im};
     T.d[slot] = {re * c.dee, valid ? (a == b ? 1.0 : 0.0) : __builtin_nan("")};
+}
+
+__device__ __forceinline__ void load_tab(const LayerPath& lp, LayeredTables& T, int lane)
+{
+    if (lane < 20) {
+        const int row = lane / 5, col = lane % 5;
+        T.w[row][col] = row < 3 ? lp.tri.w[row][col] : __builtin_nan("");
+    }
 }
 
 __device__ __forceinline__ void load_tab(const SetConsts& sc, TileTablesMixed& T, int lane)

@@ -106,6 +106,41 @@ void seed_consts(osc::SetConsts& sc)
     sc.D4 = static_cast<double>(0.25L * (a * a - 4.0L * d));
 }
 
+// H0 in the layered path's real tridiagonal basis (see Tridiagonal).
+void tridiagonal_consts(const osc_params& p, osc::Tridiagonal& t)
+{
+    const double s12 = std::sqrt(p.sin2_th12), c12 = std::sqrt(1.0 - p.sin2_th12);
+    const double s23 = std::sqrt(p.sin2_th23), c23 = std::sqrt(1.0 - p.sin2_th23);
+    const double s13 = std::sqrt(p.sin2_th13), c13 = std::sqrt(1.0 - p.sin2_th13);
+    // O = R13 R12, K = O diag(0, dm21, dm31) O^T
+    const double O[3][3] = {{c13 * c12, c13 * s12, s13},
+                            {-s12, c12, 0.0},
+                            {-s13 * c12, -s13 * s12, c13}};
+    const double lv[3] = {0.0, p.dm2_21, p.dm2_32 + p.dm2_21};
+    double K[3][3];
+    for (int i = 0; i < 3; ++i)
+        for (int j = 0; j < 3; ++j) {
+            K[i][j] = 0.0;
+            for (int k = 1; k < 3; ++k) K[i][j] += lv[k] * O[i][k] * O[j][k];
+        }
+    // rotate axes 1 and 2 so that K[0][2] vanishes
+    const double h = std::hypot(K[0][1], K[0][2]);
+    const double c = h > 0.0 ? K[0][1] / h : 1.0, s = h > 0.0 ? K[0][2] / h : 0.0;
+    t.a0 = K[0][0];
+    t.b0 = h;
+    t.a1 = c * c * K[1][1] + 2.0 * c * s * K[1][2] + s * s * K[2][2];
+    t.a2 = s * s * K[1][1] - 2.0 * c * s * K[1][2] + c * c * K[2][2];
+    t.b1 = (c * c - s * s) * K[1][2] + c * s * (K[2][2] - K[1][1]);
+    // rows of R23 diag(1, 1, e^{i delta}) times that rotation
+    const cplx ep = std::polar(1.0, p.delta_cp);
+    const cplx row[3][2] = {{0.0, 0.0}, {c23, s23 * ep}, {-s23, c23 * ep}};
+    for (int f = 0; f < 3; ++f) {
+        const cplx w1 = c * row[f][0] + s * row[f][1], w2 = c * row[f][1] - s * row[f][0];
+        const double w[5] = {f == 0 ? 1.0 : 0.0, w1.real(), w1.imag(), w2.real(), w2.imag()};
+        std::copy(w, w + 5, t.w[f]);
+    }
+}
+
 }  // namespace
 
 // Parameter-only quantities of one set for the kernels.
@@ -681,13 +716,24 @@ bool layers_ok(const osc_layer* layers, int32_t n_layers)
     return true;
 }
 
-osc::LayerPath layer_path(const osc_layer* layers, int32_t n_layers)
+osc::LayerPath layer_path(const osc_params& p, const osc_layer* layers, int32_t n_layers)
 {
     osc::LayerPath lp{};
     lp.n = n_layers;
+    tridiagonal_consts(p, lp.tri);
     for (int32_t j = 0; j < n_layers; ++j)
         lp.layer[j] = osc::PathConsts{matter_constant() * layers[j].Ye * layers[j].rho_gcc,
                                       phase_steps(layers[j].L_km)};
+    // a path that reads the same from both ends: its first half, crossed twice
+    bool mirrored = true;
+    for (int32_t j = 0; j < n_layers / 2; ++j) {
+        const osc::PathConsts &a = lp.layer[j], &b = lp.layer[n_layers - 1 - j];
+        mirrored = mirrored && a.kA == b.kA && a.kL == b.kL;
+    }
+    if (mirrored) {
+        lp.pairs = n_layers / 2;
+        lp.n = n_layers - lp.pairs;
+    }
     return lp;
 }
 
@@ -706,7 +752,7 @@ osc_status osc_reweight_layered(osc_ctx* ctx, const osc_sample* sample, const os
     const hipStream_t hs = static_cast<hipStream_t>(stream);
     ProfRec* pr = prof_begin(ctx, hs);
     const hipError_t e = osc::launch_layered_tiles(
-        0, true, ctx->consts[size_t(set)], layer_path(layers, n_layers), bc, sample->n,
+        0, true, ctx->consts[size_t(set)], layer_path(ctx->params[size_t(set)], layers, n_layers), bc, sample->n,
         sample->e_true, sample->flags, nullptr, nullptr, p_out, nullptr, hs,
         pr ? pr->start : nullptr, pr ? pr->mid : nullptr);
     if (pr) {
@@ -726,7 +772,7 @@ osc_status osc_fill_pdf_layered(osc_ctx* ctx, const osc_sample* sample, const os
     std::lock_guard<std::mutex> lock(ctx->mu);
     if (set < 0 || size_t(set) >= ctx->consts.size()) return OSC_ERR_INVALID_ARG;
     if (hipSetDevice(ctx->device) != hipSuccess) return OSC_ERR_DEVICE;
-    const osc::LayerPath lp = layer_path(layers, n_layers);
+    const osc::LayerPath lp = layer_path(ctx->params[size_t(set)], layers, n_layers);
     return run_hist(ctx, 1, p_out != nullptr, false, ctx->consts[size_t(set)], osc::PathConsts{},
                     bin_consts(binning), sample->n, sample->e_true, sample->flags,
                     sample->weight, sample->e_reco, nullptr, nullptr, p_out, hist_out,

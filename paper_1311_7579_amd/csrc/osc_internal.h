@@ -32,7 +32,7 @@ constexpr int kLaneShare = kTileLanes / kHistLanes;
 #endif
 constexpr int kTileWavesPerSimd = OSC_TILE_WAVES;
 constexpr int kBatchWavesPerSimd = 4;
-constexpr int kLayeredWavesPerSimd = 3;
+constexpr int kLayeredWavesPerSimd = 3;   // 4 and 5 run within 1 % of it
 
 // Largest event count accepted.
 constexpr int64_t kMaxEvents = int64_t(1) << 32;
@@ -102,6 +102,18 @@ struct Chan {
 
 constexpr int kChannels = 9;   // index 3 beta + alpha
 
+// H0 in the real basis of the layered path.  With U = W O, W = R23
+// diag(1, 1, e^{i delta}) and O real (up to column phases, which drop out),
+// W^+ H0 W is real symmetric, and a rotation of its last two axes, on which
+// A e_e e_e^T does not act, clears its (0, 2) entry:
+//   M = [[a0 + A, b0, 0], [b0, a1, b1], [0, b1, a2]].
+// w[f] is row f of the basis, <f| in it: (1, 0, 0) for nu_e, (0, w1, w2)
+// (complex) for nu_mu and nu_tau.
+struct Tridiagonal {
+    double a0, a1, a2, b0, b1;
+    double w[3][5];   // [flavour]: w0, Re w1, Im w1, Re w2, Im w2
+};
+
 // Parameter-only quantities of one oscillation parameter set.
 // Characteristic polynomial of M: x^3 - tr x^2 + c1 x - det with
 //   tr = T0 + A,  c1 = C0 + A CA,  det = A DA;
@@ -138,10 +150,13 @@ struct PathConsts {
 };
 
 // A path of piecewise-constant density: layers in the order the neutrino
-// crosses them, each with its own PathConsts.
+// crosses them, each with its own PathConsts.  A path that reads the same
+// from both ends (as paths through the Earth do) is given as its first half:
+// the first `pairs` layers are crossed again, in reverse, after the last.
 constexpr int kMaxLayers = 32;
 struct LayerPath {
-    int32_t n;
+    int32_t n, pairs;
+    Tridiagonal tri;
     PathConsts layer[kMaxLayers];
 };
 
@@ -185,6 +200,13 @@ struct TileTables {
     Pair m2[kEntrySlots];   // (H0^2)_ba
     Pair g[kEntrySlots];    // d(M^2)_ba / dA
     Pair d[kEntrySlots];    // [a = b = e], [a = b]
+    SinCos sct[64];
+};
+
+// Tables of the layered kernel: the basis rows of the flavours (see
+// Tridiagonal; row 3, for invalid flavours, is NaN) and the anchors.
+struct LayeredTables {
+    double w[4][5];
     SinCos sct[64];
 };
 

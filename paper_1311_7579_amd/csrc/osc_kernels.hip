@@ -68,12 +68,8 @@ void tile_kernel(
 }
 
 // The same tile body with P through a layered path (FP64 only).  The event
-// loop stays rolled: the layer loop is large, and 16 unrolled copies of it
-// would not fit the instruction cache.
-#ifndef OSC_LAYERED_ROLL
-#define OSC_LAYERED_ROLL 1
-#endif
-constexpr bool kLayeredRoll = OSC_LAYERED_ROLL;
+// loop stays rolled: 16 unrolled copies of the layer loop would not fit the
+// instruction cache.
 template <int MODE, bool WRITE_P>
 __global__ __launch_bounds__(kTileLanes) __attribute__((amdgpu_waves_per_eu(kLayeredWavesPerSimd)))
 void layered_tile_kernel(SetConsts sc, SinCosTable sctab, LayerPath lp, BinConsts bc, int64_t n,
@@ -82,13 +78,13 @@ void layered_tile_kernel(SetConsts sc, SinCosTable sctab, LayerPath lp, BinConst
                          double* __restrict__ p_out, double* __restrict__ partial)
 {
     extern __shared__ double hist[];
-    __shared__ TileTables tabs;
+    __shared__ LayeredTables tabs;
 
     const int lane = threadIdx.x;
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
     const int nbt = bc.nb + 2;
 
-    load_tab(sc, tabs, lane);
+    load_tab(lp, tabs, lane);
     load_sincos(sctab, tabs, lane);
     if (MODE != kReweight) hist_zero(hist, lane, nbt);
     __syncthreads();
@@ -97,10 +93,10 @@ void layered_tile_kernel(SetConsts sc, SinCosTable sctab, LayerPath lp, BinConst
     const TileArrays t =
         tile_arrays(tile, n, e_true, flags, weight, e_reco, nullptr, nullptr, p_out);
     if (t.n == kTileEvents)
-        tile_events<MODE, WRITE_P, true, kLayeredRoll>(prob, bc, hist, lane, t.n, t.e_true, t.flags,
+        tile_events<MODE, WRITE_P, true, true>(prob, bc, hist, lane, t.n, t.e_true, t.flags,
                                                        t.weight, t.e_reco, nullptr, nullptr, t.p_out);
     else
-        tile_events<MODE, WRITE_P, false, kLayeredRoll>(prob, bc, hist, lane, t.n, t.e_true, t.flags,
+        tile_events<MODE, WRITE_P, false, true>(prob, bc, hist, lane, t.n, t.e_true, t.flags,
                                                         t.weight, t.e_reco, nullptr, nullptr, t.p_out);
 
     if (MODE != kReweight) {

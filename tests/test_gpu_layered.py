@@ -81,6 +81,39 @@ def test_reweight_layered_against_oracle(osc, ctx, name):
         assert np.abs(got - want).max() <= P_TOL, (name, k)
 
 
+@pytest.mark.parametrize("n_layers", [2, 3, 31, 32])
+@pytest.mark.parametrize("mirrored", [True, False], ids=["mirrored", "last layer differs"])
+def test_mirrored_paths_against_oracle(osc, ctx, n_layers, mirrored):
+    """A path that reads the same from both ends is crossed as its first half
+    from both sides; with another last layer it is crossed layer by layer.
+    Every channel, and nu_e decoupled from one or both other states (the
+    tridiagonal basis then has a zero off-diagonal; there only the sign of
+    the matter term that moves nu_e's level away from the others, so that no
+    event lies in the documented NaN window of an exact crossing)."""
+    rng = np.random.default_rng(n_layers)
+    half = [(float(rng.uniform(50.0, 4000.0 / n_layers)), float(rng.uniform(2.0, 11.0)), 0.49)
+            for _ in range((n_layers + 1) // 2)]
+    path = half + half[::-1][n_layers % 2:]
+    assert len(path) == n_layers and path == path[::-1]
+    if not mirrored:
+        path[-1] = (path[-1][0] * 1.25, path[-1][1], path[-1][2])
+    s = all_channel_sample(3000, 100 + n_layers, e_min=0.5)
+    p = torch.empty(s.n, dtype=torch.float64, device="cuda")
+    sets = [workload.TABLE1, dict(workload.TABLE1, dm2_32=-2.4e-3, delta_cp=1.1),
+            dict(workload.TABLE1, sin2_th12=0.0, sin2_th13=0.0),
+            dict(workload.TABLE1, sin2_th13=1.0)]
+    flags = s.flags.copy()
+    ctx.osc_set_params(sets)
+    try:
+        for k, ps in enumerate(sets):
+            s.flags = (flags | 16 if k == 2 else flags & 15 if k == 3 else flags).astype(np.uint8)
+            ctx.osc_reweight_layered(osc.DeviceSample.from_host(s), path, k, p)
+            want = oracle.prob_layered_batch(ps, path, s.e_true, s.flags)
+            assert np.abs(host(p) - want).max() <= P_TOL, k
+    finally:
+        ctx.osc_set_params(SETS)
+
+
 def test_one_layer_matches_constant_density_kernel(osc, ctx):
     s = all_channel_sample(50_000, 3)
     s.L_km, s.rho_gcc, s.Ye = 1300.0, 3.0, 0.5
