@@ -222,6 +222,11 @@ struct osc_ctx {
     bool profiling = false;
     std::vector<ProfRec> prof;
     std::mutex mu;
+    // one-time builds (osc::host::BuildSpace)
+    std::mutex build_mu;
+    void* build_ptr = nullptr;
+    size_t build_cap = 0;
+    hipStream_t build_stream = nullptr;
 };
 
 namespace {
@@ -318,6 +323,43 @@ osc_status release_scratch(osc_ctx* ctx, Scratch* s, hipStream_t stream)
 }
 
 }  // namespace
+
+namespace {
+constexpr size_t kBuildKeepBytes = size_t(512) << 20;
+}
+
+osc_status osc::host::BuildSpace::acquire(osc_ctx* ctx, size_t bytes)
+{
+    ctx->build_mu.lock();
+    ctx_ = ctx;
+    if (!ctx->build_stream &&
+        hipStreamCreateWithFlags(&ctx->build_stream, hipStreamNonBlocking) != hipSuccess)
+        return OSC_ERR_DEVICE;
+    if (ctx->build_cap >= bytes) return OSC_OK;
+    if (ctx->build_ptr) (void)hipFree(ctx->build_ptr);
+    ctx->build_ptr = nullptr;
+    ctx->build_cap = 0;
+    if (hipMalloc(&ctx->build_ptr, bytes) != hipSuccess) {
+        ctx->build_ptr = nullptr;
+        return OSC_ERR_OUT_OF_MEMORY;
+    }
+    ctx->build_cap = bytes;
+    return OSC_OK;
+}
+
+osc::host::BuildSpace::~BuildSpace()
+{
+    if (!ctx_) return;
+    if (ctx_->build_cap > kBuildKeepBytes) {
+        (void)hipFree(ctx_->build_ptr);
+        ctx_->build_ptr = nullptr;
+        ctx_->build_cap = 0;
+    }
+    ctx_->build_mu.unlock();
+}
+
+void* osc::host::BuildSpace::ptr() const { return ctx_->build_ptr; }
+hipStream_t osc::host::BuildSpace::stream() const { return ctx_->build_stream; }
 
 bool osc::host::sample_ok(const osc_sample* s, bool needs_hist_inputs)
 {
@@ -541,6 +583,8 @@ osc_status osc_destroy(osc_ctx* ctx)
         if (s.ptr && hipFree(s.ptr) != hipSuccess) st = OSC_ERR_DEVICE;
         if (s.done && hipEventDestroy(s.done) != hipSuccess) st = OSC_ERR_DEVICE;
     }
+    if (ctx->build_ptr && hipFree(ctx->build_ptr) != hipSuccess) st = OSC_ERR_DEVICE;
+    if (ctx->build_stream && hipStreamDestroy(ctx->build_stream) != hipSuccess) st = OSC_ERR_DEVICE;
     delete ctx;
     return st;
 }

@@ -1,5 +1,5 @@
-// Host-side helpers of libosc shared by the plain entry points and the
-// batched form (defined in osc_host.hip).
+// Host-side helpers of libosc shared by the plain entry points, the batched
+// and serving forms and the templates (defined in osc_host.hip).
 #pragma once
 
 #include "../../include/osc.h"
@@ -36,6 +36,26 @@ hipError_t enqueue_fill(const SetConsts& sc, const osc_sample* sample, const uin
 // 16-bit entries at `bins`) for `binning` on `stream`.
 hipError_t enqueue_bin_slots(const osc_sample* sample, const osc_binning* binning,
                              uint16_t* bins, hipStream_t stream);
+
+// The context's device workspace and stream for one-time builds (templates).
+// A build holds them from acquire() to the end of the object's life, so
+// builds on one context run one at a time, and has to wait for its stream
+// before that end.  The workspace stays with the context for the next build
+// (allocating and freeing 300 MB costs 0.3 ms each time), unless it is larger
+// than 512 MiB: then it is freed at once.
+class BuildSpace {
+public:
+    BuildSpace() = default;
+    BuildSpace(const BuildSpace&) = delete;
+    BuildSpace& operator=(const BuildSpace&) = delete;
+    ~BuildSpace();
+    osc_status acquire(osc_ctx* ctx, size_t bytes);
+    void* ptr() const;
+    hipStream_t stream() const;
+
+private:
+    osc_ctx* ctx_ = nullptr;
+};
 
 }  // namespace host
 }  // namespace osc

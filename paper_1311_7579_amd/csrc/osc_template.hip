@@ -6,8 +6,9 @@
 //   hist[r] = sum over k = c nt + t of fl(T[r][k] * P[k]).
 //
 // Template build (once, deterministic): every event gets a cell key, a
-// stable radix sort groups the events of a cell in ascending event order,
-// and one thread per cell adds the cell's weights in that order.
+// stable radix sort of (key, weight) puts the weights of a cell in a row in
+// ascending event order, and a wave adds each cell's row with the bits of
+// one addition after the other.
 // Per call: one kernel for the 18 nt probabilities (the same per-event
 // arithmetic as the fused kernel), one wave per reconstructed bin for the
 // contraction (lane-strided sums, then the wave's binary tree).
@@ -38,7 +39,7 @@ struct TrueBins {
 __global__ __launch_bounds__(256) void template_keys_kernel(
     int64_t n, const double* __restrict__ e_true, const uint8_t* __restrict__ flags,
     const double* __restrict__ e_reco, TrueBins tb, BinConsts rb, uint32_t n_cells,
-    uint32_t* __restrict__ keys, uint32_t* __restrict__ idx)
+    uint32_t* __restrict__ keys)
 {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i >= n) return;
@@ -56,60 +57,256 @@ __global__ __launch_bounds__(256) void template_keys_kernel(
     keys[i] = (valid && inside)
                   ? (uint32_t(r) * kTemplateChannels + c) * uint32_t(tb.nt) + uint32_t(kt)
                   : n_cells;
-    idx[i] = uint32_t(i);
 }
 
-// First and one-past-last position of every cell in the sorted keys.
+// First and one-past-last position of every cell in the sorted keys, and in
+// *used the number of keys below n_cells (they sort first; *used is 0
+// beforehand).
 __global__ __launch_bounds__(256) void template_bounds_kernel(int64_t n,
                                                               const uint32_t* __restrict__ keys,
                                                               uint32_t n_cells,
-                                                              uint32_t* __restrict__ first,
-                                                              uint32_t* __restrict__ last)
+                                                              uint2* __restrict__ rows,
+                                                              uint32_t* __restrict__ used)
 {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const uint32_t k = keys[i];
     if (k >= n_cells) return;
-    if (i == 0 || keys[i - 1] != k) first[k] = uint32_t(i);
-    if (i == n - 1 || keys[i + 1] != k) last[k] = uint32_t(i + 1);
+    const uint32_t next = i + 1 < n ? keys[i + 1] : n_cells;
+    if (i == 0 || keys[i - 1] != k) rows[k].x = uint32_t(i);
+    if (next != k) rows[k].y = uint32_t(i + 1);
+    if (next >= n_cells) *used = uint32_t(i + 1);
 }
 
-// The weights in sorted order: ws[i] = weight[idx[i]] (independent loads,
-// so the per-cell sums below stream contiguous memory instead of waiting
-// on one dependent gather per addition).
-__global__ __launch_bounds__(256) void template_gather_kernel(int64_t n,
-                                                              const uint32_t* __restrict__ idx,
-                                                              const double* __restrict__ weight,
-                                                              double* __restrict__ ws)
+// The weight sum of a cell is defined as one FP64 addition after the other,
+// from +0.0 in event order: 1e5 dependent additions for the fullest cells.
+// Most of them need not wait for each other.  While the sum s stays in one
+// binade [2^k, 2^(k+1)), s is a multiple of g = 2^(k-52) and adding w >= 0
+// adds r(w), w rounded to a multiple of g, which does not depend on s unless
+// w lies exactly half way between two multiples (the tie then goes by the
+// parity of s / g).  r(w) = fl(s + w) - s for any such s, both operations
+// exact enough to recover the rounding w - r(w).  So the r of a block of
+// values are formed independently from the s before the block and added in
+// any order (sums of multiples of g below 2^(k+1) are exact), and the result
+// stands if no w was negative, NaN or a tie and the new sum is still below
+// 2^(k+1).  Otherwise the block is added row by row of 64, and a row that
+// fails the same test one value after the other.  About one value in s / w
+// is a tie, so that is the rule for the first thousand values of a cell and
+// rare afterwards.
+
+// Sum over the lanes of a wave in any order (for exact sums): DPP within
+// rows of 16, then the four rows through SGPRs.
+__device__ __forceinline__ double lanes_sum(double v)
 {
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < n) ws[i] = weight[idx[i]];
+    const auto step = [&](auto ctrl) {
+        constexpr int c = decltype(ctrl)::value;
+        v = v + __hiloint2double(
+                    __builtin_amdgcn_mov_dpp(__double2hiint(v), c, 0xf, 0xf, true),
+                    __builtin_amdgcn_mov_dpp(__double2loint(v), c, 0xf, 0xf, true));
+    };
+    step(std::integral_constant<int, 0xB1>{});    // quad_perm [1, 0, 3, 2]
+    step(std::integral_constant<int, 0x4E>{});    // quad_perm [2, 3, 0, 1]
+    step(std::integral_constant<int, 0x141>{});   // row_half_mirror
+    step(std::integral_constant<int, 0x140>{});   // row_mirror
+    const auto lane = [&](int l) {
+        return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                                __builtin_amdgcn_readlane(__double2loint(v), l));
+    };
+    return (lane(0) + lane(16)) + (lane(32) + lane(48));
 }
 
-// Weight sum of every cell, its events in ascending event order from +0.0:
-// one thread per cell adds its contiguous run of ws one value after the
-// other, with the loads of kSumBatch values issued ahead of their adds.
-constexpr uint32_t kSumBatch = 16;
-__global__ __launch_bounds__(256) void template_sum_kernel(uint32_t n_cells,
-                                                           const uint32_t* __restrict__ first,
-                                                           const uint32_t* __restrict__ last,
-                                                           const double* __restrict__ ws,
-                                                           double* __restrict__ T)
-{
-    const int64_t c = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (c >= n_cells) return;
-    double s = 0.0;
-    uint32_t i = first[c];
-    const uint32_t end = last[c];
-    for (; end - i >= kSumBatch && i < end; i += kSumBatch) {
-        double v[kSumBatch];
-#pragma unroll
-        for (uint32_t j = 0; j < kSumBatch; ++j) v[j] = ws[i + j];
-#pragma unroll
-        for (uint32_t j = 0; j < kSumBatch; ++j) s = s + v[j];
+struct RowSum {
+    double s;       // the sum before the block
+    double acc;     // this lane's part of the block's r(w)
+    bool bad;       // this lane has a value that does not fit the scheme
+    double half_g;
+    __device__ __forceinline__ explicit RowSum(double s0) : s(s0), acc(0.0)
+    {
+        const int e = (__double2hiint(s0) >> 20) & 0x7ff;
+        bad = e < 64 || e > 2040 || __double2hiint(s0) < 0;
+        half_g = __hiloint2double((e > 53 ? e - 53 : 0) << 20, 0);
     }
-    for (; i < end; ++i) s = s + ws[i];
-    T[c] = s;
+    __device__ __forceinline__ void add(double w)
+    {
+        const double t = s + w;
+        const double r = t - s;
+        bad = bad || !(w >= 0.0) || __builtin_fabs(w - r) == half_g;
+        acc = acc + r;
+    }
+    // The end of the binade of the sum before the block.
+    __device__ __forceinline__ double top() const
+    {
+        return __hiloint2double((__double2hiint(s) & 0x7ff00000) + 0x00100000, 0);
+    }
+    // The sum after the block (the same in every lane); false if it has to
+    // be formed in smaller steps.
+    __device__ __forceinline__ bool finish(double& out) const
+    {
+        if (__any(bad)) return false;
+        out = s + lanes_sum(acc);
+        return out < top();
+    }
+};
+
+// One value after the other: the 64 lanes of v.
+__device__ __forceinline__ double sum_in_order(double s, double v)
+{
+    const int hi = __double2hiint(v), lo = __double2loint(v);
+#pragma unroll
+    for (int j = 0; j < 64; ++j)
+        s = s + __hiloint2double(__builtin_amdgcn_readlane(hi, j),
+                                 __builtin_amdgcn_readlane(lo, j));
+    return s;
+}
+
+// s plus the 64 lanes of v, in order.
+__device__ __forceinline__ double add_row(double s, double v)
+{
+    RowSum row(s);
+    row.add(v);
+    double total;
+    return row.finish(total) ? total : sum_in_order(s, v);
+}
+
+// s plus the block v (kSumRows rows of 64 values, the first at `first` of
+// len; +0.0 past the end, which adds nothing).
+constexpr int kSumRows = 16;
+constexpr uint32_t kSumBlock = kSumRows * 64;
+
+__device__ __forceinline__ void load_block(const double* __restrict__ ws, uint32_t first,
+                                           uint32_t len, int lane, double (&v)[kSumRows])
+{
+#pragma unroll
+    for (int j = 0; j < kSumRows; ++j) {
+        const uint32_t i = first + j * 64 + lane;
+        v[j] = i < len ? ws[i] : 0.0;
+    }
+}
+
+// s plus the values first .. min(first + kSumBlock, len) - 1 of ws.
+__device__ __forceinline__ double add_rows(double s, const double* __restrict__ ws, uint32_t first,
+                                           uint32_t len, int lane)
+{
+    const uint32_t end = min(first + kSumBlock, len);
+    double next = first + lane < end ? ws[first + lane] : 0.0;
+#pragma unroll 1
+    for (uint32_t at = first; at < end; at += 64) {
+        const double v = next;
+        const uint32_t i = at + 64 + lane;
+        if (at + 64 < end) next = i < end ? ws[i] : 0.0;
+        s = add_row(s, v);
+    }
+    return s;
+}
+
+__device__ __forceinline__ double add_block(double s, const double (&v)[kSumRows],
+                                            const double* __restrict__ ws, uint32_t first,
+                                            uint32_t len, int lane)
+{
+    RowSum block(s);
+#pragma unroll
+    for (int j = 0; j < kSumRows; ++j) block.add(v[j]);
+    double total;
+    return block.finish(total) ? total : add_rows(s, ws, first, len, lane);
+}
+
+// Weight sum of every cell.  A workgroup takes 512 cells, a stride apart (the
+// fullest cells are neighbours).  A lane adds a short row by itself; a wave
+// adds a middling one block by block; the workgroup's eight waves add a long
+// one, each forming a block's part of 8192 values at a time from the sum
+// before them (if that does not stand, the waves go on one after the other).
+// The next values are loaded before these are added.  Bound by the memory
+// latency of the fullest cell's chain of loads: 1e7 events in 187200 cells
+// took 5900 us with one thread per cell and 16 loads ahead, 302 us with one
+// wave for each long row, 240 us now; most of that is the first few thousand
+// values of the long rows, where ties are frequent.
+constexpr uint32_t kShortRow = 32;
+constexpr uint32_t kLongRow = 16384;
+constexpr int kSumWaves = 8;
+__global__ __launch_bounds__(kSumWaves * 64) void template_sum_kernel(
+    uint32_t n_cells, const uint2* __restrict__ rows, const double* __restrict__ ws,
+    double* __restrict__ T)
+{
+    __shared__ uint3 long_rows[kSumWaves * 64];   // first, length, thread of the cell
+    __shared__ uint32_t n_long;
+    __shared__ double part[kSumWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (threadIdx.x == 0) n_long = 0;
+    __syncthreads();
+    const int64_t cell = int64_t(blockIdx.x) + int64_t(threadIdx.x) * gridDim.x;
+    const uint2 row = cell < n_cells ? rows[cell] : uint2{0u, 0u};
+    const uint32_t len = row.y - row.x;
+    double s = 0.0;
+    if (len <= kShortRow) {
+        uint32_t i = row.x;
+        for (; row.y - i >= 8u; i += 8u) {
+            double v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = ws[i + j];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) s = s + v[j];
+        }
+        for (; i < row.y; ++i) s = s + ws[i];
+    } else if (len > kLongRow) {
+        long_rows[atomicAdd(&n_long, 1u)] = uint3{row.x, len, threadIdx.x};
+    }
+    for (uint64_t mask = __ballot(len > kShortRow && len <= kLongRow); mask; mask &= mask - 1) {
+        const int l = __builtin_ctzll(mask);
+        const double* w = ws + uint32_t(__builtin_amdgcn_readlane(int(row.x), l));
+        const uint32_t n = __builtin_amdgcn_readlane(int(len), l);
+        double next[kSumRows], v[kSumRows], c = 0.0;
+        load_block(w, 0, n, lane, next);
+        for (uint32_t first = 0; first < n; first += kSumBlock) {
+#pragma unroll
+            for (int j = 0; j < kSumRows; ++j) v[j] = next[j];
+            if (first + kSumBlock < n) load_block(w, first + kSumBlock, n, lane, next);
+            c = add_block(c, v, w, first, n, lane);
+        }
+        if (lane == l) s = c;
+    }
+    __syncthreads();
+    for (uint32_t k = 0; k < n_long; ++k) {
+        const uint3 r = long_rows[k];
+        const double* w = ws + r.x;
+        const uint32_t n = r.y;
+        double next[kSumRows], v[kSumRows], c = 0.0;
+        load_block(w, wave * kSumBlock, n, lane, next);
+        for (uint32_t first = 0; first < n; first += kSumWaves * kSumBlock) {
+            const uint32_t mine = first + wave * kSumBlock;
+#pragma unroll
+            for (int j = 0; j < kSumRows; ++j) v[j] = next[j];
+            if (first + kSumWaves * kSumBlock < n)
+                load_block(w, mine + kSumWaves * kSumBlock, n, lane, next);
+            RowSum block(c);
+#pragma unroll
+            for (int j = 0; j < kSumRows; ++j) block.add(v[j]);
+            // a NaN part marks a block that does not stand
+            const bool bad = __any(block.bad);
+            const double sum = lanes_sum(block.acc);
+            if (lane == 0) part[wave] = bad ? __builtin_nan("") : sum;
+            __syncthreads();
+            double total = 0.0;
+#pragma unroll
+            for (int j = 0; j < kSumWaves; ++j) total = total + part[j];
+            total = c + total;
+            __syncthreads();
+            if (total < block.top()) {
+                c = total;
+            } else {
+                for (int j = 0; j < kSumWaves; ++j) {
+                    if (wave == j) {
+                        c = add_block(c, v, w, mine, n, lane);
+                        if (lane == 0) part[0] = c;
+                    }
+                    __syncthreads();
+                    c = part[0];
+                    __syncthreads();
+                }
+            }
+        }
+        if (threadIdx.x == r.z) s = c;
+    }
+    if (cell < n_cells) T[cell] = s;
 }
 
 // P of the 18 channels at the centre of every true bin, layout P[c][t].
@@ -237,88 +434,63 @@ osc_status osc_template_create(osc_ctx* ctx, const osc_sample* sample,
     }
 
     const int64_t n = sample->n;
-    hipStream_t s = nullptr;
-    uint32_t *keys = nullptr, *idx = nullptr, *skeys = nullptr, *sidx = nullptr;
-    uint32_t *first = nullptr, *last = nullptr;
-    double* ws = nullptr;
-    void* tmp = nullptr;
-    size_t tmp_bytes = 0;
-    osc_status st = OSC_OK;
     int end_bit = 1;
     while (end_bit < 32 && (uint64_t(1) << end_bit) <= uint64_t(n_cells)) ++end_bit;
     // the sample may have been written by work still in flight on any stream
-    if (hipDeviceSynchronize() != hipSuccess) st = OSC_ERR_DEVICE;
-    if (st == OSC_OK && hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess)
-        st = OSC_ERR_DEVICE;
-    const size_t nb = size_t(n > 0 ? n : 1) * sizeof(uint32_t);
-    if (st == OSC_OK &&
-        (hipMalloc(&keys, nb) != hipSuccess || hipMalloc(&idx, nb) != hipSuccess ||
-         hipMalloc(&skeys, nb) != hipSuccess || hipMalloc(&sidx, nb) != hipSuccess ||
-         hipMalloc(&ws, size_t(n > 0 ? n : 1) * sizeof(double)) != hipSuccess ||
-         hipMalloc(&first, size_t(n_cells) * sizeof(uint32_t)) != hipSuccess ||
-         hipMalloc(&last, size_t(n_cells) * sizeof(uint32_t)) != hipSuccess))
-        st = OSC_ERR_OUT_OF_MEMORY;
-    if (st == OSC_OK &&
-        hipcub::DeviceRadixSort::SortPairs(nullptr, tmp_bytes, keys, skeys, idx, sidx, int(n), 0,
-                                           end_bit, s) != hipSuccess)
-        st = OSC_ERR_DEVICE;
-    if (st == OSC_OK && hipMalloc(&tmp, tmp_bytes > 0 ? tmp_bytes : 1) != hipSuccess)
-        st = OSC_ERR_OUT_OF_MEMORY;
+    osc_status st = hipDeviceSynchronize() == hipSuccess ? OSC_OK : OSC_ERR_DEVICE;
+    uint32_t used = 0;
     if (st == OSC_OK) {
-        hipError_t e = hipMemsetAsync(first, 0, size_t(n_cells) * sizeof(uint32_t), s);
-        if (e == hipSuccess) e = hipMemsetAsync(last, 0, size_t(n_cells) * sizeof(uint32_t), s);
-        if (e == hipSuccess && n > 0) {
-            hipLaunchKernelGGL(osc::template_keys_kernel, dim3(blocks_for(n, 256)), dim3(256), 0,
-                               s, n, sample->e_true, sample->flags, sample->e_reco, tp->tb,
-                               osc::host::bin_consts(reco_binning), n_cells, keys, idx);
-            e = hipGetLastError();
-            if (e == hipSuccess)
-                e = hipcub::DeviceRadixSort::SortPairs(tmp, tmp_bytes, keys, skeys, idx, sidx,
-                                                       int(n), 0, end_bit, s);
-            if (e == hipSuccess) {
-                hipLaunchKernelGGL(osc::template_bounds_kernel, dim3(blocks_for(n, 256)),
-                                   dim3(256), 0, s, n, skeys, n_cells, first, last);
+        size_t sort_bytes = 0;
+        if (n > 0 && hipcub::DeviceRadixSort::SortPairs(
+                         nullptr, sort_bytes, static_cast<const uint32_t*>(nullptr),
+                         static_cast<uint32_t*>(nullptr), static_cast<const double*>(nullptr),
+                         static_cast<double*>(nullptr), int(n), 0, end_bit, nullptr) != hipSuccess)
+            st = OSC_ERR_DEVICE;
+        // one workspace: the cells' rows and the count of used events, the
+        // keys before and after the sort, the sorted weights, the sort's own
+        const auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
+        const size_t rows_b = up(size_t(n_cells) * sizeof(uint2) + sizeof(uint32_t));
+        const size_t keys_b = up(size_t(n) * sizeof(uint32_t));
+        const size_t ws_b = up(size_t(n) * sizeof(double));
+        osc::host::BuildSpace space;
+        if (st == OSC_OK) st = space.acquire(ctx, rows_b + 2 * keys_b + ws_b + up(sort_bytes));
+        if (st == OSC_OK) {
+            char* at = static_cast<char*>(space.ptr());
+            const hipStream_t s = space.stream();
+            uint2* rows = reinterpret_cast<uint2*>(at);
+            uint32_t* d_used = reinterpret_cast<uint32_t*>(rows + n_cells);
+            uint32_t* keys = reinterpret_cast<uint32_t*>(at + rows_b);
+            uint32_t* skeys = reinterpret_cast<uint32_t*>(at + rows_b + keys_b);
+            double* ws = reinterpret_cast<double*>(at + rows_b + 2 * keys_b);
+            void* tmp = at + rows_b + 2 * keys_b + ws_b;
+            hipError_t e = hipMemsetAsync(rows, 0, rows_b, s);
+            if (e == hipSuccess && n > 0) {
+                hipLaunchKernelGGL(osc::template_keys_kernel, dim3(blocks_for(n, 256)), dim3(256),
+                                   0, s, n, sample->e_true, sample->flags, sample->e_reco, tp->tb,
+                                   osc::host::bin_consts(reco_binning), n_cells, keys);
                 e = hipGetLastError();
-            }
-            if (e == hipSuccess) {
-                hipLaunchKernelGGL(osc::template_gather_kernel, dim3(blocks_for(n, 256)),
-                                   dim3(256), 0, s, n, sidx, sample->weight, ws);
-                e = hipGetLastError();
-            }
-        }
-        if (e == hipSuccess) {
-            hipLaunchKernelGGL(osc::template_sum_kernel, dim3(blocks_for(n_cells, 256)),
-                               dim3(256), 0, s, n_cells, first, last, ws, tp->d_T);
-            e = hipGetLastError();
-        }
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) st = OSC_ERR_DEVICE;
-    }
-    if (st == OSC_OK && n_used) {
-        // events in the template: the sorted keys below n_cells
-        uint32_t count = 0;
-        if (n > 0) {
-            // the sentinel key sorts last; find the first sentinel by bisection
-            int64_t lo = 0, hi = n;
-            while (lo < hi) {
-                const int64_t mid = (lo + hi) / 2;
-                uint32_t k = 0;
-                if (hipMemcpy(&k, skeys + mid, sizeof(k), hipMemcpyDeviceToHost) != hipSuccess) {
-                    st = OSC_ERR_DEVICE;
-                    break;
+                if (e == hipSuccess)
+                    e = hipcub::DeviceRadixSort::SortPairs(tmp, sort_bytes, keys, skeys,
+                                                           sample->weight, ws, int(n), 0, end_bit,
+                                                           s);
+                if (e == hipSuccess) {
+                    hipLaunchKernelGGL(osc::template_bounds_kernel, dim3(blocks_for(n, 256)),
+                                       dim3(256), 0, s, n, skeys, n_cells, rows, d_used);
+                    e = hipGetLastError();
                 }
-                if (k < n_cells) lo = mid + 1;
-                else hi = mid;
             }
-            count = uint32_t(lo);
+            if (e == hipSuccess) {
+                hipLaunchKernelGGL(osc::template_sum_kernel, dim3(blocks_for(n_cells, osc::kSumWaves * 64)),
+                                   dim3(osc::kSumWaves * 64), 0, s, n_cells, rows, ws, tp->d_T);
+                e = hipGetLastError();
+            }
+            if (e == hipSuccess)
+                e = hipMemcpyAsync(&used, d_used, sizeof used, hipMemcpyDeviceToHost, s);
+            if (e == hipSuccess) e = hipStreamSynchronize(s);
+            if (e != hipSuccess) st = OSC_ERR_DEVICE;
         }
-        *n_used = count;
     }
-    for (void* p : {static_cast<void*>(keys), static_cast<void*>(idx), static_cast<void*>(skeys),
-                    static_cast<void*>(sidx), static_cast<void*>(first), static_cast<void*>(last),
-                    static_cast<void*>(ws), tmp})
-        if (p) (void)hipFree(p);
-    if (s) (void)hipStreamDestroy(s);
+    if (st == OSC_OK && n_used) *n_used = used;
     if (st != OSC_OK) {
         osc_template_destroy(tp);
         return st;

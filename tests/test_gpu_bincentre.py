@@ -86,6 +86,53 @@ def test_template_and_pdf_against_oracle(osc, ctx, n, nt, nr):
     assert np.all(np.abs(h - h_o) <= tol)
 
 
+def hard_weights(kind, n):
+    """Weights whose sum in order is easy to get wrong in blocks."""
+    rng = np.random.default_rng(4)
+    w = rng.uniform(0.5, 1.5, n)
+    if kind == "ties":            # every third value halfway between two sums
+        w[::3] = 2.0 ** -40 * (2 * rng.integers(0, 1 << 20, w[::3].size) + 1)
+    elif kind == "signs":
+        w *= np.where(rng.random(n) < 0.3, -1.0, 1.0)
+    elif kind == "binades":       # 80 orders of magnitude, ascending
+        w = np.sort(10.0 ** rng.uniform(-40, 40, n))
+    elif kind == "special":
+        w[n // 2], w[n // 3] = np.inf, 0.0
+        w[n // 5] = -0.0
+    elif kind == "nan":
+        w[n // 2] = np.nan
+    elif kind == "tiny":          # subnormal sums
+        w *= 2.0 ** -1074 * 1000
+    elif kind == "huge":          # overflows to infinity
+        w *= 2.0 ** 1022
+    elif kind == "ones":
+        w[:] = 1.0
+    return w
+
+
+@pytest.mark.parametrize("kind", ["plain", "ones", "ties", "signs", "binades", "special", "nan",
+                                  "tiny", "huge"])
+@pytest.mark.parametrize("n", [31, 32, 33, 65, 1024, 1025, 16384, 16385, 70_001])
+def test_cell_sums_are_the_sums_in_order(osc, ctx, kind, n):
+    """All events in one cell: the template's entry has the bits of adding
+    the weights one after the other (rows added by a lane, a wave and a
+    workgroup, whole and ragged blocks)."""
+    w = hard_weights(kind, n)
+    e = np.full(n, 0.6)
+    s = workload.Sample(e, workload.make_flags(np.ones(n, int), np.ones(n, int),
+                                               np.zeros(n, bool)), w, e.copy())
+    tp = osc.Template(ctx, osc.DeviceSample.from_host(s), 1, 0.5, 1.0, 1, 0.5, 1.0)
+    try:
+        got = host(tp.copy())[0, 4, 0]
+    finally:
+        tp.close()
+    with np.errstate(all="ignore"):
+        want = np.add.accumulate(np.concatenate([[0.0], w]))[-1]
+    assert tp.n_used == n
+    assert np.array_equal(np.array([got]).view(np.uint64), np.array([want]).view(np.uint64)) or (
+        np.isnan(got) and np.isnan(want)), (got, want)
+
+
 def test_energy_scale_and_other_sets(osc, ctx):
     s = mixed_sample(50_000, 5, L=1300.0, rho=3.0)
     for k, e_scale in ((1, 0.02), (2, -0.015), (3, 0.0)):
