@@ -95,7 +95,7 @@ __global__ void reset_queue(unsigned* queue)
 
 template <bool MIXED>
 __global__ __launch_bounds__(kTileLanes) __attribute__((amdgpu_waves_per_eu(kBatchWavesPerSimd)))
-void batch_kernel(BatchArgs a, SinCosTable sctab, const BatchSampleDev* __restrict__ samples,
+void batch_kernel(BatchArgs a, const BatchSampleDev* __restrict__ samples,
                   const SetConsts* __restrict__ sets, double* __restrict__ partial,
                   unsigned* __restrict__ queue)
 {
@@ -103,7 +103,7 @@ void batch_kernel(BatchArgs a, SinCosTable sctab, const BatchSampleDev* __restri
     __shared__ Tables<MIXED> tabs;
     const int lane = threadIdx.x;
     const int nbt = a.nbt;
-    if constexpr (!MIXED) load_sincos(sctab, tabs, lane);   // read after the first barrier below
+    if constexpr (!MIXED) load_sincos(tabs, lane);   // read after the first barrier below
 
     const int64_t G = gridDim.x, b = blockIdx.x;
     int64_t item, end, stride = 0, base = 0;
@@ -254,14 +254,13 @@ hipError_t enqueue(osc_batch* b, int n_sets, const osc_batch_config& c, hipStrea
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
-        const osc::SinCosTable& sct = osc::host::sincos_table();
         if (b->precision == OSC_FP32_MIXED)
             hipLaunchKernelGGL(osc::batch_kernel<true>, dim3(unsigned(grid)), dim3(osc::kTileLanes),
-                               lds, stream, a, sct, b->d_samples, b->d_sets, b->d_scratch,
+                               lds, stream, a, b->d_samples, b->d_sets, b->d_scratch,
                                b->d_queue);
         else
             hipLaunchKernelGGL(osc::batch_kernel<false>, dim3(unsigned(grid)), dim3(osc::kTileLanes),
-                               lds, stream, a, sct, b->d_samples, b->d_sets, b->d_scratch,
+                               lds, stream, a, b->d_samples, b->d_sets, b->d_scratch,
                                b->d_queue);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

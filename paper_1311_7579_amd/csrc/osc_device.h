@@ -66,11 +66,13 @@ __device__ __forceinline__ void phase_sincos(double a, double b, const SinCos* _
     cs = __builtin_fma(k.c, cm, __builtin_fma(-k.s, s, k.c));
 }
 
+__device__ constexpr SinCosTable kAnchors = make_anchors();
+
 // Copy the sin/cos anchors into LDS (the 64 lanes of a wave, one each).
 template <class Tab>
-__device__ __forceinline__ void load_sincos(const SinCosTable& t, Tab& T, int lane)
+__device__ __forceinline__ void load_sincos(Tab& T, int lane)
 {
-    if (lane < 64) T.sct[lane] = t.e[lane];
+    if (lane < 64) T.sct[lane] = kAnchors.e[lane];
 }
 
 // Mixed tier: the phase (a b in units of pi/32, so a b / 64 in revolutions)
@@ -770,15 +772,16 @@ __device__ __forceinline__ EventIn load_event(const TileBufs& b, uint32_t l, uin
                                               uint32_t n)
 {
     EventIn v;
-    const bool in = FULL || l + g0 < n;
-    const uint32_t l8 = l * 8u, g8 = g0 * 8u;
-    v.e = in ? buf_load_f64(b.e, l8, g8) : 1.0;
-    v.f = (MODE != kHist && in) ? uint32_t(__builtin_amdgcn_raw_buffer_load_b8(b.f, l, g0, 0))
-                                : 0u;
-    v.w = (has_hist(MODE) && in) ? buf_load_f64(b.w, l8, g8) : 0.0;
-    v.x = (has_hist(MODE) && !reads_bins(MODE) && in) ? buf_load_f64(b.x, l8, g8) : 0.0;
-    v.slot = (reads_bins(MODE) && in)
-                 ? uint32_t(__builtin_amdgcn_raw_buffer_load_b16(b.x, l * 2u, g0 * 2u, 0))
+    // a ragged tile's offset goes through the VGPR, which the resource's
+    // bound covers: lanes past the end read 0 without a branch
+    const uint32_t lv = FULL ? l : l + g0, gs = FULL ? g0 : 0u;
+    const uint32_t l8 = lv * 8u, g8 = gs * 8u;
+    v.e = buf_load_f64(b.e, l8, g8);
+    v.f = MODE != kHist ? uint32_t(__builtin_amdgcn_raw_buffer_load_b8(b.f, lv, gs, 0)) : 0u;
+    v.w = has_hist(MODE) ? buf_load_f64(b.w, l8, g8) : 0.0;
+    v.x = has_hist(MODE) && !reads_bins(MODE) ? buf_load_f64(b.x, l8, g8) : 0.0;
+    v.slot = reads_bins(MODE)
+                 ? uint32_t(__builtin_amdgcn_raw_buffer_load_b16(b.x, lv * 2u, gs * 2u, 0))
                  : 0u;
     return v;
 }
@@ -787,6 +790,23 @@ __device__ __forceinline__ void store_p(const TileBufs& b, uint32_t l, uint32_t 
 {
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(BufU2, P), b.p, l * 8u, g0 * 8u,
                                           kBufNonTemporal);
+}
+
+// Adds cval of every active lane into its accumulator.  The lanes sharing an
+// accumulator add in ascending lane order: one masked LDS atomic add per lane
+// group, group after group.  Within a group the lanes hit distinct
+// accumulators, and the DS instructions of a wave execute in issue order, so
+// every accumulator receives its additions in the contract's order (the LDS
+// adder rounds like v_add_f64: round to nearest even).  The empty asm with a
+// memory clobber keeps the compiler from merging or reordering the groups.
+__device__ __forceinline__ void add_in_lane_order(double* slot, double cval, int lane)
+{
+#pragma unroll
+    for (int p = 0; p < kLaneShare; ++p) {
+        if (lane / kHistLanes == p)
+            __hip_atomic_fetch_add(slot, cval, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        asm volatile("" ::: "memory");
+    }
 }
 
 // One group of kGroup events of a lane: the probabilities are computed in
@@ -831,21 +851,7 @@ __device__ __forceinline__ void tile_group(const PROB& prob, const BinConsts& bc
             const double cval = ev[j].w * P[j];            // rounded, never fused
             const int slot = reads_bins(MODE) ? int(ev[j].slot)
                                               : hslot(lds_bin(k[j], bc), lane & (kHistLanes - 1));
-            // The lanes sharing an accumulator add in ascending lane order:
-            // one masked LDS atomic add per lane group, group after group.
-            // Within a group the lanes hit distinct accumulators, and the
-            // DS instructions of a wave execute in issue order, so every
-            // accumulator receives its additions in the contract's order
-            // (the LDS adder rounds like v_add_f64: round to nearest even).
-            // The empty asm with a memory clobber keeps the compiler from
-            // merging or reordering the groups.
-#pragma unroll
-            for (int p = 0; p < kLaneShare; ++p) {
-                if (lane / kHistLanes == p)
-                    __hip_atomic_fetch_add(hist + slot, cval, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
-                asm volatile("" ::: "memory");
-            }
+            add_in_lane_order(hist + slot, cval, lane);
         }
     }
 }
@@ -904,6 +910,54 @@ __device__ __forceinline__ void tile_events(const PROB& prob, const BinConsts& b
             }
             tile_group<MODE, WRITE_P, FULL>(prob, bc, hist, lane, l, g * kGroup * kTileLanes,
                                             n, ev[g], bufs);
+        }
+    }
+}
+
+// A tile shared by the SPLIT waves of a workgroup: wave v computes events m =
+// v K / SPLIT .. (v + 1) K / SPLIT - 1 of every lane (all their loads in flight
+// at once), then the waves add their contributions one after the other, so
+// that every accumulator still takes its additions in ascending m.
+template <int MODE, bool WRITE_P, int SPLIT, class PROB>
+__device__ __forceinline__ void split_tile_events(const PROB& prob, const BinConsts& bc,
+                                                  double* hist, int wave, int lane, uint32_t n,
+                                                  const double* e_true, const uint8_t* flags,
+                                                  const double* weight, const double* e_reco,
+                                                  const uint16_t* bins, const double* value,
+                                                  double* p_out)
+{
+    constexpr int kShare = kLaneEvents / SPLIT;
+    constexpr bool kComputeBins = has_hist(MODE) && !reads_bins(MODE);
+    const uint32_t l = uint32_t(lane);
+    const TileBufs bufs = tile_bufs<MODE>(n, e_true, flags, weight, e_reco, bins, value, p_out);
+    EventIn ev[kShare];
+#pragma unroll
+    for (int j = 0; j < kShare; ++j)
+        ev[j] = load_event<MODE, false>(bufs, l, uint32_t(wave * kShare + j) * kTileLanes, n);
+    double c[kShare];
+    int slot[kShare];
+#pragma unroll
+    for (int j = 0; j < kShare; ++j) {
+        const uint32_t g0 = uint32_t(wave * kShare + j) * kTileLanes;
+        const double P = (MODE != kHist) ? prob(ev[j].e, ev[j].f) : ev[j].e;
+        if (WRITE_P && l + g0 < n) store_p(bufs, l, g0, P);
+        c[j] = ev[j].w * P;   // only ever an operand of an LDS addition: never fused
+        // the correctly rounded division at once: the short cut of
+        // bin_floor_fast with its rare branch kept these arrays in scratch
+        slot[j] = kComputeBins ? hslot(lds_bin(bin_floor_exact(ev[j].x, bc), bc),
+                                       lane & (kHistLanes - 1))
+                               : int(ev[j].slot);
+    }
+    if constexpr (has_hist(MODE)) {
+#pragma unroll 1
+        for (int v = 0; v < SPLIT; ++v) {
+            if (v == wave) {
+#pragma unroll
+                for (int j = 0; j < kShare; ++j)
+                    if (l + uint32_t(wave * kShare + j) * kTileLanes < n)
+                        add_in_lane_order(hist + slot[j], c[j], lane);
+            }
+            __syncthreads();
         }
     }
 }
@@ -1009,17 +1063,19 @@ __device__ __forceinline__ void load_tab(const SetConsts& sc, TileTablesMixed& T
     }
 }
 
-__device__ __forceinline__ void hist_zero(double* hist, int lane, int nbt)
+template <int THREADS = kTileLanes>
+__device__ __forceinline__ void hist_zero(double* hist, int thread, int nbt)
 {
-    for (int i = lane; i < nbt * kHistLanes; i += kTileLanes) hist[i] = 0.0;
+    for (int i = thread; i < nbt * kHistLanes; i += THREADS) hist[i] = 0.0;
 }
 
 // Tree over the 64 lanes of every bin of a finished tile, written as row
 // `row` of the tile results at `out` (chunked bin-major layout).
-__device__ __forceinline__ void tile_write(const double* hist, int lane, int nbt, int64_t row,
+template <int THREADS = kTileLanes>
+__device__ __forceinline__ void tile_write(const double* hist, int thread, int nbt, int64_t row,
                                            double* out)
 {
-    for (int bin = lane; bin < nbt; bin += kTileLanes)
+    for (int bin = thread; bin < nbt; bin += THREADS)
         out[partial_index(row, bin, nbt)] =
             lane_tree<kHistLanes, 0>(hist, lds_row_of_output(bin, nbt - 2));
 }

@@ -133,14 +133,35 @@ struct SetConsts {
     Chan ch[kChannels];
 };
 
-// sin and cos of k pi / 32, k = 0..63 (the anchors of the FP64 phase
-// sine/cosine), computed once on the host in extended precision.
+// sin and cos of k pi / 32, k = 0..63: the anchors of the FP64 phase
+// sine/cosine, correctly rounded (sin of 0 .. pi/2 below, the rest by
+// symmetry).  The table lives in device memory with the code: as a kernel
+// argument its 1 KB was copied by the host and fetched from there by every
+// launch.
 struct SinCos {
     double s, c;
 };
 struct SinCosTable {
     SinCos e[64];
 };
+constexpr double kSinQuarter[17] = {
+    0.0, 0.0980171403295606, 0.19509032201612828,
+    0.2902846772544624, 0.3826834323650898, 0.47139673682599764,
+    0.5555702330196022, 0.6343932841636455, 0.7071067811865476,
+    0.773010453362737, 0.8314696123025452, 0.881921264348355,
+    0.9238795325112867, 0.9569403357322088, 0.9807852804032304,
+    0.9951847266721969, 1.0};
+constexpr double anchor_sin(int k)
+{
+    const int q = k & 63, r = q & 31, m = r > 16 ? 32 - r : r;
+    return q < 32 ? kSinQuarter[m] : -kSinQuarter[m];
+}
+constexpr SinCosTable make_anchors()
+{
+    SinCosTable t{};
+    for (int k = 0; k < 64; ++k) t.e[k] = SinCos{anchor_sin(k), anchor_sin(k + 16)};
+    return t;
+}
 
 // Path constants of one sample.
 struct PathConsts {
@@ -178,7 +199,7 @@ struct BinConsts {
 constexpr uint32_t kValidFlags = 0x07770777u;
 
 // Tables a per-event kernel keeps in LDS, built by each block from a
-// SetConsts and the SinCosTable:
+// SetConsts and the anchors:
 //  * the channel entry of each flag byte below 28 (complex conjugates for
 //    antineutrinos: the imaginary parts negated), with dba = [alpha = beta];
 //    invalid flag bytes have a zero entry with dba = NaN, so P comes out

@@ -14,6 +14,8 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <type_traits>
+#include <vector>
 
 #include "osc_device.h"
 #include "osc_host_common.h"
@@ -27,10 +29,11 @@ namespace {
 using namespace dev;
 
 // Register budget for kTileWavesPerSimd resident waves per SIMD.
-template <int MODE, bool WRITE_P, bool MIXED = false>
-__global__ __launch_bounds__(kTileLanes) __attribute__((amdgpu_waves_per_eu(kTileWavesPerSimd)))
+template <int MODE, bool WRITE_P, bool MIXED = false, int SPLIT = 1>
+__global__ __launch_bounds__(kTileLanes * SPLIT)
+__attribute__((amdgpu_waves_per_eu(kTileWavesPerSimd)))
 void tile_kernel(
-    SetConsts sc, SinCosTable sctab, PathConsts pc, BinConsts bc, int64_t n,
+    SetConsts sc, PathConsts pc, BinConsts bc, int64_t n,
     [[maybe_unused]] int64_t ntiles,
     const double* __restrict__ e_true, const uint8_t* __restrict__ flags,
     const double* __restrict__ weight, const double* __restrict__ e_reco,
@@ -40,39 +43,46 @@ void tile_kernel(
     extern __shared__ double hist[];
     __shared__ Tables<MIXED> tabs;
 
-    const int lane = threadIdx.x;
+    const int thread = threadIdx.x;
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
     const int nbt = bc.nb + 2;
 
     if (MODE != kHist) {
-        load_tab(sc, tabs, lane);
-        if constexpr (!MIXED) load_sincos(sctab, tabs, lane);
+        load_tab(sc, tabs, thread);
+        if constexpr (!MIXED) load_sincos(tabs, thread);
     }
-    if (MODE != kReweight) hist_zero(hist, lane, nbt);
+    if (MODE != kReweight) hist_zero<kTileLanes * SPLIT>(hist, thread, nbt);
     __syncthreads();
 
     const ConstDensityProb<MIXED> prob{&sc, &tabs, pc.kA, pc.kL,
                                        MIXED ? PolyRegs{} : PolyRegs::in_vgprs()};
     const TileArrays t = tile_arrays(tile, n, e_true, flags, weight, e_reco, bins, value, p_out);
-    if (t.n == kTileEvents)
-        tile_events<MODE, WRITE_P, true, WRITE_P>(prob, bc, hist, lane, t.n, t.e_true, t.flags,
+    if constexpr (SPLIT > 1) {
+        const int wave = __builtin_amdgcn_readfirstlane(thread / kTileLanes);
+        split_tile_events<MODE, WRITE_P, SPLIT>(prob, bc, hist, wave, thread % kTileLanes, t.n,
+                                                t.e_true, t.flags, t.weight, t.e_reco, t.bins,
+                                                t.value, t.p_out);
+    } else if (t.n == kTileEvents) {
+        tile_events<MODE, WRITE_P, true, WRITE_P>(prob, bc, hist, thread, t.n, t.e_true, t.flags,
                                                   t.weight, t.e_reco, t.bins, t.value, t.p_out);
-    else
-        tile_events<MODE, WRITE_P, false, WRITE_P>(prob, bc, hist, lane, t.n, t.e_true, t.flags,
+    } else {
+        tile_events<MODE, WRITE_P, false, WRITE_P>(prob, bc, hist, thread, t.n, t.e_true, t.flags,
                                                    t.weight, t.e_reco, t.bins, t.value, t.p_out);
+    }
 
     if (MODE != kReweight) {
-        __syncthreads();
-        tile_write(hist, lane, nbt, tile, partial);
+        if (SPLIT == 1) __syncthreads();   // split tiles end with a barrier
+        tile_write<kTileLanes * SPLIT>(hist, thread, nbt, tile, partial);
     }
 }
 
 // The same tile body with P through a layered path (FP64 only).  The event
 // loop stays rolled: 16 unrolled copies of the layer loop would not fit the
 // instruction cache.
-template <int MODE, bool WRITE_P>
-__global__ __launch_bounds__(kTileLanes) __attribute__((amdgpu_waves_per_eu(kLayeredWavesPerSimd)))
-void layered_tile_kernel(SetConsts sc, SinCosTable sctab, LayerPath lp, BinConsts bc, int64_t n,
+template <int MODE, bool WRITE_P, int SPLIT = 1>
+__global__ __launch_bounds__(kTileLanes * SPLIT)
+__attribute__((amdgpu_waves_per_eu(kLayeredWavesPerSimd)))
+void layered_tile_kernel(SetConsts sc, LayerPath lp, BinConsts bc, int64_t n,
                          const double* __restrict__ e_true, const uint8_t* __restrict__ flags,
                          const double* __restrict__ weight, const double* __restrict__ e_reco,
                          double* __restrict__ p_out, double* __restrict__ partial)
@@ -80,28 +90,34 @@ void layered_tile_kernel(SetConsts sc, SinCosTable sctab, LayerPath lp, BinConst
     extern __shared__ double hist[];
     __shared__ LayeredTables tabs;
 
-    const int lane = threadIdx.x;
+    const int thread = threadIdx.x;
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
     const int nbt = bc.nb + 2;
 
-    load_tab(lp, tabs, lane);
-    load_sincos(sctab, tabs, lane);
-    if (MODE != kReweight) hist_zero(hist, lane, nbt);
+    load_tab(lp, tabs, thread);
+    load_sincos(tabs, thread);
+    if (MODE != kReweight) hist_zero<kTileLanes * SPLIT>(hist, thread, nbt);
     __syncthreads();
 
     const LayeredProb prob{&sc, &tabs, &lp};
     const TileArrays t =
         tile_arrays(tile, n, e_true, flags, weight, e_reco, nullptr, nullptr, p_out);
-    if (t.n == kTileEvents)
-        tile_events<MODE, WRITE_P, true, true>(prob, bc, hist, lane, t.n, t.e_true, t.flags,
-                                                       t.weight, t.e_reco, nullptr, nullptr, t.p_out);
-    else
-        tile_events<MODE, WRITE_P, false, true>(prob, bc, hist, lane, t.n, t.e_true, t.flags,
-                                                        t.weight, t.e_reco, nullptr, nullptr, t.p_out);
+    if constexpr (SPLIT > 1) {
+        const int wave = __builtin_amdgcn_readfirstlane(thread / kTileLanes);
+        split_tile_events<MODE, WRITE_P, SPLIT>(prob, bc, hist, wave, thread % kTileLanes, t.n,
+                                                t.e_true, t.flags, t.weight, t.e_reco, nullptr,
+                                                nullptr, t.p_out);
+    } else if (t.n == kTileEvents) {
+        tile_events<MODE, WRITE_P, true, true>(prob, bc, hist, thread, t.n, t.e_true, t.flags,
+                                               t.weight, t.e_reco, nullptr, nullptr, t.p_out);
+    } else {
+        tile_events<MODE, WRITE_P, false, true>(prob, bc, hist, thread, t.n, t.e_true, t.flags,
+                                                t.weight, t.e_reco, nullptr, nullptr, t.p_out);
+    }
 
     if (MODE != kReweight) {
-        __syncthreads();
-        tile_write(hist, lane, nbt, tile, partial);
+        if (SPLIT == 1) __syncthreads();   // split tiles end with a barrier
+        tile_write<kTileLanes * SPLIT>(hist, thread, nbt, tile, partial);
     }
 }
 
@@ -212,6 +228,31 @@ hipError_t launch_poisson_nll(const double* hist, int64_t n_hist, double scale,
     return hipGetLastError();
 }
 
+namespace {
+
+// Waves that share a tile.  Few tiles leave the chip's 1024 SIMDs with a wave
+// or less each, and a wave's 16 events then run one after the other at the
+// latency of their dependent arithmetic and loads; more waves per tile cost
+// barriers between their additions and tables filled per tile.  Per-event
+// kernel with one wave | four | eight a tile (us, FP64, 50 bins, no P unless
+// said): 1e4 events 10.6 | 6.6 | 6.1, 7.7e5 12.1 | 9.0 | 8.9, 1e6 11.6 | 10.3
+// | 11.1, 6e6 36.2 | 35.0 | 46.8, 1e7 57.4 | 57.3 | 81.6; with P written 2e6
+// 17.5 | 17.3 | 19.2, 3e6 22.4 | 22.8 | 26.3; P alone 1e3 8.2 | 4.0 | 4.0,
+// 6e6 31.1 | 30.0 | 32.2; five layers 1e4 33.5 | 13.1 | 10.8, 4e6 99 | 98 | 97.
+int tile_split(int64_t ntiles, int mode, bool write_p)
+{
+    if (mode == kReweight) return ntiles <= 6144 ? 4 : 1;
+    if (ntiles <= 768) return 8;
+    return ntiles <= (write_p ? 2048 : 6144) ? 4 : 1;
+}
+
+int layered_split(int64_t ntiles) { return ntiles <= 4096 ? 8 : 1; }
+
+template <int N>
+using Int = std::integral_constant<int, N>;
+
+}  // namespace
+
 hipError_t launch_tiles(int mode, bool write_p, bool mixed, const SetConsts& sc,
                         const PathConsts& pc, const BinConsts& bc, int64_t n,
                         const double* e_true, const uint8_t* flags, const double* weight,
@@ -222,29 +263,34 @@ hipError_t launch_tiles(int mode, bool write_p, bool mixed, const SetConsts& sc,
     const int64_t ntiles = (n + kTileEvents - 1) / kTileEvents;
     if (ntiles == 0) return hipSuccess;
     const size_t lds = mode == kReweight ? 0 : size_t(bc.nb + 2) * kHistLanes * sizeof(double);
-    const dim3 grid{unsigned(ntiles)}, block{unsigned(kTileLanes)};
-    const SinCosTable& sctab = host::sincos_table();
-#define OSC_LAUNCH(M, W, X)                                                                      \
-    hipExtLaunchKernelGGL((tile_kernel<M, W, X>), grid, block, lds, stream, ev_begin, ev_end, 0,  \
-                          sc, sctab, pc, bc, n, ntiles, e_true, flags, weight, e_reco, bins,      \
-                          value, p_out, partial)
-    if (mode == kReweight) {
-        if (mixed) OSC_LAUNCH(kReweight, true, true);
-        else OSC_LAUNCH(kReweight, true, false);
-    } else if (mode == kPdf) {
-        if (write_p && mixed) OSC_LAUNCH(kPdf, true, true);
-        else if (write_p) OSC_LAUNCH(kPdf, true, false);
-        else if (mixed) OSC_LAUNCH(kPdf, false, true);
-        else OSC_LAUNCH(kPdf, false, false);
-    } else if (mode == kPdfBinned) {
-        if (write_p && mixed) OSC_LAUNCH(kPdfBinned, true, true);
-        else if (write_p) OSC_LAUNCH(kPdfBinned, true, false);
-        else if (mixed) OSC_LAUNCH(kPdfBinned, false, true);
-        else OSC_LAUNCH(kPdfBinned, false, false);
-    } else {
-        OSC_LAUNCH(kHist, false, false);
-    }
-#undef OSC_LAUNCH
+    const auto launch = [&](auto m, auto w, auto x) {
+        const auto with = [&](auto split) {
+            constexpr int kSplit = decltype(split)::value;
+            hipExtLaunchKernelGGL(
+                (tile_kernel<decltype(m)::value, decltype(w)::value, decltype(x)::value, kSplit>),
+                dim3{unsigned(ntiles)}, dim3{unsigned(kTileLanes * kSplit)}, lds, stream, ev_begin,
+                ev_end, 0, sc, pc, bc, n, ntiles, e_true, flags, weight, e_reco, bins, value,
+                p_out, partial);
+        };
+        constexpr int kMode = decltype(m)::value;
+        const int split = tile_split(ntiles, kMode, decltype(w)::value);
+        if (split == 4) return with(Int<4>{});
+        if constexpr (kMode != kReweight)
+            if (split == 8) return with(Int<8>{});
+        with(Int<1>{});
+    };
+    using std::false_type;
+    using std::true_type;
+    const auto by_output = [&](auto m) {
+        if (write_p && mixed) launch(m, true_type{}, true_type{});
+        else if (write_p) launch(m, true_type{}, false_type{});
+        else if (mixed) launch(m, false_type{}, true_type{});
+        else launch(m, false_type{}, false_type{});
+    };
+    if (mode == kReweight) launch(Int<kReweight>{}, true_type{}, false_type{});
+    else if (mode == kPdf) by_output(Int<kPdf>{});
+    else if (mode == kPdfBinned) by_output(Int<kPdfBinned>{});
+    else launch(Int<kHist>{}, false_type{}, false_type{});
     return hipGetLastError();
 }
 
@@ -257,20 +303,20 @@ hipError_t launch_layered_tiles(int mode, bool write_p, const SetConsts& sc,
     const int64_t ntiles = (n + kTileEvents - 1) / kTileEvents;
     if (ntiles == 0) return hipSuccess;
     const size_t lds = mode == kReweight ? 0 : size_t(bc.nb + 2) * kHistLanes * sizeof(double);
-    const dim3 grid{unsigned(ntiles)}, block{unsigned(kTileLanes)};
-    const SinCosTable& sctab = host::sincos_table();
-    if (mode == kReweight)
-        hipExtLaunchKernelGGL((layered_tile_kernel<kReweight, true>), grid, block, lds, stream,
-                              ev_begin, ev_end, 0, sc, sctab, lp, bc, n, e_true, flags, weight,
-                              e_reco, p_out, partial);
-    else if (write_p)
-        hipExtLaunchKernelGGL((layered_tile_kernel<kPdf, true>), grid, block, lds, stream,
-                              ev_begin, ev_end, 0, sc, sctab, lp, bc, n, e_true, flags, weight,
-                              e_reco, p_out, partial);
-    else
-        hipExtLaunchKernelGGL((layered_tile_kernel<kPdf, false>), grid, block, lds, stream,
-                              ev_begin, ev_end, 0, sc, sctab, lp, bc, n, e_true, flags, weight,
-                              e_reco, p_out, partial);
+    const auto launch = [&](auto m, auto w) {
+        const auto with = [&](auto split) {
+            constexpr int kSplit = decltype(split)::value;
+            hipExtLaunchKernelGGL(
+                (layered_tile_kernel<decltype(m)::value, decltype(w)::value, kSplit>),
+                dim3{unsigned(ntiles)}, dim3{unsigned(kTileLanes * kSplit)}, lds, stream, ev_begin,
+                ev_end, 0, sc, lp, bc, n, e_true, flags, weight, e_reco, p_out, partial);
+        };
+        if (layered_split(ntiles) == 8) return with(Int<8>{});
+        with(Int<1>{});
+    };
+    if (mode == kReweight) launch(Int<kReweight>{}, std::true_type{});
+    else if (write_p) launch(Int<kPdf>{}, std::true_type{});
+    else launch(Int<kPdf>{}, std::false_type{});
     return hipGetLastError();
 }
 
@@ -365,27 +411,43 @@ hipError_t occupancy(int mode, int nbins, int* blocks_per_cu)
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, f, kTileLanes, lds);
 }
 
-hipError_t set_kernel_attributes(size_t max_dyn_lds)
+namespace {
+
+// The kernels that keep histograms in dynamic LDS, with SPLIT waves a tile.
+template <int SPLIT>
+hipError_t raise_lds_limit(int bytes)
 {
-    const void* fns[] = {
-        reinterpret_cast<const void*>(&tile_kernel<kPdf, true, false>),
-        reinterpret_cast<const void*>(&tile_kernel<kPdf, false, false>),
-        reinterpret_cast<const void*>(&tile_kernel<kPdf, true, true>),
-        reinterpret_cast<const void*>(&tile_kernel<kPdf, false, true>),
-        reinterpret_cast<const void*>(&tile_kernel<kHist, false, false>),
-        reinterpret_cast<const void*>(&tile_kernel<kPdfBinned, true, false>),
-        reinterpret_cast<const void*>(&tile_kernel<kPdfBinned, false, false>),
-        reinterpret_cast<const void*>(&tile_kernel<kPdfBinned, true, true>),
-        reinterpret_cast<const void*>(&tile_kernel<kPdfBinned, false, true>),
-        reinterpret_cast<const void*>(&layered_tile_kernel<kPdf, true>),
-        reinterpret_cast<const void*>(&layered_tile_kernel<kPdf, false>),
+    std::vector<const void*> fns{
+        reinterpret_cast<const void*>(&tile_kernel<kPdf, true, false, SPLIT>),
+        reinterpret_cast<const void*>(&tile_kernel<kPdf, false, false, SPLIT>),
+        reinterpret_cast<const void*>(&tile_kernel<kPdf, true, true, SPLIT>),
+        reinterpret_cast<const void*>(&tile_kernel<kPdf, false, true, SPLIT>),
+        reinterpret_cast<const void*>(&tile_kernel<kHist, false, false, SPLIT>),
+        reinterpret_cast<const void*>(&tile_kernel<kPdfBinned, true, false, SPLIT>),
+        reinterpret_cast<const void*>(&tile_kernel<kPdfBinned, false, false, SPLIT>),
+        reinterpret_cast<const void*>(&tile_kernel<kPdfBinned, true, true, SPLIT>),
+        reinterpret_cast<const void*>(&tile_kernel<kPdfBinned, false, true, SPLIT>),
     };
+    if constexpr (SPLIT != 4) {
+        fns.push_back(reinterpret_cast<const void*>(&layered_tile_kernel<kPdf, true, SPLIT>));
+        fns.push_back(reinterpret_cast<const void*>(&layered_tile_kernel<kPdf, false, SPLIT>));
+    }
     for (const void* f : fns) {
-        hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           int(max_dyn_lds));
+        const hipError_t e =
+            hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+}  // namespace
+
+hipError_t set_kernel_attributes(size_t max_dyn_lds)
+{
+    hipError_t e = raise_lds_limit<1>(int(max_dyn_lds));
+    if (e == hipSuccess) e = raise_lds_limit<4>(int(max_dyn_lds));
+    if (e == hipSuccess) e = raise_lds_limit<8>(int(max_dyn_lds));
+    return e;
 }
 
 }  // namespace osc

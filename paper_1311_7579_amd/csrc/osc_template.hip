@@ -310,13 +310,12 @@ __global__ __launch_bounds__(kSumWaves * 64) void template_sum_kernel(
 }
 
 // P of the 18 channels at the centre of every true bin, layout P[c][t].
-__global__ __launch_bounds__(64) void centre_probs_kernel(SetConsts sc, SinCosTable sctab,
-                                                          PathConsts pc, TrueBins tb,
+__global__ __launch_bounds__(64) void centre_probs_kernel(SetConsts sc, PathConsts pc, TrueBins tb,
                                                           double* __restrict__ P)
 {
     __shared__ TileTables tabs;
     load_tab(sc, tabs, threadIdx.x);
-    load_sincos(sctab, tabs, threadIdx.x);
+    load_sincos(tabs, threadIdx.x);
     __syncthreads();
     const int64_t k = int64_t(blockIdx.x) * 64 + threadIdx.x;
     if (k >= int64_t(kTemplateChannels) * tb.nt) return;
@@ -533,7 +532,7 @@ osc_status osc_fill_pdf_bincentre(osc_ctx* ctx, const osc_template* t, int32_t s
     double* P = p_centre_out ? p_centre_out : t->d_P;
     const int64_t K = int64_t(osc::kTemplateChannels) * t->tb.nt;
     hipLaunchKernelGGL(osc::centre_probs_kernel, dim3(blocks_for(K, 64)), dim3(64), 0, s, sc,
-                       osc::host::sincos_table(), t->pc, t->tb, P);
+                       t->pc, t->tb, P);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) {
         hipLaunchKernelGGL(osc::bincentre_contract_kernel, dim3(unsigned(t->nr + 2)), dim3(64), 0,

@@ -1,0 +1,92 @@
+"""A tile shared by several waves (one, four or eight, by the number of tiles)
+gives the bits of the reduction contract: sizes on both sides of every rule,
+whole and ragged last tiles, every form that takes a histogram."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import P_TOL, assert_bits_equal
+from paper_1311_7579_amd import workload
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+NB, HI = 37, 4.0
+TILE = 1024
+
+
+@pytest.fixture(scope="module")
+def osc():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1311_7579_amd import osc as _osc
+    _osc.load()
+    return _osc
+
+
+def hist_of(s, P, hist):
+    """hist has the bits of the contract on this P."""
+    bins = oracle.bin_indices(s.e_reco, 0.0, HI, NB)
+    assert_bits_equal(hist.cpu().numpy(), oracle.hist_contract(s.weight * P, bins, NB + 2))
+
+
+@pytest.mark.parametrize("n", [1, 64, 257, TILE, TILE + 1, 768 * TILE, 768 * TILE + 1,
+                               2048 * TILE, 2048 * TILE + 65, 6144 * TILE, 6144 * TILE + 1])
+def test_constant_density_splits(osc, n):
+    s = workload.make_sample(n, 5)
+    s.flags[::97] = 15                      # invalid bytes: NaN in their bins
+    with osc.Context(0) as ctx:
+        ctx.osc_set_params([workload.TABLE1])
+        ds = osc.DeviceSample.from_host(s)
+        new = lambda m: torch.empty(m, dtype=torch.float64, device="cuda")
+        p0 = new(n)
+        ctx.osc_reweight(ds, 0, p0)
+        P = p0.cpu().numpy()
+        few = np.arange(0, n, max(1, n // 20000))
+        want = oracle.prob_batch(workload.TABLE1, s.L_km, s.rho_gcc, s.Ye, s.e_true[few],
+                                 s.flags[few])
+        ok = s.flags[few] != 15
+        assert np.isnan(P[few][~ok]).all()
+        assert np.abs(P[few] - want)[ok].max(initial=0.0) <= P_TOL
+        value = new(n).copy_(torch.from_numpy(np.nan_to_num(P)))
+        h = new(NB + 2)
+        ctx.osc_fill_hist(value, ds.weight, ds.e_reco, NB, 0.0, HI, h)
+        hist_of(s, np.nan_to_num(P), h)
+        with ctx.osc_binned_create(ds, NB, 0.0, HI) as binned:
+            for tier in (osc.OSC_FP64, osc.OSC_FP32_MIXED):
+                p, h1 = new(n), new(NB + 2)
+                ctx.osc_fill_pdf(ds, 0, NB, 0.0, HI, h1, p, precision=tier)
+                if tier == osc.OSC_FP64:
+                    assert_bits_equal(p.cpu().numpy(), P)
+                hist_of(s, p.cpu().numpy(), h1)
+                for fill in (lambda q: ctx.osc_fill_pdf(ds, 0, NB, 0.0, HI, h, q, precision=tier),
+                             lambda q: ctx.osc_fill_pdf_binned(binned, 0, h, q, precision=tier)):
+                    q = new(n)
+                    for out in (None, q):
+                        fill(out)
+                        assert_bits_equal(h.cpu().numpy(), h1.cpu().numpy())
+                    assert_bits_equal(q.cpu().numpy(), p.cpu().numpy())
+
+
+@pytest.mark.parametrize("n", [1, 257, TILE + 1, 4096 * TILE, 4096 * TILE + 3])
+def test_layered_splits(osc, n):
+    s = workload.make_sample(n, 6)
+    s.flags[::89] = 32
+    path = [(500.0, 3.0, 0.5), (1200.0, 5.0, 0.49), (300.0, 4.0, 0.5)]
+    with osc.Context(0) as ctx:
+        ctx.osc_set_params([workload.TABLE1])
+        ds = osc.DeviceSample.from_host(s)
+        new = lambda m: torch.empty(m, dtype=torch.float64, device="cuda")
+        p0, p1, h0, h1 = new(n), new(n), new(NB + 2), new(NB + 2)
+        ctx.osc_reweight_layered(ds, path, 0, p0)
+        ctx.osc_fill_pdf_layered(ds, path, 0, NB, 0.0, HI, h0, p1)
+        ctx.osc_fill_pdf_layered(ds, path, 0, NB, 0.0, HI, h1)
+        P = p0.cpu().numpy()
+        few = np.nonzero(s.flags != 32)[0][::max(1, n // 5000)]
+        want = oracle.prob_layered_batch(workload.TABLE1, path, s.e_true[few], s.flags[few])
+        assert np.abs(P[few] - want).max(initial=0.0) <= P_TOL
+        assert np.isnan(P[s.flags == 32]).all()
+        assert_bits_equal(p1.cpu().numpy(), P)
+        assert_bits_equal(h1.cpu().numpy(), h0.cpu().numpy())
+        hist_of(s, P, h0)
