@@ -281,12 +281,39 @@ def device_vec(t, name, dtype, device=None, **kw):
     return device_vecs((t, name, dtype, kw), device=device)
 
 
-def _stream(stream):
-    if stream is None:
+_torch = None
+
+
+def _load_torch():
+    global _torch
+    if _torch is None:
         import torch
+        _torch = torch
+    return _torch
+
+
+def _f64_ptr(t, n, device):
+    """The data pointer of a float64 tensor with n > 0 entries that passes
+    every check of device_vecs, else None: the calls try this first (0.3 us a
+    tensor against 1.5) and leave the other cases, absent and empty tensors
+    and the error messages among them, to device_vecs."""
+    torch = _torch or _load_torch()
+    if (n and isinstance(t, torch.Tensor) and t.dtype is torch.float64 and t.numel() == n
+            and t.is_contiguous() and t.is_cuda and t.get_device() == device):
+        return t.data_ptr()
+    return None
+
+
+def _stream(stream):
+    """The raw handle of a stream (torch's current stream when None)."""
+    if stream is None:
+        torch = _torch or _load_torch()
+        if torch.cuda.is_initialized():
+            # the same handle as torch.cuda.current_stream().cuda_stream,
+            # without the 3 us it takes to build the stream object
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         stream = torch.cuda.current_stream()
-    handle = getattr(stream, "cuda_stream", stream)
-    return ctypes.c_void_p(int(handle))
+    return int(getattr(stream, "cuda_stream", stream))
 
 
 def osc_reduction_layout():
@@ -328,8 +355,10 @@ class DeviceSample:
         return self.e_true.device.index
 
     def c_struct(self) -> osc_sample:
-        return osc_sample(self.n, _ptr(self.e_true), _ptr(self.flags), _ptr(self.weight),
-                          _ptr(self.e_reco), float(self.L_km), float(self.rho_gcc), float(self.Ye))
+        e, w, x = self.e_true, self.weight, self.e_reco
+        return osc_sample(e.numel(), e.data_ptr(), self.flags.data_ptr(),
+                          None if w is None else w.data_ptr(), None if x is None else x.data_ptr(),
+                          float(self.L_km), float(self.rho_gcc), float(self.Ye))
 
     def require_hist_inputs(self):
         if self.weight is None or self.e_reco is None:
@@ -412,12 +441,26 @@ class Context:
     def _sample(self, sample, hist_inputs):
         if not isinstance(sample, DeviceSample):
             raise ValueError("sample must be a DeviceSample")
-        if sample.device not in (None, self.device):
+        if sample.e_true.get_device() != self.device and sample.device not in (None, self.device):
             raise ValueError(f"the sample is on GPU {sample.device}, the context on "
                              f"GPU {self.device}")
         if hist_inputs:
             sample.require_hist_inputs()
         return sample.c_struct()
+
+    def _out(self, hist_out, nbins, p_out, n):
+        """Checked data pointers of a call's histogram and optional P."""
+        nbins = int(nbins)
+        hp = _f64_ptr(hist_out, nbins + 2, self.device) if nbins > 0 else None
+        if hp is not None:
+            if p_out is None:
+                return hp, None
+            pp = _f64_ptr(p_out, n, self.device)
+            if pp is not None:
+                return hp, pp
+        return device_vecs(self._hist(hist_out, nbins),
+                           (p_out, "p_out", "float64", dict(n=n, optional=True)),
+                           device=self.device)
 
     @staticmethod
     def _hist(hist_out, nbins):
@@ -427,16 +470,15 @@ class Context:
 
     def osc_reweight(self, sample: DeviceSample, set_index, p_out, stream=None):
         cs = self._sample(sample, False)
-        pp = device_vec(p_out, "p_out", "float64", n=sample.n, device=self.device)
+        pp = (_f64_ptr(p_out, cs.n, self.device) or
+              device_vec(p_out, "p_out", "float64", n=cs.n, device=self.device))
         _check(load().osc_reweight(self.handle, ctypes.byref(cs), int(set_index), pp,
                                    _stream(stream)), "osc_reweight")
 
     def osc_fill_pdf(self, sample: DeviceSample, set_index, nbins, lo, hi, hist_out,
                      p_out=None, precision=OSC_FP64, stream=None, e_scale=0.0):
         cs = self._sample(sample, True)
-        hp, pp = device_vecs(self._hist(hist_out, nbins),
-                             (p_out, "p_out", "float64", dict(n=sample.n, optional=True)),
-                             device=self.device)
+        hp, pp = self._out(hist_out, nbins, p_out, cs.n)
         b = osc_binning(int(nbins), float(lo), float(hi), float(e_scale))
         _check(load().osc_fill_pdf(self.handle, ctypes.byref(cs), int(set_index), ctypes.byref(b),
                                    int(precision), hp, pp, _stream(stream)),
@@ -448,9 +490,7 @@ class Context:
         scratch array (OSC_NOALLOC_SCRATCH_BYTES per GPU) holds the tile
         results; calls that overlap on one GPU race."""
         cs = self._sample(sample, True)
-        hp, pp = device_vecs(self._hist(hist_out, nbins),
-                             (p_out, "p_out", "float64", dict(n=sample.n, optional=True)),
-                             device=self.device)
+        hp, pp = self._out(hist_out, nbins, p_out, cs.n)
         b = osc_binning(int(nbins), float(lo), float(hi), float(e_scale))
         _check(load().osc_fill_pdf_noalloc(self.handle, ctypes.byref(cs), int(set_index),
                                            ctypes.byref(b), int(precision), hp, pp,
@@ -472,9 +512,7 @@ class Context:
                             stream=None):
         if not isinstance(binned, BinnedSample) or binned.ctx is not self or not binned.handle:
             raise ValueError("binned must be a live BinnedSample of this context")
-        hp, pp = device_vecs(self._hist(hist_out, binned.nbins),
-                             (p_out, "p_out", "float64", dict(n=binned.sample.n, optional=True)),
-                             device=self.device)
+        hp, pp = self._out(hist_out, binned.nbins, p_out, binned.sample.n)
         _check(load().osc_fill_pdf_binned(self.handle, binned.handle, int(set_index),
                                           int(precision), hp, pp, _stream(stream)),
                "osc_fill_pdf_binned")
@@ -491,7 +529,8 @@ class Context:
 
     def osc_reweight_layered(self, sample: DeviceSample, layers, set_index, p_out, stream=None):
         cs = self._sample(sample, False)
-        pp = device_vec(p_out, "p_out", "float64", n=sample.n, device=self.device)
+        pp = (_f64_ptr(p_out, cs.n, self.device) or
+              device_vec(p_out, "p_out", "float64", n=cs.n, device=self.device))
         arr = layers_array(layers)
         _check(load().osc_reweight_layered(self.handle, ctypes.byref(cs), arr, len(arr),
                                            int(set_index), pp, _stream(stream)),
@@ -500,9 +539,7 @@ class Context:
     def osc_fill_pdf_layered(self, sample: DeviceSample, layers, set_index, nbins, lo, hi,
                              hist_out, p_out=None, stream=None, e_scale=0.0):
         cs = self._sample(sample, True)
-        hp, pp = device_vecs(self._hist(hist_out, nbins),
-                             (p_out, "p_out", "float64", dict(n=sample.n, optional=True)),
-                             device=self.device)
+        hp, pp = self._out(hist_out, nbins, p_out, cs.n)
         arr = layers_array(layers)
         b = osc_binning(int(nbins), float(lo), float(hi), float(e_scale))
         _check(load().osc_fill_pdf_layered(self.handle, ctypes.byref(cs), arr, len(arr),
@@ -528,6 +565,17 @@ class Context:
         nbins = int(data.shape[-1])
         if nbins < 1:
             raise ValueError("data must have at least one bin")
+        tensor = (_torch or _load_torch()).Tensor
+        hp = dp = op = None
+        if isinstance(hist, tensor) and isinstance(data, tensor):
+            n_hist, n_data = hist.numel() // (nbins + 2), data.numel() // nbins
+            hp = _f64_ptr(hist, n_hist * (nbins + 2), self.device)
+            dp = _f64_ptr(data, n_data * nbins, self.device)
+            op = _f64_ptr(nll_out, n_hist, self.device)
+        if hp and dp and op:
+            _check(load().osc_poisson_nll(self.handle, hp, n_hist, float(mu_scale), dp, n_data,
+                                          nbins, op, _stream(stream)), "osc_poisson_nll")
+            return
         _vec_layout(hist, "hist", "float64", multiple_of=nbins + 2)
         _vec_layout(data, "data", "float64", multiple_of=nbins)
         n_hist = int(hist.numel() // (nbins + 2))
@@ -596,10 +644,13 @@ class Template:
         return out
 
     def fill_pdf(self, set_index, hist_out, p_centre_out=None, stream=None):
-        hp, cp = device_vecs(self.ctx._hist(hist_out, self.nr),
-                             (p_centre_out, "p_centre_out", "float64",
-                              dict(n=N_CHANNELS * self.nt, optional=True)),
-                             device=self.ctx.device)
+        hp = _f64_ptr(hist_out, self.nr + 2, self.ctx.device)
+        cp = _f64_ptr(p_centre_out, N_CHANNELS * self.nt, self.ctx.device)
+        if hp is None or (cp is None and p_centre_out is not None):
+            hp, cp = device_vecs(self.ctx._hist(hist_out, self.nr),
+                                 (p_centre_out, "p_centre_out", "float64",
+                                  dict(n=N_CHANNELS * self.nt, optional=True)),
+                                 device=self.ctx.device)
         _check(load().osc_fill_pdf_bincentre(self.ctx.handle, self.handle, int(set_index), hp, cp,
                                              _stream(stream)), "osc_fill_pdf_bincentre")
 
