@@ -917,19 +917,17 @@ __device__ __forceinline__ void tile_events(const PROB& prob, const BinConsts& b
 // A tile shared by the SPLIT waves of a workgroup: wave v computes events m =
 // v K / SPLIT .. (v + 1) K / SPLIT - 1 of every lane (all their loads in flight
 // at once), then the waves add their contributions one after the other, so
-// that every accumulator still takes its additions in ascending m.
+// that every accumulator still takes its additions in ascending m.  (Issuing
+// the loads before the workgroup builds its tables delayed the tables: 16.2
+// against 14.8 us at 2e6 events.)
 template <int MODE, bool WRITE_P, int SPLIT, class PROB>
 __device__ __forceinline__ void split_tile_events(const PROB& prob, const BinConsts& bc,
-                                                  double* hist, int wave, int lane, uint32_t n,
-                                                  const double* e_true, const uint8_t* flags,
-                                                  const double* weight, const double* e_reco,
-                                                  const uint16_t* bins, const double* value,
-                                                  double* p_out)
+                                                  double* hist, const TileBufs& bufs, int wave,
+                                                  int lane, uint32_t n)
 {
     constexpr int kShare = kLaneEvents / SPLIT;
     constexpr bool kComputeBins = has_hist(MODE) && !reads_bins(MODE);
     const uint32_t l = uint32_t(lane);
-    const TileBufs bufs = tile_bufs<MODE>(n, e_true, flags, weight, e_reco, bins, value, p_out);
     EventIn ev[kShare];
 #pragma unroll
     for (int j = 0; j < kShare; ++j)
@@ -1071,12 +1069,13 @@ __device__ __forceinline__ void hist_zero(double* hist, int thread, int nbt)
 
 // Tree over the 64 lanes of every bin of a finished tile, written as row
 // `row` of the tile results at `out` (chunked bin-major layout).
+// With `only` it is the histogram itself, bin after bin.
 template <int THREADS = kTileLanes>
 __device__ __forceinline__ void tile_write(const double* hist, int thread, int nbt, int64_t row,
-                                           double* out)
+                                           double* out, bool only = false)
 {
     for (int bin = thread; bin < nbt; bin += THREADS)
-        out[partial_index(row, bin, nbt)] =
+        out[only ? bin : partial_index(row, bin, nbt)] =
             lane_tree<kHistLanes, 0>(hist, lds_row_of_output(bin, nbt - 2));
 }
 
@@ -1090,15 +1089,15 @@ __device__ __forceinline__ double wave_tree(double v)
 }
 
 // One merge level (see MergeLevel): block (gc, bin, set) reduces chunk gc
-// of the set's input rows for one bin.  Thread t adds its kMergeThreadRows
-// contiguous rows (+0.0 beyond the sample's rows) as a binary tree in
-// registers; the 64 lanes of a wave meet in the butterfly tree and the
-// block's waves in a last binary tree.
-template <bool FINAL>
+// of the set's input rows for one bin.  Thread t adds its ROWS contiguous
+// rows (+0.0 beyond the sample's rows) as a binary tree in registers; the 64
+// lanes of a wave meet in the butterfly tree and the block's waves in a last
+// binary tree.
+template <bool FINAL, int WAVES, int ROWS>
 __device__ __forceinline__ void merge_level_block(const MergeLevel& L, const double* __restrict__ in,
                                                   double* __restrict__ out)
 {
-    __shared__ double wave_sum[kMergeWaves];
+    __shared__ double wave_sum[WAVES];
     const int nbt = L.nbt;
     const int bin = int(blockIdx.y);
     const int64_t gc = blockIdx.x, set = blockIdx.z;
@@ -1106,39 +1105,41 @@ __device__ __forceinline__ void merge_level_block(const MergeLevel& L, const dou
     while (s + 1 < L.n_samples && gc >= L.chunk0[s + 1]) ++s;
     const int64_t c = gc - L.chunk0[s];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int64_t first = c * kMergeChunkRows + int64_t(t) * kMergeThreadRows;
+    const int64_t first = c * (WAVES * 64 * ROWS) + int64_t(t) * ROWS;
     const int64_t count = L.rows[s] - first;
     const double* src = in + set * L.set_stride_in + partial_index(L.in_row0[s] + first, bin, nbt);
-    double v[kMergeThreadRows];
-    if (count >= kMergeThreadRows) {
+    double v[ROWS];
+    if (count >= ROWS) {
 #pragma unroll
-        for (int i = 0; i < kMergeThreadRows; ++i) v[i] = src[i];
+        for (int i = 0; i < ROWS; ++i) v[i] = src[i];
     } else {
 #pragma unroll
-        for (int i = 0; i < kMergeThreadRows; ++i) v[i] = i < count ? src[i] : 0.0;
+        for (int i = 0; i < ROWS; ++i) v[i] = i < count ? src[i] : 0.0;
     }
 #pragma unroll
-    for (int w = kMergeThreadRows / 2; w >= 1; w >>= 1)
+    for (int w = ROWS / 2; w >= 1; w >>= 1)
 #pragma unroll
         for (int i = 0; i < w; ++i) v[i] = v[2 * i] + v[2 * i + 1];
-    const double r = wave_tree(v[0]);
-    if (lane == 0) wave_sum[wave] = r;
-    __syncthreads();
-    if (t == 0) {
+    double total = wave_tree(v[0]);
+    if constexpr (WAVES > 1) {
+        if (lane == 0) wave_sum[wave] = total;
+        __syncthreads();
+        if (t != 0) return;
         // binary tree over the waves' sums, in wave order
-        double w[kMergeWaves];
+        double w[WAVES];
 #pragma unroll
-        for (int i = 0; i < kMergeWaves; ++i) w[i] = wave_sum[i];
+        for (int i = 0; i < WAVES; ++i) w[i] = wave_sum[i];
 #pragma unroll
-        for (int h = kMergeWaves / 2; h >= 1; h >>= 1)
+        for (int h = WAVES / 2; h >= 1; h >>= 1)
 #pragma unroll
             for (int i = 0; i < h; ++i) w[i] = w[2 * i] + w[2 * i + 1];
-        const double total = w[0];
-        if (FINAL)
-            out[(set * L.n_samples + s) * nbt + bin] = total;
-        else
-            out[set * L.set_stride_out + partial_index(L.out_row0[s] + c, bin, nbt)] = total;
+        total = w[0];
     }
+    if (t != 0) return;
+    if (FINAL)
+        out[(set * L.n_samples + s) * nbt + bin] = total;
+    else
+        out[set * L.set_stride_out + partial_index(L.out_row0[s] + c, bin, nbt)] = total;
 }
 
 }  // namespace dev

@@ -261,6 +261,14 @@ ProfRec* prof_begin(osc_ctx* ctx, hipStream_t)
     return &ctx->prof.back();
 }
 
+// A call without a merge: the record ends with the per-event kernel.
+void prof_no_merge(ProfRec* r)
+{
+    if (!r) return;
+    (void)hipEventDestroy(r->end);
+    r->end = nullptr;
+}
+
 void prof_mark(hipEvent_t ev, hipStream_t stream)
 {
     if (ev) (void)hipEventRecord(ev, stream);
@@ -417,12 +425,13 @@ hipError_t osc::host::enqueue_fill(const osc::SetConsts& sc, const osc_sample* s
 {
     const osc::BinConsts bc = bin_consts(binning);
     const int64_t tiles = (sample->n + osc::kTileEvents - 1) / osc::kTileEvents;
-    const osc::MergePlan plan = osc::plan_merge(&tiles, 1, bc.nb + 2);
     hipError_t e = osc::launch_tiles(bins ? 3 : 1, p_out != nullptr, mixed, sc,
                                      path_consts(sample), bc, sample->n, sample->e_true,
                                      sample->flags, sample->weight, bins ? nullptr : sample->e_reco,
-                                     bins, nullptr, p_out, partials, stream);
-    if (e == hipSuccess) e = osc::launch_merge(plan, 1, partials, hist_out, stream);
+                                     bins, nullptr, p_out, tiles == 1 ? hist_out : partials,
+                                     stream);
+    if (e == hipSuccess && tiles != 1)
+        e = osc::launch_merge(osc::plan_merge(&tiles, 1, bc.nb + 2), 1, partials, hist_out, stream);
     return e;
 }
 
@@ -442,23 +451,25 @@ using osc::host::set_consts;
 
 // The per-event kernel and the merge of one histogram on `stream`, with
 // the tile results and level buffers in `partials` (merge_scratch_bytes of
-// `plan`).  t0 / t1 (nullable) receive the per-event kernel's own begin and
+// `plan`; a sample of one tile needs neither: its result is the histogram).
+// t0 / t1 (nullable) receive the per-event kernel's own begin and
 // end times.
 hipError_t enqueue_hist(int mode, bool write_p, bool mixed, const osc::SetConsts& sc,
                         const osc::PathConsts& pc, const osc::BinConsts& bc, int64_t n,
                         const double* e_true, const uint8_t* flags, const double* weight,
                         const double* e_reco, const uint16_t* bins, const double* value,
-                        double* p_out, double* hist_out, const osc::MergePlan& plan,
+                        double* p_out, double* hist_out, const osc::MergePlan* plan,
                         double* partials, hipStream_t stream, const osc::LayerPath* lp,
                         hipEvent_t t0, hipEvent_t t1)
 {
+    if (!plan) partials = hist_out;
     hipError_t e = lp ? osc::launch_layered_tiles(mode, write_p, sc, *lp, bc, n, e_true, flags,
                                                   weight, e_reco, p_out, partials, stream, t0,
                                                   t1)
                       : osc::launch_tiles(mode, write_p, mixed, sc, pc, bc, n, e_true, flags,
                                           weight, e_reco, bins, value, p_out, partials, stream,
                                           t0, t1);
-    if (e == hipSuccess) e = osc::launch_merge(plan, 1, partials, hist_out, stream);
+    if (e == hipSuccess && plan) e = osc::launch_merge(*plan, 1, partials, hist_out, stream);
     return e;
 }
 
@@ -472,13 +483,22 @@ osc_status run_hist(osc_ctx* ctx, int mode, bool write_p, bool mixed, const osc:
                     const osc::LayerPath* lp = nullptr)
 {
     const int64_t tiles = (n + osc::kTileEvents - 1) / osc::kTileEvents;
+    if (tiles == 1) {   // one launch, no scratch, nothing to merge
+        ProfRec* pr = prof_begin(ctx, stream);
+        const hipError_t e = enqueue_hist(mode, write_p, mixed, sc, pc, bc, n, e_true, flags,
+                                          weight, e_reco, bins, value, p_out, hist_out, nullptr,
+                                          nullptr, stream, lp, pr ? pr->start : nullptr,
+                                          pr ? pr->mid : nullptr);
+        prof_no_merge(pr);
+        return device_status(e);
+    }
     const osc::MergePlan plan = osc::plan_merge(&tiles, 1, bc.nb + 2);
     Scratch* s = nullptr;
     osc_status st = acquire_scratch(ctx, osc::merge_scratch_bytes(plan, 1), stream, &s);
     if (st != OSC_OK) return st;
     ProfRec* pr = prof_begin(ctx, stream);
     const hipError_t e = enqueue_hist(mode, write_p, mixed, sc, pc, bc, n, e_true, flags, weight,
-                                      e_reco, bins, value, p_out, hist_out, plan,
+                                      e_reco, bins, value, p_out, hist_out, &plan,
                                       static_cast<double*>(s->ptr), stream, lp,
                                       pr ? pr->start : nullptr, pr ? pr->mid : nullptr);
     if (pr) prof_mark(pr->end, stream);
@@ -615,10 +635,7 @@ osc_status osc_reweight(osc_ctx* ctx, const osc_sample* sample, int32_t set, dou
                                            sample->n, sample->e_true, sample->flags, nullptr,
                                            nullptr, nullptr, nullptr, p_out, nullptr, hs,
                                            pr ? pr->start : nullptr, pr ? pr->mid : nullptr);
-    if (pr) {
-        (void)hipEventDestroy(pr->end);
-        pr->end = nullptr;
-    }
+    prof_no_merge(pr);
     return device_status(e);
 }
 
@@ -657,7 +674,8 @@ osc_status osc_fill_pdf_noalloc(osc_ctx* ctx, const osc_sample* sample, int32_t 
     const hipError_t e = enqueue_hist(
         1, p_out != nullptr, precision == OSC_FP32_MIXED, ctx->consts[size_t(set)],
         path_consts(sample), bc, sample->n, sample->e_true, sample->flags, sample->weight,
-        sample->e_reco, nullptr, nullptr, p_out, hist_out, plan, ctx->noalloc,
+        sample->e_reco, nullptr, nullptr, p_out, hist_out, tiles == 1 ? nullptr : &plan,
+        ctx->noalloc,
         static_cast<hipStream_t>(stream), nullptr, nullptr, nullptr);
     return device_status(e);
 }
@@ -785,10 +803,7 @@ osc_status osc_reweight_layered(osc_ctx* ctx, const osc_sample* sample, const os
         0, true, ctx->consts[size_t(set)], layer_path(ctx->params[size_t(set)], layers, n_layers), bc, sample->n,
         sample->e_true, sample->flags, nullptr, nullptr, p_out, nullptr, hs,
         pr ? pr->start : nullptr, pr ? pr->mid : nullptr);
-    if (pr) {
-        (void)hipEventDestroy(pr->end);
-        pr->end = nullptr;
-    }
+    prof_no_merge(pr);
     return device_status(e);
 }
 

@@ -36,24 +36,16 @@ constexpr int kLayeredWavesPerSimd = 3;   // 4 and 5 run within 1 % of it
 
 // Largest event count accepted.
 constexpr int64_t kMaxEvents = int64_t(1) << 32;
-// Histogram merge: launches of 1024-thread blocks, one block per (chunk of
-// kMergeChunkRows = 16384 rows, bin, parameter set); thread t of a block
-// adds rows 16 t .. 16 t + 15 of its chunk as a binary tree, and the
-// block's threads meet in a binary tree (the 64 lanes of a wave, then the
-// 16 waves) -- one aligned subtree of the tile tree per block, so the
-// thread count changes no bits (1024 threads ran the one-level merge of
-// 9766 tiles in 7.1 us per call against 8.1 us with 256).  Levels repeat
-// until one row per histogram is left (one level up to kMergeChunkRows
-// tiles, i.e. 1.6e7 events, per sample).  Rows are stored bin-major
-// within chunks of kLayoutChunk rows (partial_index), so a thread's rows
-// of one bin are contiguous.  The macro exists for build-time sweeps.
-#ifndef OSC_MERGE_THREADS
-#define OSC_MERGE_THREADS 1024
-#endif
-constexpr int kMergeThreads = OSC_MERGE_THREADS;
-constexpr int kMergeWaves = kMergeThreads / 64;
-constexpr int kMergeThreadRows = 16384 / kMergeThreads;
-constexpr int64_t kMergeChunkRows = int64_t(kMergeThreads) * kMergeThreadRows;
+// Histogram merge: one block per (chunk of rows, bin, parameter set) forms
+// one aligned subtree of the tile tree: thread t adds kRows contiguous rows as
+// a binary tree in registers, and the block's threads meet in a binary tree
+// (the 64 lanes of a wave, then the waves).  The shape of a block changes no
+// bits, so it follows the largest sample's row count (merge_shape).  A chunk
+// is at most 1024 threads x 64 rows; one level serves samples up to 65536
+// tiles (6.7e7 events), a second one the rest.  Rows are stored bin-major
+// within chunks of kLayoutChunk rows (partial_index), so a thread's rows of
+// one bin are contiguous.
+constexpr int64_t kMergeMaxRows = 65536;
 constexpr int kLayoutChunk = 128;
 constexpr int kMaxBatchSamples = 16;
 // Largest number of parameter sets of one batch (the merge grid's z extent).
@@ -62,8 +54,8 @@ constexpr int kMaxBatchSets = 65535;
 // One level of the merge for n_samples samples (x any number of parameter
 // sets, one set per grid layer z): sample s has rows[s] input rows stored
 // from row in_row0[s] (a multiple of kLayoutChunk) of the set's input
-// region, takes blocks chunk0[s] .. and produces ceil(rows[s] /
-// kMergeChunkRows) (at least one) output rows, stored from row out_row0[s]
+// region, takes blocks chunk0[s] .. and produces ceil(rows[s] / chunk rows)
+// (at least one) output rows, stored from row out_row0[s]
 // (a multiple of kLayoutChunk) of the set's output region.  The final level
 // writes hist[set][sample][bin] instead.
 struct MergeLevel {

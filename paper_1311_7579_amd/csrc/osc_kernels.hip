@@ -34,7 +34,6 @@ __global__ __launch_bounds__(kTileLanes * SPLIT)
 __attribute__((amdgpu_waves_per_eu(kTileWavesPerSimd)))
 void tile_kernel(
     SetConsts sc, PathConsts pc, BinConsts bc, int64_t n,
-    [[maybe_unused]] int64_t ntiles,
     const double* __restrict__ e_true, const uint8_t* __restrict__ flags,
     const double* __restrict__ weight, const double* __restrict__ e_reco,
     const uint16_t* __restrict__ bins, const double* __restrict__ value,
@@ -46,6 +45,11 @@ void tile_kernel(
     const int thread = threadIdx.x;
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
     const int nbt = bc.nb + 2;
+    const TileArrays t = tile_arrays(tile, n, e_true, flags, weight, e_reco, bins, value, p_out);
+    const int wave = __builtin_amdgcn_readfirstlane(thread / kTileLanes);
+    const int lane = thread % kTileLanes;
+    const TileBufs bufs = tile_bufs<MODE>(t.n, t.e_true, t.flags, t.weight, t.e_reco, t.bins,
+                                          t.value, t.p_out);
 
     if (MODE != kHist) {
         load_tab(sc, tabs, thread);
@@ -56,23 +60,18 @@ void tile_kernel(
 
     const ConstDensityProb<MIXED> prob{&sc, &tabs, pc.kA, pc.kL,
                                        MIXED ? PolyRegs{} : PolyRegs::in_vgprs()};
-    const TileArrays t = tile_arrays(tile, n, e_true, flags, weight, e_reco, bins, value, p_out);
-    if constexpr (SPLIT > 1) {
-        const int wave = __builtin_amdgcn_readfirstlane(thread / kTileLanes);
-        split_tile_events<MODE, WRITE_P, SPLIT>(prob, bc, hist, wave, thread % kTileLanes, t.n,
-                                                t.e_true, t.flags, t.weight, t.e_reco, t.bins,
-                                                t.value, t.p_out);
-    } else if (t.n == kTileEvents) {
+    if constexpr (SPLIT > 1)
+        split_tile_events<MODE, WRITE_P, SPLIT>(prob, bc, hist, bufs, wave, lane, t.n);
+    else if (t.n == kTileEvents)
         tile_events<MODE, WRITE_P, true, WRITE_P>(prob, bc, hist, thread, t.n, t.e_true, t.flags,
                                                   t.weight, t.e_reco, t.bins, t.value, t.p_out);
-    } else {
+    else
         tile_events<MODE, WRITE_P, false, WRITE_P>(prob, bc, hist, thread, t.n, t.e_true, t.flags,
                                                    t.weight, t.e_reco, t.bins, t.value, t.p_out);
-    }
 
     if (MODE != kReweight) {
         if (SPLIT == 1) __syncthreads();   // split tiles end with a barrier
-        tile_write<kTileLanes * SPLIT>(hist, thread, nbt, tile, partial);
+        tile_write<kTileLanes * SPLIT>(hist, thread, nbt, tile, partial, gridDim.x == 1);
     }
 }
 
@@ -93,6 +92,12 @@ void layered_tile_kernel(SetConsts sc, LayerPath lp, BinConsts bc, int64_t n,
     const int thread = threadIdx.x;
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
     const int nbt = bc.nb + 2;
+    const TileArrays t =
+        tile_arrays(tile, n, e_true, flags, weight, e_reco, nullptr, nullptr, p_out);
+    const int wave = __builtin_amdgcn_readfirstlane(thread / kTileLanes);
+    const int lane = thread % kTileLanes;
+    const TileBufs bufs = tile_bufs<MODE>(t.n, t.e_true, t.flags, t.weight, t.e_reco, nullptr,
+                                          nullptr, t.p_out);
 
     load_tab(lp, tabs, thread);
     load_sincos(tabs, thread);
@@ -100,33 +105,27 @@ void layered_tile_kernel(SetConsts sc, LayerPath lp, BinConsts bc, int64_t n,
     __syncthreads();
 
     const LayeredProb prob{&sc, &tabs, &lp};
-    const TileArrays t =
-        tile_arrays(tile, n, e_true, flags, weight, e_reco, nullptr, nullptr, p_out);
-    if constexpr (SPLIT > 1) {
-        const int wave = __builtin_amdgcn_readfirstlane(thread / kTileLanes);
-        split_tile_events<MODE, WRITE_P, SPLIT>(prob, bc, hist, wave, thread % kTileLanes, t.n,
-                                                t.e_true, t.flags, t.weight, t.e_reco, nullptr,
-                                                nullptr, t.p_out);
-    } else if (t.n == kTileEvents) {
+    if constexpr (SPLIT > 1)
+        split_tile_events<MODE, WRITE_P, SPLIT>(prob, bc, hist, bufs, wave, lane, t.n);
+    else if (t.n == kTileEvents)
         tile_events<MODE, WRITE_P, true, true>(prob, bc, hist, thread, t.n, t.e_true, t.flags,
                                                t.weight, t.e_reco, nullptr, nullptr, t.p_out);
-    } else {
+    else
         tile_events<MODE, WRITE_P, false, true>(prob, bc, hist, thread, t.n, t.e_true, t.flags,
                                                 t.weight, t.e_reco, nullptr, nullptr, t.p_out);
-    }
 
     if (MODE != kReweight) {
         if (SPLIT == 1) __syncthreads();   // split tiles end with a barrier
-        tile_write<kTileLanes * SPLIT>(hist, thread, nbt, tile, partial);
+        tile_write<kTileLanes * SPLIT>(hist, thread, nbt, tile, partial, gridDim.x == 1);
     }
 }
 
-template <bool FINAL>
-__global__ __launch_bounds__(kMergeThreads) void merge_level_kernel(MergeLevel L,
-                                                                   const double* __restrict__ in,
-                                                                   double* __restrict__ out)
+template <bool FINAL, int WAVES, int ROWS>
+__global__ __launch_bounds__(WAVES * 64) void merge_level_kernel(MergeLevel L,
+                                                                 const double* __restrict__ in,
+                                                                 double* __restrict__ out)
 {
-    merge_level_block<FINAL>(L, in, out);
+    merge_level_block<FINAL, WAVES, ROWS>(L, in, out);
 }
 
 // Eq. (2) as a product of Poisson probabilities over the regular bins:
@@ -269,8 +268,8 @@ hipError_t launch_tiles(int mode, bool write_p, bool mixed, const SetConsts& sc,
             hipExtLaunchKernelGGL(
                 (tile_kernel<decltype(m)::value, decltype(w)::value, decltype(x)::value, kSplit>),
                 dim3{unsigned(ntiles)}, dim3{unsigned(kTileLanes * kSplit)}, lds, stream, ev_begin,
-                ev_end, 0, sc, pc, bc, n, ntiles, e_true, flags, weight, e_reco, bins, value,
-                p_out, partial);
+                ev_end, 0, sc, pc, bc, n, e_true, flags, weight, e_reco, bins, value, p_out,
+                partial);
         };
         constexpr int kMode = decltype(m)::value;
         const int split = tile_split(ntiles, kMode, decltype(w)::value);
@@ -320,11 +319,32 @@ hipError_t launch_layered_tiles(int mode, bool write_p, const SetConsts& sc,
     return hipGetLastError();
 }
 
-// A level divides every sample's row count by kMergeChunkRows (rounding
+// A level divides every sample's row count by at most kMergeMaxRows (rounding
 // up), so two levels reduce the largest accepted sample to one row.
-static_assert(kMaxEvents / kTileEvents <= kMergeChunkRows * kMergeChunkRows &&
-                  kMaxMergeLevels >= 2,
+static_assert(kMaxEvents / kTileEvents <= kMergeMaxRows * kMergeMaxRows && kMaxMergeLevels >= 2,
               "the merge plan's level capacity covers every accepted sample");
+
+namespace {
+
+// Threads and rows per thread of a merge block, for samples of up to `rows`
+// rows: few waves for few rows (most of a large block's threads would only
+// wait for the others), and one launch instead of two up to 65536 rows: at
+// 19532 rows x 52 bins 10.2 us from the per-event kernel's end against 12.9
+// with two levels.
+constexpr int64_t kScratchChunk = 16384;
+struct MergeShape {
+    int waves, rows;
+};
+MergeShape merge_shape(int64_t rows)
+{
+    if (rows <= 1024) return {1, 16};
+    if (rows <= 4096) return {4, 16};
+    if (rows <= 16384) return {16, 16};
+    if (rows <= 32768) return {16, 32};
+    return {16, 64};
+}
+
+}  // namespace
 
 MergePlan plan_merge(const int64_t* tiles, int n_samples, int nbt)
 {
@@ -339,16 +359,32 @@ MergePlan plan_merge(const int64_t* tiles, int n_samples, int nbt)
         row0[s] = in_rows;
         in_rows += align(rows[s]);
     }
-    int64_t level_max = 0;
+    // The level buffers are sized for chunks of kScratchChunk rows, the figure
+    // that include/osc.h states and budgets are counted in; the chunks of the
+    // levels are at least as large wherever a second level is needed.
+    int64_t level_rows = 0;
+    bool level_buffers = false;
+    for (int s = 0; s < n_samples; ++s) {
+        level_rows += align((rows[s] + kScratchChunk - 1) / kScratchChunk + (rows[s] == 0));
+        level_buffers |= rows[s] > kScratchChunk;
+    }
+    p.level_set_stride = level_buffers ? level_rows * nbt : 0;
     for (bool first = true;; first = false) {
-        MergeLevel L{};
+        MergeLevel& L = p.levels[p.n_levels];
+        L = MergeLevel{};
         L.n_samples = n_samples;
         L.nbt = nbt;
+        int64_t most = 0;
+        for (int s = 0; s < n_samples; ++s) most = std::max(most, rows[s]);
+        const MergeShape shape = merge_shape(most);
+        const int64_t chunk = int64_t(shape.waves) * 64 * shape.rows;
+        p.waves[p.n_levels] = shape.waves;
+        p.thread_rows[p.n_levels] = shape.rows;
         int64_t chunks = 0, out_rows = 0;
         bool final_level = true;
         for (int s = 0; s < n_samples; ++s) {
             const int64_t r = rows[s];
-            const int64_t ch = r > kMergeChunkRows ? (r + kMergeChunkRows - 1) / kMergeChunkRows : 1;
+            const int64_t ch = r > chunk ? (r + chunk - 1) / chunk : 1;
             L.rows[s] = r;
             L.in_row0[s] = row0[s];
             L.chunk0[s] = chunks;
@@ -363,13 +399,10 @@ MergePlan plan_merge(const int64_t* tiles, int n_samples, int nbt)
         L.set_stride_in = in_rows * nbt;
         L.set_stride_out = final_level ? 0 : out_rows * nbt;
         if (first) p.tile_set_stride = L.set_stride_in;
-        else level_max = std::max(level_max, L.set_stride_in);
-        if (!final_level) level_max = std::max(level_max, L.set_stride_out);
-        p.levels[p.n_levels++] = L;
+        ++p.n_levels;
         in_rows = out_rows;
         if (final_level) break;
     }
-    p.level_set_stride = level_max;
     return p;
 }
 
@@ -389,12 +422,20 @@ hipError_t launch_merge(const MergePlan& p, int64_t n_sets, double* scratch, dou
         const dim3 grid{unsigned(L.total_chunks), unsigned(p.nbt), unsigned(n_sets)};
         const bool final_level = l + 1 == p.n_levels;
         double* out = final_level ? hist_out : bufs[l % 2];
-        if (final_level)
-            hipLaunchKernelGGL(merge_level_kernel<true>, grid, dim3(kMergeThreads), 0, stream, L,
-                               in, out);
-        else
-            hipLaunchKernelGGL(merge_level_kernel<false>, grid, dim3(kMergeThreads), 0, stream, L,
-                               in, out);
+        const auto launch = [&](auto waves, auto rows) {
+            constexpr int W = decltype(waves)::value, R = decltype(rows)::value;
+            if (final_level)
+                hipLaunchKernelGGL((merge_level_kernel<true, W, R>), grid, dim3(W * 64), 0, stream,
+                                   L, in, out);
+            else
+                hipLaunchKernelGGL((merge_level_kernel<false, W, R>), grid, dim3(W * 64), 0, stream,
+                                   L, in, out);
+        };
+        if (p.waves[l] == 1) launch(Int<1>{}, Int<16>{});
+        else if (p.waves[l] == 4) launch(Int<4>{}, Int<16>{});
+        else if (p.thread_rows[l] == 16) launch(Int<16>{}, Int<16>{});
+        else if (p.thread_rows[l] == 32) launch(Int<16>{}, Int<32>{});
+        else launch(Int<16>{}, Int<64>{});
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         in = out;

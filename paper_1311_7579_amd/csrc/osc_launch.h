@@ -8,7 +8,8 @@ namespace osc {
 // mode: 0 = probabilities only, 1 = probabilities + histogram partials,
 // 2 = histogram partials of given values, 3 = mode 1 with the events'
 // histogram slots read from `bins` (launch_bin_slots) instead of computed
-// from e_reco.  partial holds ntiles x (nbins + 2) FP64 entries, tile-major.
+// from e_reco.  partial receives the tile results (partial_index), or, when
+// the sample is a single tile, the histogram itself.
 // mixed selects the FP32-mixed tier (FP64 eigenvalues and phases, FP32
 // sine/cosine and amplitude assembly).  ev_begin / ev_end (optional,
 // created by the caller) receive the kernel's own begin and end times.
@@ -35,14 +36,15 @@ hipError_t launch_layered_tiles(int mode, bool write_p, const SetConsts& sc,
 // The levels of the histogram merge for n_samples samples of tiles[s]
 // tiles each (per parameter set), and the scratch strides they need.  A
 // fixed-capacity value: planning a merge allocates nothing.  A sample has
-// at most kMaxEvents / kTileEvents = 2^22 tiles, which two levels of
-// kMergeChunkRows = 2^14 rows reduce to one.
+// at most kMaxEvents / kTileEvents = 2^22 tiles, which two levels of up to
+// kMergeMaxRows = 2^16 rows reduce to one.
 constexpr int kMaxMergeLevels = 3;
 struct MergePlan {
     int nbt = 0;
     int n_samples = 0;
     int n_levels = 0;
     MergeLevel levels[kMaxMergeLevels];
+    int waves[kMaxMergeLevels], thread_rows[kMaxMergeLevels];   // the blocks' shapes
     int64_t tile_set_stride = 0;   // elements of tile results per set
     int64_t level_set_stride = 0;  // elements of each of the two level buffers per set
 };

@@ -90,3 +90,20 @@ def test_layered_splits(osc, n):
         assert_bits_equal(p1.cpu().numpy(), P)
         assert_bits_equal(h1.cpu().numpy(), h0.cpu().numpy())
         hist_of(s, P, h0)
+
+
+@pytest.mark.parametrize("tiles", [2, 1024, 1025, 4096, 4097, 16384, 16385, 32769, 65537])
+def test_merge_shapes(osc, tiles):
+    """Both sides of every merge shape's row count (one launch up to 65536
+    tiles, two above), with a ragged last tile: the contract's bits."""
+    n = tiles * TILE - 700
+    rng = np.random.default_rng(tiles)
+    value = rng.random(n, dtype=np.float32).astype(np.float64)
+    x = rng.integers(0, 5, n).astype(np.float64)
+    with osc.Context(0) as ctx:
+        d = lambda a: torch.from_numpy(a).cuda()
+        h = torch.empty(6, dtype=torch.float64, device="cuda")
+        w = torch.full((n,), 1.0 / 3.0, dtype=torch.float64, device="cuda")
+        ctx.osc_fill_hist(d(value), w, d(x), 4, 0.0, 4.0, h)
+        want = oracle.hist_contract((1.0 / 3.0) * value, np.where(x < 4, x, 5).astype(np.int32), 6)
+        assert_bits_equal(h.cpu().numpy(), want)
