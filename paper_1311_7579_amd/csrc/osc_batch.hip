@@ -93,17 +93,54 @@ __global__ void reset_queue(unsigned* queue)
     if (threadIdx.x < kQueueParts) queue[threadIdx.x * kQueueStride] = 0u;
 }
 
-template <bool MIXED>
+// The parameter sets first .. first + NS - 1 on one tile: tables and
+// histograms in LDS, the tile's events, the tile rows.
+template <bool MIXED, int NS, class Tab>
+__device__ __forceinline__ void tile_sets(const BatchArgs& a, const BatchSampleDev& S,
+                                          const TileArrays& t, const SetConsts* sets, int first,
+                                          int64_t tile, Tab* tabs, double* hist, int lane,
+                                          double* partial)
+{
+    const int stride = a.nbt * kHistLanes;
+    const SetConsts* sc[NS];
+    const Tab* T[NS];
+    __syncthreads();   // the previous sets' tables and histograms are read
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+        sc[k] = &sets[first + k];
+        T[k] = &tabs[k];
+        load_tab(*sc[k], tabs[k], lane);
+        hist_zero(hist + k * stride, lane, a.nbt);
+    }
+    __syncthreads();
+    const TilePtrs arr{t.e_true, t.flags, t.weight, nullptr, t.bins};
+    if (t.n == kTileEvents)
+        tile_events_sets<MIXED, true, NS>(sc, T, S.pc.kA, S.pc.kL, hist, stride, lane, t.n, arr);
+    else
+        tile_events_sets<MIXED, false, NS>(sc, T, S.pc.kA, S.pc.kL, hist, stride, lane, t.n, arr);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NS; ++k)
+        tile_write(hist + k * stride, lane, a.nbt, S.row0 + tile,
+                   partial + int64_t(first + k) * a.set_stride);
+}
+
+// SETS: parameter sets run side by side on a tile (a group's last odd set
+// runs alone): each event is loaded and decoded once for them, and the
+// arithmetic of the two interleaves.  Bound by VALU issue.
+template <bool MIXED, int SETS>
 __global__ __launch_bounds__(kTileLanes) __attribute__((amdgpu_waves_per_eu(kBatchWavesPerSimd)))
 void batch_kernel(BatchArgs a, const BatchSampleDev* __restrict__ samples,
                   const SetConsts* __restrict__ sets, double* __restrict__ partial,
                   unsigned* __restrict__ queue)
 {
     extern __shared__ double hist[];
-    __shared__ Tables<MIXED> tabs;
+    __shared__ Tables<MIXED> tabs[SETS];
     const int lane = threadIdx.x;
-    const int nbt = a.nbt;
-    if constexpr (!MIXED) load_sincos(tabs, lane);   // read after the first barrier below
+    if constexpr (!MIXED) {   // read after the first barrier below
+#pragma unroll
+        for (int k = 0; k < SETS; ++k) load_sincos(tabs[k], lane);
+    }
 
     const int64_t G = gridDim.x, b = blockIdx.x;
     int64_t item, end, stride = 0, base = 0;
@@ -139,24 +176,13 @@ void batch_kernel(BatchArgs a, const BatchSampleDev* __restrict__ samples,
         const TileArrays t = tile_arrays(tile, S.n, S.e_true, S.flags, S.weight, nullptr, S.bins,
                                          nullptr, nullptr);
         const int set_end = int(min(int64_t(a.n_sets), (g + 1) * a.sets_per_item));
-        for (int set = int(g) * a.sets_per_item; set < set_end; ++set) {
-            const SetConsts& sc = sets[set];
-            __syncthreads();   // the previous set's table and histogram are read
-            load_tab(sc, tabs, lane);
-            hist_zero(hist, lane, nbt);
-            __syncthreads();
-            const ConstDensityProb<MIXED> prob{&sc, &tabs, S.pc.kA, S.pc.kL};
-            if (t.n == kTileEvents)
-                tile_events<kPdfBinned, false, true, true, false>(
-                    prob, a.bc, hist, lane, t.n, t.e_true, t.flags, t.weight, nullptr, t.bins,
-                    nullptr, nullptr);
-            else
-                tile_events<kPdfBinned, false, false, true, false>(
-                    prob, a.bc, hist, lane, t.n, t.e_true, t.flags, t.weight, nullptr, t.bins,
-                    nullptr, nullptr);
-            __syncthreads();
-            tile_write(hist, lane, nbt, S.row0 + tile, partial + int64_t(set) * a.set_stride);
+        int set = int(g) * a.sets_per_item;
+        if constexpr (SETS > 1) {
+            for (; set + SETS <= set_end; set += SETS)
+                tile_sets<MIXED, SETS>(a, S, t, sets, set, tile, tabs, hist, lane, partial);
         }
+        for (; set < set_end; ++set)
+            tile_sets<MIXED, 1>(a, S, t, sets, set, tile, tabs, hist, lane, partial);
         item = next;
     }
 }
@@ -237,12 +263,40 @@ bool launchable(const osc_batch* b, int n_sets, const osc_batch_config& c)
     return a.n_items + int64_t(b->num_cus) * kMaxWavesPerCu <= kMaxTickets;
 }
 
+using BatchKernel = void (*)(osc::BatchArgs, const osc::BatchSampleDev*, const osc::SetConsts*,
+                             double*, unsigned*);
+
+// Parameter sets that a wave runs side by side.  Two in the FP32-mixed tier
+// while their histograms and tables leave room for 16 waves per CU (256 sets x
+// 4 samples of 50 bins: 9.06 -> 8.75 ms); above that the waves they cost weigh
+// more (100 bins: 535 -> 617 us for 64 sets x 1.6e6 events, 200 bins 651 ->
+// 974).  One in the FP64 tier, which two do not speed up (524 against 535 us).
+int side_by_side(osc_precision precision, int nbt)
+{
+    return precision == OSC_FP32_MIXED && nbt <= 64 ? 2 : 1;
+}
+
+struct BatchLaunch {
+    BatchKernel kernel;
+    size_t lds;
+};
+
+BatchLaunch batch_launch(osc_precision precision, int nbt)
+{
+    const bool mixed = precision == OSC_FP32_MIXED;
+    const int sets = side_by_side(precision, nbt);
+    return {!mixed       ? &osc::batch_kernel<false, 1>
+            : sets == 2  ? &osc::batch_kernel<true, 2>
+                         : &osc::batch_kernel<true, 1>,
+            size_t(sets) * size_t(nbt) * osc::kHistLanes * sizeof(double)};
+}
+
 // Enqueues one batched evaluation of n_sets sets (parameters already in
 // d_sets) on `stream`: queue reset, persistent kernel, merge levels.
 hipError_t enqueue(osc_batch* b, int n_sets, const osc_batch_config& c, hipStream_t stream)
 {
     const osc::BatchArgs a = batch_args(b, n_sets, c);
-    const size_t lds = size_t(a.nbt) * osc::kHistLanes * sizeof(double);
+    const BatchLaunch k = batch_launch(b->precision, a.nbt);
     int64_t grid = a.n_items;
     if (c.schedule != osc::kOnePerBlock) {
         const int wpc = c.waves_per_cu > 0 ? c.waves_per_cu : b->occupancy;
@@ -254,14 +308,8 @@ hipError_t enqueue(osc_batch* b, int n_sets, const osc_batch_config& c, hipStrea
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
-        if (b->precision == OSC_FP32_MIXED)
-            hipLaunchKernelGGL(osc::batch_kernel<true>, dim3(unsigned(grid)), dim3(osc::kTileLanes),
-                               lds, stream, a, b->d_samples, b->d_sets, b->d_scratch,
-                               b->d_queue);
-        else
-            hipLaunchKernelGGL(osc::batch_kernel<false>, dim3(unsigned(grid)), dim3(osc::kTileLanes),
-                               lds, stream, a, b->d_samples, b->d_sets, b->d_scratch,
-                               b->d_queue);
+        hipLaunchKernelGGL(k.kernel, dim3(unsigned(grid)), dim3(osc::kTileLanes), k.lds, stream, a,
+                           b->d_samples, b->d_sets, b->d_scratch, b->d_queue);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -406,21 +454,19 @@ osc_status osc_batch_create(osc_ctx* ctx, const osc_sample* samples, int32_t n_s
                                             osc::host::path_consts(&samples[s])};
         tile0 += t;
     }
-    b->plan = osc::plan_merge(b->tiles.data(), n_samples, nbt);
+    b->plan = osc::plan_merge(b->tiles.data(), n_samples, nbt, max_sets);
     for (int s = 0; s < n_samples; ++s)
         hs[size_t(s)].row0 = b->plan.levels[0].in_row0[s];
 
     hipDeviceProp_t prop;
     int occ = 0;
-    const size_t lds = size_t(nbt) * osc::kHistLanes * sizeof(double);
+    const BatchLaunch k = batch_launch(precision, nbt);
+    const void* kernel = reinterpret_cast<const void*>(k.kernel);
     const bool ok =
         hipGetDeviceProperties(&prop, device) == hipSuccess &&
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&osc::batch_kernel<true>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) == hipSuccess &&
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&osc::batch_kernel<false>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) == hipSuccess &&
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &occ, reinterpret_cast<const void*>(&osc::batch_kernel<false>), osc::kTileLanes, lds) ==
+        hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, int(k.lds)) ==
+            hipSuccess &&
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, osc::kTileLanes, k.lds) ==
             hipSuccess;
     if (!ok) {
         free_batch(b);

@@ -335,9 +335,14 @@ constexpr double kHalleyOnly = 0x1p-12;
 // vacuum splitting) assemble the amplitude in FP64.
 constexpr double kMixedWideA = 0.01;
 
-__device__ __forceinline__ void cubic_roots_mixed(const SetConsts& sc, double A, double& l0,
-                                                  double& l1, double& l2)
+struct MixedRoots {
+    double tr, c1, det, x0, x1;
+    bool done;   // this lane needs no Newton step
+};
+
+__device__ __forceinline__ MixedRoots halley_roots(const SetConsts& sc, double A)
 {
+    MixedRoots v;
     const double tr = sc.T0 + A, c1 = fma(A, sc.CA, sc.C0), det = A * sc.DA;
     const double qh = fma(fma(A + sc.QH2, A, sc.QH1), A, sc.QH0);
     const double p = fma(tr, tr, -3.0 * c1);
@@ -355,49 +360,46 @@ __device__ __forceinline__ void cubic_roots_mixed(const SetConsts& sc, double A,
     double x1 = double(__builtin_fmaf(kf, __builtin_amdgcn_cosf(th - 0.33333333f), t3f));
     const double three = sgpr_value(3.0);
     // Halley: x -= 2 f f' / (2 f'^2 - f f'')
-    {
-        const double f0 = fma(fma(x0 - tr, x0, c1), x0, -det);
-        const double f1 = fma(fma(x1 - tr, x1, c1), x1, -det);
-        // m = tr - 3x = -f''/2, and f' = x (3x - 2 tr) + c1 = c1 - x (m + tr)
-        const double m0 = fma(-three, x0, tr), m1 = fma(-three, x1, tr);
-        const double g0 = fma(-x0, m0 + tr, c1);
-        const double g1 = fma(-x1, m1 + tr, c1);
-        const double d0 = fma(g0, g0, f0 * m0);
-        const double d1 = fma(g1, g1, f1 * m1);
-        const double r = recip_coarse(d0 * d1);
-        const double h0 = (f0 * g0) * (d1 * r), h1 = (f1 * g1) * (d0 * r);
-        x0 -= h0;
-        x1 -= h1;
-        // x0 > x1 > x2 = tr - x0 - x1: the smallest root distance is
-        // x0 - x1 or x1 - x2 = 2 x1 + x0 - tr
-        const double dmin = __builtin_fmin(__builtin_fabs(x0 - x1),
-                                           __builtin_fabs(fma(2.0, x1, x0) - tr));
-        const bool done = __builtin_fmax(__builtin_fabs(h0), __builtin_fabs(h1)) <=
-                          kHalleyOnly * dmin;
-        if (__builtin_expect(__all(done), 1)) {
-            l0 = x0;
-            l1 = x1;
-            l2 = (tr - l0) - l1;
-            return;
-        }
-    }
-    // Newton: x -= f / f'
-    {
-        const double tr2 = 2.0 * tr;
-        const double f0 = fma(fma(x0 - tr, x0, c1), x0, -det);
-        const double f1 = fma(fma(x1 - tr, x1, c1), x1, -det);
-        const double g0 = fma(x0, fma(three, x0, -tr2), c1);
-        const double g1 = fma(x1, fma(three, x1, -tr2), c1);
-        const double r = recip_coarse(g0 * g1);
-        x0 -= f0 * (g1 * r);
-        x1 -= f1 * (g0 * r);
-        // the FP64 tier's rule, so that both give NaN on the same events
-        // (every such lane's Halley step is large, so its wave comes here)
-        if (__builtin_fabsf(seed_angle(sc, A).r) > 1.0f - kUnresolved) x0 = __builtin_nan("");
-    }
-    l0 = x0;
-    l1 = x1;
-    l2 = (tr - l0) - l1;
+    const double f0 = fma(fma(x0 - tr, x0, c1), x0, -det);
+    const double f1 = fma(fma(x1 - tr, x1, c1), x1, -det);
+    // m = tr - 3x = -f''/2, and f' = x (3x - 2 tr) + c1 = c1 - x (m + tr)
+    const double m0 = fma(-three, x0, tr), m1 = fma(-three, x1, tr);
+    const double g0 = fma(-x0, m0 + tr, c1);
+    const double g1 = fma(-x1, m1 + tr, c1);
+    const double d0 = fma(g0, g0, f0 * m0);
+    const double d1 = fma(g1, g1, f1 * m1);
+    const double r = recip_coarse(d0 * d1);
+    const double h0 = (f0 * g0) * (d1 * r), h1 = (f1 * g1) * (d0 * r);
+    x0 -= h0;
+    x1 -= h1;
+    // x0 > x1 > x2 = tr - x0 - x1: the smallest root distance is
+    // x0 - x1 or x1 - x2 = 2 x1 + x0 - tr
+    const double dmin = __builtin_fmin(__builtin_fabs(x0 - x1),
+                                       __builtin_fabs(fma(2.0, x1, x0) - tr));
+    v.done = __builtin_fmax(__builtin_fabs(h0), __builtin_fabs(h1)) <= kHalleyOnly * dmin;
+    v.tr = tr;
+    v.c1 = c1;
+    v.det = det;
+    v.x0 = x0;
+    v.x1 = x1;
+    return v;
+}
+
+// One Newton step x -= f / f' on both roots.
+__device__ __forceinline__ void newton_roots(const SetConsts& sc, double A, MixedRoots& v)
+{
+    const double three = sgpr_value(3.0);
+    const double tr2 = 2.0 * v.tr;
+    const double f0 = fma(fma(v.x0 - v.tr, v.x0, v.c1), v.x0, -v.det);
+    const double f1 = fma(fma(v.x1 - v.tr, v.x1, v.c1), v.x1, -v.det);
+    const double g0 = fma(v.x0, fma(three, v.x0, -tr2), v.c1);
+    const double g1 = fma(v.x1, fma(three, v.x1, -tr2), v.c1);
+    const double r = recip_coarse(g0 * g1);
+    v.x0 -= f0 * (g1 * r);
+    v.x1 -= f1 * (g0 * r);
+    // the FP64 tier's rule, so that both give NaN on the same events
+    // (every such lane's Halley step is large, so its wave comes here)
+    if (__builtin_fabsf(seed_angle(sc, A).r) > 1.0f - kUnresolved) v.x0 = __builtin_nan("");
 }
 
 // P of one event in the FP32-mixed tier.  The evolution operator is sum_k
@@ -405,24 +407,12 @@ __device__ __forceinline__ void cubic_roots_mixed(const SetConsts& sc, double A,
 // ((l_k - l_j)(l_k - l_l)); the common phase exp(-i phi_0) drops out, and
 // the projectors sum to the identity, so S' = [a = b] + (exp(-i dphi1) - 1)
 // X1 + (exp(-i dphi2) - 1) X2.  Eigenvalues and phase differences are FP64,
-// the rest FP32.
-__device__ __forceinline__ double event_prob_mixed(const SetConsts& sc, const TileTablesMixed& T,
-                                                   double kA, double kL, double E, uint32_t f)
+// the rest FP32.  `wide` (the same for the whole wave): the amplitude in FP64.
+template <bool WIDE>
+__device__ __forceinline__ double mixed_amplitude(const MixedRoots& v, const ChanF& c, double A,
+                                                  double kL, double E)
 {
-    const FlagInfo fl = T.flag[min(f, uint32_t(kMixedFlags - 1))];
-    const ChanF c = *reinterpret_cast<const ChanF*>(
-        reinterpret_cast<const unsigned char*>(T.ch) + fl.ch_off);
-    const double A = flip_sign(kA * E, fl.sign);
-
-    // amplitude inputs: M_ba and (M^2)_ba
-    const float Ar = float(A);
-    const float mre = __builtin_fmaf(Ar, c.dee, c.m_re), mim = c.m_im;
-    const float m2re = __builtin_fmaf(Ar, __builtin_fmaf(Ar, c.dee, c.g_re), c.m2_re);
-    const float m2im = __builtin_fmaf(Ar, c.g_im, c.m2_im);
-
-    double l0, l1, l2;
-    cubic_roots_mixed(sc, A, l0, l1, l2);
-
+    const double l0 = v.x0, l1 = v.x1, l2 = (v.tr - l0) - l1;
     const double d01 = l0 - l1, d02 = l0 - l2, d12 = l1 - l2;
     const double Q = d01 * d02 * d12;
     const double R = recip(E * Q);
@@ -436,7 +426,7 @@ __device__ __forceinline__ double event_prob_mixed(const SetConsts& sc, const Ti
     float s1, c1, s2, c2;
     phase_sincos_mixed(-d01, ph, s1, c1);
     phase_sincos_mixed(-d02, ph, s2, c2);
-    if (__any(__builtin_fabs(A) > kMixedWideA)) {
+    if constexpr (WIDE) {
         // Matter terms well above the vacuum splittings: the projector
         // numerators cancel over about |A| / dm^2_31, beyond what FP32
         // resolves, so such waves form them and the sum in FP64 (from
@@ -455,20 +445,71 @@ __device__ __forceinline__ double event_prob_mixed(const SetConsts& sc, const Ti
         const double sr = d_dba + e1 * x1r + ds1 * x1i + e2 * x2r + ds2 * x2i;
         const double si = e1 * x1i - ds1 * x1r + e2 * x2i - ds2 * x2r;
         return sr * sr + si * si;
+    } else {
+        // amplitude inputs M_ba and (M^2)_ba and the assembly in FP32 from
+        // FP32-rounded inputs
+        const float Ar = float(A);
+        const float mre = __builtin_fmaf(Ar, c.dee, c.m_re), mim = c.m_im;
+        const float m2re = __builtin_fmaf(Ar, __builtin_fmaf(Ar, c.dee, c.g_re), c.m2_re);
+        const float m2im = __builtin_fmaf(Ar, c.g_im, c.m2_im);
+        const float fdba = c.dba;
+        const float fu1 = float(u1), fu2 = float(u2);
+        const float fv1 = float(v1), fv2 = float(v2);
+        const float fi1 = float(iD1), fi2 = float(iD2);
+        const float x1r = __builtin_fmaf(fv1, fdba, __builtin_fmaf(-fu1, mre, m2re)) * fi1;
+        const float x1i = __builtin_fmaf(-fu1, mim, m2im) * fi1;
+        const float x2r = __builtin_fmaf(fv2, fdba, __builtin_fmaf(-fu2, mre, m2re)) * fi2;
+        const float x2i = __builtin_fmaf(-fu2, mim, m2im) * fi2;
+        const float e1 = c1 - 1.0f, e2 = c2 - 1.0f;
+        const float sr = fdba + e1 * x1r + s1 * x1i + e2 * x2r + s2 * x2i;
+        const float si = e1 * x1i - s1 * x1r + e2 * x2i - s2 * x2r;
+        return double(sr * sr + si * si);
     }
-    // amplitude assembly in FP32 from FP32-rounded inputs
-    const float fdba = c.dba;
-    const float fu1 = float(u1), fu2 = float(u2);
-    const float fv1 = float(v1), fv2 = float(v2);
-    const float fi1 = float(iD1), fi2 = float(iD2);
-    const float x1r = __builtin_fmaf(fv1, fdba, __builtin_fmaf(-fu1, mre, m2re)) * fi1;
-    const float x1i = __builtin_fmaf(-fu1, mim, m2im) * fi1;
-    const float x2r = __builtin_fmaf(fv2, fdba, __builtin_fmaf(-fu2, mre, m2re)) * fi2;
-    const float x2i = __builtin_fmaf(-fu2, mim, m2im) * fi2;
-    const float e1 = c1 - 1.0f, e2 = c2 - 1.0f;
-    const float sr = fdba + e1 * x1r + s1 * x1i + e2 * x2r + s2 * x2i;
-    const float si = e1 * x1i - s1 * x1r + e2 * x2i - s2 * x2r;
-    return double(sr * sr + si * si);
+}
+
+// P of one event under NS parameter sets.  The sets share the event's flag
+// decode and matter term, and the arithmetic of two sets runs side by side:
+// only the rare steps (Newton, wide matter terms) are branches, taken by the
+// wave for each set as it would alone.
+template <int NS>
+__device__ __forceinline__ void event_probs_mixed(const SetConsts* const (&sc)[NS],
+                                                  const TileTablesMixed* const (&T)[NS], double kA,
+                                                  double kL, double E, uint32_t f, double (&P)[NS])
+{
+    const FlagInfo fl = T[0]->flag[min(f, uint32_t(kMixedFlags - 1))];
+    const double A = flip_sign(kA * E, fl.sign);
+    ChanF c[NS];
+    MixedRoots v[NS];
+    bool newton = false;
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+        c[k] = *reinterpret_cast<const ChanF*>(
+            reinterpret_cast<const unsigned char*>(T[k]->ch) + fl.ch_off);
+        v[k] = halley_roots(*sc[k], A);
+        newton |= !v[k].done;
+    }
+    if (__builtin_expect(__any(newton), 0)) {
+#pragma unroll
+        for (int k = 0; k < NS; ++k)
+            if (!__all(v[k].done)) newton_roots(*sc[k], A, v[k]);
+    }
+    if (__builtin_expect(__any(__builtin_fabs(A) > kMixedWideA), 0)) {
+#pragma unroll
+        for (int k = 0; k < NS; ++k) P[k] = mixed_amplitude<true>(v[k], c[k], A, kL, E);
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < NS; ++k) P[k] = mixed_amplitude<false>(v[k], c[k], A, kL, E);
+}
+
+__device__ __forceinline__ double event_prob_mixed(const SetConsts& sc, const TileTablesMixed& T,
+                                                   double kA, double kL, double E, uint32_t f)
+{
+    const SetConsts* const s[1] = {&sc};
+    const TileTablesMixed* const t[1] = {&T};
+    double P[1];
+    event_probs_mixed<1>(s, t, kA, kL, E, f, P);
+    return P[0];
 }
 
 // P of one event through one constant-density layer: the policy the tile
@@ -733,17 +774,7 @@ struct TilePtrs {
     const double* w;
     const double* x;
     const uint16_t* s;
-    double* p;
 };
-
-template <int MODE>
-__device__ __forceinline__ TilePtrs tile_ptrs(const double* e_true, const uint8_t* flags,
-                                              const double* weight, const double* e_reco,
-                                              const uint16_t* bins, const double* value,
-                                              double* p_out)
-{
-    return TilePtrs{MODE == kHist ? value : e_true, flags, weight, e_reco, bins, p_out};
-}
 
 template <int MODE, bool FULL>
 __device__ __forceinline__ EventIn load_event(const TilePtrs& b, uint32_t l, uint32_t g0,
@@ -758,11 +789,6 @@ __device__ __forceinline__ EventIn load_event(const TilePtrs& b, uint32_t l, uin
     v.x = (has_hist(MODE) && !reads_bins(MODE) && in) ? b.x[i] : 0.0;
     v.slot = (reads_bins(MODE) && in) ? uint32_t(b.s[i]) : 0u;
     return v;
-}
-
-__device__ __forceinline__ void store_p(const TilePtrs& b, uint32_t l, uint32_t g0, double P)
-{
-    __builtin_nontemporal_store(P, &b.p[l + g0]);
 }
 
 // Event g0 + l of a tile (0 <= g0 + l < kTileEvents); n = the tile's events
@@ -864,7 +890,7 @@ __device__ __forceinline__ void tile_group(const PROB& prob, const BinConsts& bc
 // kernel from measurements: rolled for the kernels that write P (both
 // tiers) and for the batched kernel, fully unrolled for the kernels that
 // write no P.
-template <int MODE, bool WRITE_P, bool FULL, bool ROLL, bool BUF = true, class PROB>
+template <int MODE, bool WRITE_P, bool FULL, bool ROLL, class PROB>
 __device__ __forceinline__ void tile_events(const PROB& prob, const BinConsts& bc, double* hist,
                                             int lane, uint32_t n, const double* e_true,
                                             const uint8_t* flags, const double* weight,
@@ -873,12 +899,7 @@ __device__ __forceinline__ void tile_events(const PROB& prob, const BinConsts& b
 {
     constexpr int kGroups = kLaneEvents / kGroup;
     const uint32_t l = uint32_t(lane);
-    const auto bufs = [&] {
-        if constexpr (BUF)
-            return tile_bufs<MODE>(n, e_true, flags, weight, e_reco, bins, value, p_out);
-        else
-            return tile_ptrs<MODE>(e_true, flags, weight, e_reco, bins, value, p_out);
-    }();
+    const TileBufs bufs = tile_bufs<MODE>(n, e_true, flags, weight, e_reco, bins, value, p_out);
     if constexpr (ROLL) {
         EventIn cur[kGroup], nxt[kGroup];
 #pragma unroll
@@ -911,6 +932,39 @@ __device__ __forceinline__ void tile_events(const PROB& prob, const BinConsts& b
             tile_group<MODE, WRITE_P, FULL>(prob, bc, hist, lane, l, g * kGroup * kTileLanes,
                                             n, ev[g], bufs);
         }
+    }
+}
+
+// The events of one tile of a binned sample under NS parameter sets, each with
+// its own histogram (hist + k * stride): every event is loaded once for all of
+// them (plain pointers, the next event's loads ahead).
+template <bool MIXED, bool FULL, int NS>
+__device__ __forceinline__ void tile_events_sets(const SetConsts* const (&sc)[NS],
+                                                 const Tables<MIXED>* const (&T)[NS], double kA,
+                                                 double kL, double* hist, int stride, int lane,
+                                                 uint32_t n, const TilePtrs& arr)
+{
+    const uint32_t l = uint32_t(lane);
+    EventIn cur = load_event<kPdfBinned, FULL>(arr, l, 0, n);
+#pragma unroll 1
+    for (int m = 0; m < kLaneEvents; ++m) {
+        const uint32_t next = uint32_t(m + 1 < kLaneEvents ? m + 1 : m) * kTileLanes;
+        const EventIn nxt = load_event<kPdfBinned, FULL>(arr, l, next, n);
+        double P[NS];
+        if constexpr (MIXED) {
+            event_probs_mixed<NS>(sc, T, kA, kL, cur.e, cur.f, P);
+        } else {
+#pragma unroll
+            for (int k = 0; k < NS; ++k) P[k] = event_prob(*sc[k], *T[k], kA, kL, cur.e, cur.f);
+        }
+        if (FULL || l + uint32_t(m) * kTileLanes < n) {
+#pragma unroll
+            for (int k = 0; k < NS; ++k) {
+                const double c = cur.w * P[k];   // an operand of an LDS addition: never fused
+                add_in_lane_order(hist + k * stride + int(cur.slot), c, lane);
+            }
+        }
+        cur = nxt;
     }
 }
 

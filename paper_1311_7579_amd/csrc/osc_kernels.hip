@@ -330,15 +330,19 @@ namespace {
 // rows: few waves for few rows (most of a large block's threads would only
 // wait for the others), and one launch instead of two up to 65536 rows: at
 // 19532 rows x 52 bins 10.2 us from the per-event kernel's end against 12.9
-// with two levels.
+// with two levels.  With blocks enough to fill the chip several times
+// (`many`) 4097 to 8192 rows take 256 threads of 32 rows too: the 256-set x
+// 4-sample batch (rows 98 to 4883) merges in 297 instead of 388 us with 1024
+// threads of 16.
 constexpr int64_t kScratchChunk = 16384;
 struct MergeShape {
     int waves, rows;
 };
-MergeShape merge_shape(int64_t rows)
+MergeShape merge_shape(int64_t rows, bool many)
 {
     if (rows <= 1024) return {1, 16};
     if (rows <= 4096) return {4, 16};
+    if (many && rows <= 8192) return {4, 32};
     if (rows <= 16384) return {16, 16};
     if (rows <= 32768) return {16, 32};
     return {16, 64};
@@ -346,8 +350,9 @@ MergeShape merge_shape(int64_t rows)
 
 }  // namespace
 
-MergePlan plan_merge(const int64_t* tiles, int n_samples, int nbt)
+MergePlan plan_merge(const int64_t* tiles, int n_samples, int nbt, int64_t n_sets)
 {
+    const bool many = n_sets * n_samples * nbt >= 4096;
     auto align = [](int64_t r) { return (r + kLayoutChunk - 1) / kLayoutChunk * kLayoutChunk; };
     MergePlan p;
     p.nbt = nbt;
@@ -376,7 +381,7 @@ MergePlan plan_merge(const int64_t* tiles, int n_samples, int nbt)
         L.nbt = nbt;
         int64_t most = 0;
         for (int s = 0; s < n_samples; ++s) most = std::max(most, rows[s]);
-        const MergeShape shape = merge_shape(most);
+        const MergeShape shape = merge_shape(most, many);
         const int64_t chunk = int64_t(shape.waves) * 64 * shape.rows;
         p.waves[p.n_levels] = shape.waves;
         p.thread_rows[p.n_levels] = shape.rows;
@@ -432,7 +437,8 @@ hipError_t launch_merge(const MergePlan& p, int64_t n_sets, double* scratch, dou
                                    L, in, out);
         };
         if (p.waves[l] == 1) launch(Int<1>{}, Int<16>{});
-        else if (p.waves[l] == 4) launch(Int<4>{}, Int<16>{});
+        else if (p.waves[l] == 4 && p.thread_rows[l] == 16) launch(Int<4>{}, Int<16>{});
+        else if (p.waves[l] == 4) launch(Int<4>{}, Int<32>{});
         else if (p.thread_rows[l] == 16) launch(Int<16>{}, Int<16>{});
         else if (p.thread_rows[l] == 32) launch(Int<16>{}, Int<32>{});
         else launch(Int<16>{}, Int<64>{});

@@ -34,7 +34,8 @@ hipError_t launch_layered_tiles(int mode, bool write_p, const SetConsts& sc,
                                 hipEvent_t ev_end = nullptr);
 
 // The levels of the histogram merge for n_samples samples of tiles[s]
-// tiles each (per parameter set), and the scratch strides they need.  A
+// tiles each (per parameter set, for up to n_sets of them at once), and the
+// scratch strides they need.  A
 // fixed-capacity value: planning a merge allocates nothing.  A sample has
 // at most kMaxEvents / kTileEvents = 2^22 tiles, which two levels of up to
 // kMergeMaxRows = 2^16 rows reduce to one.
@@ -49,7 +50,7 @@ struct MergePlan {
     int64_t level_set_stride = 0;  // elements of each of the two level buffers per set
 };
 
-MergePlan plan_merge(const int64_t* tiles, int n_samples, int nbt);
+MergePlan plan_merge(const int64_t* tiles, int n_samples, int nbt, int64_t n_sets = 1);
 
 // Scratch (bytes) for the tile results and the level buffers of n_sets sets.
 size_t merge_scratch_bytes(const MergePlan& p, int64_t n_sets);

@@ -107,3 +107,34 @@ def test_merge_shapes(osc, tiles):
         ctx.osc_fill_hist(d(value), w, d(x), 4, 0.0, 4.0, h)
         want = oracle.hist_contract((1.0 / 3.0) * value, np.where(x < 4, x, 5).astype(np.int32), 6)
         assert_bits_equal(h.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("nbins", [62, 63])          # two sets side by side, or one
+@pytest.mark.parametrize("n_sets,spi", [(1, 1), (2, 2), (3, 2), (5, 4), (5, 8)])
+def test_sets_side_by_side(osc, nbins, n_sets, spi):
+    """Batched FP32-mixed histograms with whole and odd groups of sets equal
+    the plain call's bits, also where only some waves, and only one of two
+    sets, take the eigenvalues' Newton step (a set with a level crossing) or
+    the FP64 assembly (matter terms above 0.01 eV^2)."""
+    n = 30_001
+    s = workload.make_sample(n, 8, L_km=2500.0, rho_gcc=11.0, e_range=(0.1, 60.0))
+    order = np.argsort(s.e_true)
+    for a in ("e_true", "flags", "weight", "e_reco"):
+        setattr(s, a, np.ascontiguousarray(getattr(s, a)[order]))
+    sets = workload.make_param_sets(n_sets, 9)
+    for k in range(1, n_sets, 2):
+        sets[k]["sin2_th13"] = 0.0
+    with osc.Context(0) as ctx:
+        ds = osc.DeviceSample.from_host(s)
+        batch = osc.Batch(ctx, [ds], nbins, 0.0, 20.0, osc.OSC_FP32_MIXED, max_sets=n_sets)
+        ctx.osc_set_params(sets)
+        try:
+            for schedule in (0, 2):
+                batch.config = dict(sets_per_item=spi, schedule=schedule)
+                got = batch.run(sets).cpu().numpy()
+                for k in range(n_sets):
+                    h = torch.empty(nbins + 2, dtype=torch.float64, device="cuda")
+                    ctx.osc_fill_pdf(ds, k, nbins, 0.0, 20.0, h, precision=osc.OSC_FP32_MIXED)
+                    assert_bits_equal(got[k, 0], h.cpu().numpy(), (k, schedule))
+        finally:
+            batch.close()
