@@ -79,12 +79,12 @@ KERNEL_SOURCES = ("paper_1311_7579_amd/csrc/osc_device.h",
                   "paper_1311_7579_amd/csrc/osc_kernels.hip",
                   "paper_1311_7579_amd/build.py")
 COUNTER_TRAFFIC = {
-    "fetch_kib": 92823.4, "fetch_scale": 2.0,     # copy of 512 MiB: FETCH_SIZE 262157 KiB
-    "write_kib": 82430.4, "write_scale": 1.0,     # copy of 512 MiB: WRITE_SIZE 524288 KiB
+    "fetch_kib": 92833.2, "fetch_scale": 2.0,     # copy of 512 MiB: FETCH_SIZE 262157 KiB
+    "write_kib": 82429.8, "write_scale": 1.0,     # copy of 512 MiB: WRITE_SIZE 524288 KiB
     "valu_per_event": 145.2,
     "classes_per_event": {"fp64": 95.9, "fp64_trans": 1.0, "fp32": 19.0, "fp32_trans": 2.0,
                           "cvt": 3.0, "int32": 6.81, "int64": 0.438, "other": 17.05},
-    "source_sha256": "3943e64a0d3eac2ecd43ebd3ff11f62adfb72af21b6a06f878d627316b0b8748",
+    "source_sha256": "c7587d2fa31a7543de12d7a31907e47990c77a5811eee2739f93ab02aed1268e",
 }
 # Issue time of one wave instruction on one SIMD, measured on the box with
 # probe kernels of independent chains (ns): FP64 FMA/MUL/ADD 2.08, FP32

@@ -1147,9 +1147,11 @@ __device__ __forceinline__ double wave_tree(double v)
 // rows (+0.0 beyond the sample's rows) as a binary tree in registers; the 64
 // lanes of a wave meet in the butterfly tree and the block's waves in a last
 // binary tree.
-template <bool FINAL, int WAVES, int ROWS>
+// The block's total is handed to emit(set, sample, chunk, bin, total) by
+// thread 0.
+template <int WAVES, int ROWS, class EMIT>
 __device__ __forceinline__ void merge_level_block(const MergeLevel& L, const double* __restrict__ in,
-                                                  double* __restrict__ out)
+                                                  EMIT&& emit)
 {
     __shared__ double wave_sum[WAVES];
     const int nbt = L.nbt;
@@ -1178,22 +1180,37 @@ __device__ __forceinline__ void merge_level_block(const MergeLevel& L, const dou
     if constexpr (WAVES > 1) {
         if (lane == 0) wave_sum[wave] = total;
         __syncthreads();
-        if (t != 0) return;
-        // binary tree over the waves' sums, in wave order
-        double w[WAVES];
+        if (t == 0) {
+            // binary tree over the waves' sums, in wave order
+            double w[WAVES];
 #pragma unroll
-        for (int i = 0; i < WAVES; ++i) w[i] = wave_sum[i];
+            for (int i = 0; i < WAVES; ++i) w[i] = wave_sum[i];
 #pragma unroll
-        for (int h = WAVES / 2; h >= 1; h >>= 1)
+            for (int h = WAVES / 2; h >= 1; h >>= 1)
 #pragma unroll
-            for (int i = 0; i < h; ++i) w[i] = w[2 * i] + w[2 * i + 1];
-        total = w[0];
+                for (int i = 0; i < h; ++i) w[i] = w[2 * i] + w[2 * i + 1];
+            total = w[0];
+        }
     }
-    if (t != 0) return;
-    if (FINAL)
-        out[(set * L.n_samples + s) * nbt + bin] = total;
-    else
-        out[set * L.set_stride_out + partial_index(L.out_row0[s] + c, bin, nbt)] = total;
+    if (t == 0) emit(set, s, c, bin, total);
+}
+
+// -2 ln L of one histogram by a whole wave: 2 sum_b (mu_b - d_b ln mu_b +
+// lgamma(d_b + 1)), mu_b = scale hist_b.  Lane l adds bins l, l + 64, ... in
+// ascending order, then the lanes meet in the wave's butterfly tree (a fixed
+// order).  mu(b) gives hist_b.
+template <class MU>
+__device__ __forceinline__ double poisson_nll(MU&& mu, const double* __restrict__ d, double scale,
+                                              int nbins, int lane)
+{
+    double acc = 0.0;
+    for (int b = lane; b < nbins; b += 64) {
+        const double m = scale * mu(b), x = d[b];
+        const double term = m == 0.0 ? (x == 0.0 ? 0.0 : __builtin_inf())
+                                     : m - x * log(m) + lgamma(x + 1.0);
+        acc = acc + term;
+    }
+    return 2.0 * wave_tree(acc);
 }
 
 }  // namespace dev

@@ -418,21 +418,19 @@ size_t osc::host::fill_scratch_bytes(int64_t n, int nbins)
     return osc::merge_scratch_bytes(osc::plan_merge(&tiles, 1, nbins + 2), 1);
 }
 
-hipError_t osc::host::enqueue_fill(const osc::SetConsts& sc, const osc_sample* sample,
-                                   const uint16_t* bins, const osc_binning* binning, bool mixed,
-                                   double* partials, double* hist_out, double* p_out,
-                                   hipStream_t stream)
+hipError_t osc::host::enqueue_served(const osc::SetConsts& sc, const osc_sample* sample,
+                                     const uint16_t* bins, const osc_binning* binning, bool mixed,
+                                     double* scratch, const osc::ServeFinish& finish,
+                                     hipStream_t stream)
 {
     const osc::BinConsts bc = bin_consts(binning);
     const int64_t tiles = (sample->n + osc::kTileEvents - 1) / osc::kTileEvents;
-    hipError_t e = osc::launch_tiles(bins ? 3 : 1, p_out != nullptr, mixed, sc,
-                                     path_consts(sample), bc, sample->n, sample->e_true,
-                                     sample->flags, sample->weight, bins ? nullptr : sample->e_reco,
-                                     bins, nullptr, p_out, tiles == 1 ? hist_out : partials,
-                                     stream);
-    if (e == hipSuccess && tiles != 1)
-        e = osc::launch_merge(osc::plan_merge(&tiles, 1, bc.nb + 2), 1, partials, hist_out, stream);
-    return e;
+    hipError_t e = osc::launch_tiles(3, false, mixed, sc, path_consts(sample), bc, sample->n,
+                                     sample->e_true, sample->flags, sample->weight, nullptr, bins,
+                                     nullptr, nullptr, tiles == 1 ? finish.hist : scratch, stream);
+    if (e != hipSuccess) return e;
+    if (tiles == 1) return osc::launch_serve_finish(finish, bc.nb + 2, stream);
+    return osc::launch_merge_serve(osc::plan_merge(&tiles, 1, bc.nb + 2), scratch, finish, stream);
 }
 
 hipError_t osc::host::enqueue_bin_slots(const osc_sample* sample, const osc_binning* binning,

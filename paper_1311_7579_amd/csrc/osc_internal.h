@@ -69,6 +69,19 @@ struct MergeLevel {
     int64_t out_row0[kMaxBatchSamples];
 };
 
+// How a served request ends on the device: its finished histogram and, with a
+// data row, -2 ln L are copied to host memory, and then `seq` is stored to
+// *flag, on which the host waits.
+struct ServeFinish {
+    unsigned* ticket;      // device counter of finished blocks, 0 between requests
+    double* hist;          // device, nbt entries
+    double* host;          // pinned host memory: nbt entries, then -2 ln L
+    unsigned* flag;        // pinned host memory
+    unsigned seq;
+    const double* data;    // nbt - 2 counts, or null
+    double mu_scale;
+};
+
 // Position of the result of (tile, bin) among the tile results.
 __host__ __device__ inline int64_t partial_index(int64_t tile, int bin, int nbt)
 {

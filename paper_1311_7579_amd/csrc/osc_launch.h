@@ -60,6 +60,12 @@ size_t merge_scratch_bytes(const MergePlan& p, int64_t n_sets);
 hipError_t launch_merge(const MergePlan& p, int64_t n_sets, double* scratch, double* hist_out,
                         hipStream_t stream);
 
+// The merge of one histogram whose last block ends a served request, and the
+// end alone, for a histogram that is finished (a single tile's).
+hipError_t launch_merge_serve(const MergePlan& p, double* scratch, const ServeFinish& finish,
+                              hipStream_t stream);
+hipError_t launch_serve_finish(const ServeFinish& finish, int nbt, hipStream_t stream);
+
 // -2 ln L (Eq. 2, Poisson per regular bin, mu = scale * hist) of n_hist
 // histograms (nbins + 2 entries each) against data rows (nbins entries;
 // histogram k uses row k % n_data).

@@ -9,8 +9,9 @@
 // reduces its histogram privately in the fixed order of osc_fill_pdf, so its
 // result is the same alone and in any mix.  When data rows are set, each
 // request also computes -2 ln L (Eq. 2) of its histogram against its
-// sample's row on the device.  Completion is signalled by a host function
-// enqueued after the device-to-host copy of the histogram (and -2 ln L).
+// sample's row on the device.  The last kernel of a request writes the results
+// to the slot's pinned host memory and then a flag, which the dispatcher
+// watches: a request takes two launches, and neither a copy nor a callback.
 #include <atomic>
 #include <chrono>
 #include <condition_variable>
@@ -38,6 +39,11 @@ double now_s()
 }
 
 constexpr size_t kArenaAlign = 256;
+// How long the dispatcher watches the flags before it sleeps between looks (a
+// sleep of 20 us lasts 70 and more; the small requests end within 40), and
+// when a request without its flag is asked after.
+constexpr double kSpinS = 100e-6;
+constexpr double kOverdueS = 0.1;
 
 struct Request {
     osc_params params{};
@@ -53,13 +59,16 @@ struct Request {
 
 struct Slot {
     hipStream_t stream = nullptr;
-    double* d_hist = nullptr;   // nbins + 2 histogram entries, then -2 ln L
-    double* h_hist = nullptr;   // pinned, same layout
+    double* d_hist = nullptr;   // nbins + 2 histogram entries, then the block counter
+    double* h_hist = nullptr;   // pinned: nbins + 2 entries, -2 ln L, then the flag
+    unsigned* flag = nullptr;   // holds `seq` once the slot's request is on the host
+    unsigned seq = 0;
     bool busy = false;
     uint64_t ticket = 0;
     size_t off = 0, bytes = 0;
-    std::atomic<int> finished{0};
-    std::atomic<double> t_done{0.0};
+    double t_query = 0.0;       // when to ask the runtime about an overdue request
+
+    bool arrived() const { return __atomic_load_n(flag, __ATOMIC_ACQUIRE) == seq; }
 };
 
 // First-fit allocator over [0, size) with coalescing frees.
@@ -136,41 +145,45 @@ struct osc_server {
     std::mutex mu;
     std::condition_variable cv_dispatch, cv_done;
     std::thread dispatcher;
+    std::atomic<uint64_t> calls{0};   // submissions and the stop: ends the dispatcher's watch
     bool stop = false;
 };
 
 namespace {
-
-void on_slot_done(void* user)
-{
-    // runs on a HIP runtime thread once the histogram is on the host:
-    // lock-free hand-over to the dispatcher
-    Slot* s = static_cast<Slot*>(user);
-    s->t_done.store(now_s(), std::memory_order_relaxed);
-    s->finished.store(1, std::memory_order_release);
-}
 
 // Launch one admitted request on its slot (lock held).
 osc_status launch(osc_server* sv, Slot& slot, Request& r)
 {
     const osc::SetConsts sc = osc::host::set_consts(r.params);
     double* scratch = reinterpret_cast<double*>(sv->arena_mem + slot.off);
-    if (osc::host::enqueue_fill(sc, &sv->samples[size_t(r.sample)], sv->bins[size_t(r.sample)],
-                                &sv->binning, r.precision == OSC_FP32_MIXED, scratch,
-                                slot.d_hist, nullptr, slot.stream) != hipSuccess)
-        return OSC_ERR_DEVICE;
     r.with_nll = sv->has_data;
-    const int nb = sv->binning.nbins;
-    if (r.with_nll &&
-        osc::launch_poisson_nll(slot.d_hist, 1, sv->mu_scale, sv->d_data + size_t(r.sample) * nb,
-                                1, nb, slot.d_hist + sv->nbt, slot.stream) != hipSuccess)
-        return OSC_ERR_DEVICE;
-    if (hipMemcpyAsync(slot.h_hist, slot.d_hist,
-                       size_t(sv->nbt + (r.with_nll ? 1 : 0)) * sizeof(double),
-                       hipMemcpyDeviceToHost, slot.stream) != hipSuccess)
-        return OSC_ERR_DEVICE;
-    if (hipLaunchHostFunc(slot.stream, on_slot_done, &slot) != hipSuccess) return OSC_ERR_DEVICE;
-    return OSC_OK;
+    osc::ServeFinish finish{};
+    finish.ticket = reinterpret_cast<unsigned*>(slot.d_hist + sv->nbt);
+    finish.hist = slot.d_hist;
+    finish.host = slot.h_hist;
+    finish.flag = slot.flag;
+    finish.seq = ++slot.seq;
+    finish.data =
+        r.with_nll ? sv->d_data + size_t(r.sample) * size_t(sv->binning.nbins) : nullptr;
+    finish.mu_scale = sv->mu_scale;
+    return osc::host::enqueue_served(sc, &sv->samples[size_t(r.sample)],
+                                     sv->bins[size_t(r.sample)], &sv->binning,
+                                     r.precision == OSC_FP32_MIXED, scratch, finish,
+                                     slot.stream) == hipSuccess
+               ? OSC_OK
+               : OSC_ERR_DEVICE;
+}
+
+// Gives a slot's scratch back and marks its request done (lock held).
+void retire(osc_server* sv, Slot& slot, Request& r, osc_status st)
+{
+    r.status = st;
+    r.t_done = now_s();
+    r.done = true;
+    sv->arena.release(slot.off, slot.bytes);
+    slot.busy = false;
+    --sv->stats.in_flight;
+    ++(st == OSC_OK ? sv->stats.completed : sv->stats.failed);
 }
 
 void dispatch_loop(osc_server* sv)
@@ -179,20 +192,27 @@ void dispatch_loop(osc_server* sv)
     std::unique_lock<std::mutex> lock(sv->mu);
     while (!sv->stop) {
         // retire finished slots
+        bool retired = false;
         for (Slot& slot : sv->slots) {
-            if (!slot.busy || !slot.finished.load(std::memory_order_acquire)) continue;
+            if (!slot.busy) continue;
+            osc_status st = OSC_OK;
+            if (!slot.arrived()) {
+                // a stream that has drained or failed without the flag: the
+                // device lost the request
+                if (now_s() < slot.t_query) continue;
+                slot.t_query = now_s() + kOverdueS;
+                if (hipStreamQuery(slot.stream) == hipErrorNotReady || slot.arrived()) continue;
+                st = OSC_ERR_DEVICE;
+            }
             Request& r = sv->reqs[slot.ticket];
-            r.hist.assign(slot.h_hist, slot.h_hist + sv->nbt);
-            if (r.with_nll) r.nll = slot.h_hist[sv->nbt];
-            r.t_done = slot.t_done.load(std::memory_order_relaxed);
-            r.done = true;
-            sv->arena.release(slot.off, slot.bytes);
-            slot.busy = false;
-            slot.finished.store(0, std::memory_order_relaxed);
-            ++sv->stats.completed;
-            --sv->stats.in_flight;
-            sv->cv_done.notify_all();
+            if (st == OSC_OK) {
+                r.hist.assign(slot.h_hist, slot.h_hist + sv->nbt);
+                if (r.with_nll) r.nll = slot.h_hist[sv->nbt];
+            }
+            retire(sv, slot, r, st);
+            retired = true;
         }
+        if (retired) sv->cv_done.notify_all();
         // admit from the head of the queue while a slot and the budget allow
         while (!sv->pending.empty()) {
             Slot* free_slot = nullptr;
@@ -219,6 +239,7 @@ void dispatch_loop(osc_server* sv)
             free_slot->off = off;
             free_slot->bytes = bytes;
             r.t_admit = now_s();
+            free_slot->t_query = r.t_admit + kOverdueS;
             ++sv->stats.admitted;
             ++sv->stats.in_flight;
             sv->stats.max_in_flight = std::max(sv->stats.max_in_flight, sv->stats.in_flight);
@@ -230,22 +251,27 @@ void dispatch_loop(osc_server* sv)
                 // enqueued before the failure may still use the scratch, so
                 // the slot's stream drains first
                 (void)hipStreamSynchronize(free_slot->stream);
-                r.status = st;
-                r.done = true;
-                r.t_done = now_s();
-                sv->arena.release(off, bytes);
-                free_slot->busy = false;
-                --sv->stats.in_flight;
-                ++sv->stats.failed;
+                retire(sv, *free_slot, r, st);
                 sv->cv_done.notify_all();
             }
         }
         bool any_busy = false;
         for (const Slot& slot : sv->slots) any_busy |= slot.busy;
-        // completions arrive without a notification (lock-free callback), so
-        // poll briefly while work is in flight
-        sv->cv_dispatch.wait_for(lock, any_busy ? std::chrono::microseconds(20)
-                                                : std::chrono::microseconds(2000));
+        if (!any_busy) {
+            sv->cv_dispatch.wait_for(lock, std::chrono::microseconds(2000));
+            continue;
+        }
+        // completions arrive without a notification: watch the flags for
+        // kSpinS with the lock open, then sleep between looks
+        const uint64_t calls = sv->calls.load(std::memory_order_relaxed);
+        lock.unlock();
+        const double until = now_s() + kSpinS;
+        bool arrived = false;
+        while (!arrived && now_s() < until && sv->calls.load(std::memory_order_relaxed) == calls)
+            for (const Slot& slot : sv->slots) arrived |= slot.busy && slot.arrived();
+        lock.lock();
+        if (!arrived && sv->calls.load(std::memory_order_relaxed) == calls)
+            sv->cv_dispatch.wait_for(lock, std::chrono::microseconds(20));
     }
 }
 
@@ -312,9 +338,14 @@ osc_status osc_server_create(osc_ctx* ctx, const osc_sample* samples, int32_t n_
     for (Slot& slot : sv->slots) {
         ok = ok && hipStreamCreateWithFlags(&slot.stream, hipStreamNonBlocking) == hipSuccess &&
              hipMalloc(&slot.d_hist, size_t(sv->nbt + 1) * sizeof(double)) == hipSuccess &&
-             hipHostMalloc(&slot.h_hist, size_t(sv->nbt + 1) * sizeof(double),
-                           hipHostMallocDefault) == hipSuccess;
+             hipMemset(slot.d_hist, 0, size_t(sv->nbt + 1) * sizeof(double)) == hipSuccess &&
+             hipHostMalloc(&slot.h_hist, size_t(sv->nbt + 2) * sizeof(double),
+                           hipHostMallocCoherent) == hipSuccess;
+        if (!ok) break;
+        slot.flag = reinterpret_cast<unsigned*>(slot.h_hist + sv->nbt + 1);
+        *slot.flag = 0;
     }
+    ok = ok && hipDeviceSynchronize() == hipSuccess;
     if (!ok) {
         destroy_server(sv);
         return OSC_ERR_OUT_OF_MEMORY;
@@ -336,6 +367,7 @@ osc_status osc_server_destroy(osc_server* sv)
     {
         std::lock_guard<std::mutex> lock(sv->mu);
         sv->stop = true;
+        sv->calls.fetch_add(1, std::memory_order_relaxed);
     }
     sv->cv_dispatch.notify_all();
     if (sv->dispatcher.joinable()) sv->dispatcher.join();
@@ -366,6 +398,7 @@ osc_status osc_server_submit(osc_server* sv, const osc_params* set, int32_t samp
         r.precision = precision;
         r.t_submit = now_s();
         sv->pending.push_back(t);
+        sv->calls.fetch_add(1, std::memory_order_relaxed);
         ++sv->stats.submitted;
         sv->stats.max_queued = std::max<int64_t>(sv->stats.max_queued, int64_t(sv->pending.size()));
         *ticket = t;

@@ -231,3 +231,33 @@ def test_server_likelihood_and_mcmc(osc, ctx, resident):
             server.set_data(data, -1.0)
     finally:
         server.close()
+
+
+@pytest.mark.parametrize("nbins", [3, 63, 150])          # one lane round, and several
+@pytest.mark.parametrize("tiles", [1, 2, 1024, 1025, 4097, 16385, 65537])
+def test_request_ends_on_the_device(osc, ctx, tiles, nbins):
+    """Both sides of every merge shape that can end a request (a single tile
+    has no merge, above 65536 tiles a level comes before): histogram and
+    -2 ln L bit-identical to osc_fill_pdf and osc_poisson_nll, request after
+    request on the same slot, with and without a data row."""
+    s = workload.make_sample(4096, 7, L_km=295.0, rho_gcc=2.6)
+    n = tiles * 1024 - 300
+    ds = osc.DeviceSample.from_host(s)
+    for a in ("e_true", "flags", "weight", "e_reco"):
+        setattr(ds, a, getattr(ds, a).repeat(-(-n // 4096))[:n].contiguous())
+    counts = np.random.default_rng(tiles).integers(0, 9, (1, nbins)).astype(np.float64)
+    sets = workload.make_param_sets(3, 21)
+    h = torch.empty(nbins + 2, dtype=torch.float64, device="cuda")
+    nll = torch.empty(1, dtype=torch.float64, device="cuda")
+    server = osc.Server(ctx, [ds], nbins, 0.0, 3.0, slots=1)
+    try:
+        for k, tier in enumerate((osc.OSC_FP64, osc.OSC_FP32_MIXED, osc.OSC_FP64)):
+            server.set_data(None if k == 2 else counts, 1e-3)
+            got = server.wait(server.submit(sets[k], 0, tier))
+            ctx.osc_set_params([sets[k]])
+            ctx.osc_fill_pdf(ds, 0, nbins, 0.0, 3.0, h, precision=tier)
+            ctx.osc_poisson_nll(h, torch.from_numpy(counts).cuda(), nll, mu_scale=1e-3)
+            assert_bits_equal(got.hist, h.cpu().numpy())
+            assert np.isnan(got.nll) if k == 2 else got.nll == float(nll.cpu()[0])
+    finally:
+        server.close()
