@@ -223,3 +223,14 @@ def test_full_size_template(osc, ctx):
     np.testing.assert_array_equal(h, oracle.bincentre_contract(T, P))
     P_o = oracle.centre_probs(workload.TABLE1, s.L_km, s.rho_gcc, s.Ye, 200, 0.1, 10.1)
     assert np.abs(P - P_o).max() <= P_TOL
+
+
+@pytest.mark.parametrize("nt", [2, 3, 28, 29, 227, 228, 455, 456, 2731])
+def test_contraction_rounds(osc, ctx, nt):
+    """Both sides of one and two rounds of terms (4096 each), of one group of
+    rows (512) and of the first rows, and many rounds: the fixed order's bits,
+    with NaN and infinite terms of a bad event kept in their own bin."""
+    s = mixed_sample(20_000, 5 + nt)
+    s.weight[::500] = np.inf
+    used, T, P, h = run_bincentre(osc, ctx, s, nt, 0.1, 6.1, 4, 0.0, 5.0)
+    np.testing.assert_array_equal(h, oracle.bincentre_contract(T, P))
