@@ -54,14 +54,19 @@ FLOPS_PER_EVENT_COMPUTED_BINS = 158
 # phase scale 3, two sines and cosines 52, the operator's coefficients 18;
 # per vector taken through a layer: y = N v 22, t = kappa y - i s v 30, c0 v
 # 18, N t 28; per event 1/E 7, u . v 24, |S|^2 3 and the weighted add 2.  A
-# path that reads the same from both ends solves its first half only.
+# path that reads the same from both ends solves its first half only and takes
+# two vectors through each of its layers by the operator's elements: N^2 10,
+# real parts 9, imaginary parts 19, and 66 a vector.
 LAYER_SOLVE_FLOPS = 122
 LAYER_VECTOR_FLOPS = 98
+LAYER_PAIR_FLOPS = 170
 
 
 def layered_flops_per_event(n_layers, mirrored):
-    solved = (n_layers + 1) // 2 if mirrored else n_layers
-    return LAYER_SOLVE_FLOPS * solved + LAYER_VECTOR_FLOPS * n_layers + 36
+    pairs = n_layers // 2 if mirrored else 0
+    single = n_layers - 2 * pairs
+    return (LAYER_SOLVE_FLOPS * (pairs + single) + LAYER_PAIR_FLOPS * pairs +
+            LAYER_VECTOR_FLOPS * single + 36)
 
 
 # FP64 vector peak: 256 CUs x 4 SIMDs x 16 lanes x 2 flop (FMA) x 2.4 GHz.
@@ -79,12 +84,12 @@ KERNEL_SOURCES = ("paper_1311_7579_amd/csrc/osc_device.h",
                   "paper_1311_7579_amd/csrc/osc_kernels.hip",
                   "paper_1311_7579_amd/build.py")
 COUNTER_TRAFFIC = {
-    "fetch_kib": 92833.2, "fetch_scale": 2.0,     # copy of 512 MiB: FETCH_SIZE 262157 KiB
-    "write_kib": 82429.8, "write_scale": 1.0,     # copy of 512 MiB: WRITE_SIZE 524288 KiB
+    "fetch_kib": 92838.8, "fetch_scale": 2.0,     # copy of 512 MiB: FETCH_SIZE 262157 KiB
+    "write_kib": 82419.5, "write_scale": 1.0,     # copy of 512 MiB: WRITE_SIZE 524288 KiB
     "valu_per_event": 145.2,
     "classes_per_event": {"fp64": 95.9, "fp64_trans": 1.0, "fp32": 19.0, "fp32_trans": 2.0,
                           "cvt": 3.0, "int32": 6.81, "int64": 0.438, "other": 17.05},
-    "source_sha256": "c7587d2fa31a7543de12d7a31907e47990c77a5811eee2739f93ab02aed1268e",
+    "source_sha256": "1b5fafd76e078f55d15fd225df831077ae1a4d5f9f80cabe1b4400e4107dec3c",
 }
 # Issue time of one wave instruction on one SIMD, measured on the box with
 # probe kernels of independent chains (ns): FP64 FMA/MUL/ADD 2.08, FP32

@@ -541,7 +541,7 @@ struct ConstDensityProb {
 //   cos psi - i (sin psi / del) N + kappa (N^2 - del^2)
 //     = c0 + N (kappa N - i s),   s = sin psi / del,
 //   kappa = (exp(-i theta) - cos psi + i s b) / f'(x),  c0 = cos psi - kappa del^2,
-// two products with a real tridiagonal matrix per vector.
+// two products with a real tridiagonal matrix per vector (propagate).
 //
 // M is symmetric, so every layer's operator is, and a path that reads the
 // same from both ends gives S = T^T T or T^T S_mid T with T the first
@@ -549,10 +549,11 @@ struct ConstDensityProb {
 // through each layer of the first half with one set of coefficients.
 //
 // Bound by VALU issue: about 95 FP64 issue slots for a layer's coefficients
-// and 58 for each vector through it.  With complex 3x3 products in the
-// flavour basis and every layer solved, 1e7 events took 424 us through the
-// five-layer Earth path (now 229) and 3e6 events 300 us through 12 layers
-// (now 137).
+// and 58 for a vector through it, or 96 for two (by the operator's elements:
+// 24 to form them, 36 a vector; two times 58 took 3 % longer over five layers
+// and 8 % over 12 and 31).  With complex 3x3 products in the flavour basis and
+// every layer solved, 1e7 events took 424 us through the five-layer Earth path
+// (now 231) and 3e6 events 300 us through 12 layers (now 133).
 struct Vec3 {
     double r[3], i[3];
 };
@@ -591,6 +592,41 @@ __device__ __forceinline__ void propagate(const LayerOp& o, Vec3& v)
     add_times(o, t.i, v.i);
 }
 
+// Both vectors through one layer, by the operator's six elements (it is
+// symmetric): S = c0 + kappa N^2 - i s N.
+__device__ __forceinline__ void propagate_both(const LayerOp& o, const Tridiagonal& tri, Vec3& v,
+                                               Vec3& u)
+{
+    // N^2
+    const double n00 = fma(o.p0, o.p0, tri.b00), n11 = fma(o.p1, o.p1, tri.b00 + tri.b11),
+                 n22 = fma(o.p2, o.p2, tri.b11), n01 = o.b0 * (o.p0 + o.p1),
+                 n12 = o.b1 * (o.p1 + o.p2), n02 = tri.b01;
+    const double r00 = fma(o.kr, n00, o.c0r), r11 = fma(o.kr, n11, o.c0r),
+                 r22 = fma(o.kr, n22, o.c0r), r01 = o.kr * n01, r12 = o.kr * n12,
+                 r02 = o.kr * n02;
+    const double i00 = fma(o.ki, n00, fma(-o.s, o.p0, o.c0i)),
+                 i11 = fma(o.ki, n11, fma(-o.s, o.p1, o.c0i)),
+                 i22 = fma(o.ki, n22, fma(-o.s, o.p2, o.c0i)),
+                 i01 = fma(o.ki, n01, -(o.s * o.b0)), i12 = fma(o.ki, n12, -(o.s * o.b1)),
+                 i02 = o.ki * n02;
+    const auto row = [](double ar, double ai, double br, double bi, double cr, double ci,
+                        const Vec3& x, double& re, double& im) {
+        re = fma(ar, x.r[0], fma(-ai, x.i[0], fma(br, x.r[1], fma(-bi, x.i[1],
+             fma(cr, x.r[2], -(ci * x.i[2]))))));
+        im = fma(ar, x.i[0], fma(ai, x.r[0], fma(br, x.i[1], fma(bi, x.r[1],
+             fma(cr, x.i[2], ci * x.r[2])))));
+    };
+    const auto apply = [&](Vec3& x) {
+        Vec3 y;
+        row(r00, i00, r01, i01, r02, i02, x, y.r[0], y.i[0]);
+        row(r01, i01, r11, i11, r12, i12, x, y.r[1], y.i[1]);
+        row(r02, i02, r12, i12, r22, i22, x, y.r[2], y.i[2]);
+        x = y;
+    };
+    apply(v);
+    apply(u);
+}
+
 __device__ __forceinline__ double event_prob_layered(const SetConsts& sc, const LayeredTables& T,
                                                      const LayerPath& lp, double E, uint32_t f)
 {
@@ -626,8 +662,10 @@ __device__ __forceinline__ double event_prob_layered(const SetConsts& sc, const 
         o.p2 = fma(0.5, lv.e, lp.tri.a2);
         o.b0 = lp.tri.b0;
         o.b1 = lp.tri.b1;
-        propagate(o, v);
-        if (k < lp.pairs) propagate(o, u);
+        if (k < lp.pairs)
+            propagate_both(o, lp.tri, v, u);
+        else
+            propagate(o, v);
     }
     double zr = 0.0, zi = 0.0;
 #pragma unroll

@@ -131,6 +131,9 @@ void tridiagonal_consts(const osc_params& p, osc::Tridiagonal& t)
     t.a1 = c * c * K[1][1] + 2.0 * c * s * K[1][2] + s * s * K[2][2];
     t.a2 = s * s * K[1][1] - 2.0 * c * s * K[1][2] + c * c * K[2][2];
     t.b1 = (c * c - s * s) * K[1][2] + c * s * (K[2][2] - K[1][1]);
+    t.b00 = t.b0 * t.b0;
+    t.b01 = t.b0 * t.b1;
+    t.b11 = t.b1 * t.b1;
     // rows of R23 diag(1, 1, e^{i delta}) times that rotation
     const cplx ep = std::polar(1.0, p.delta_cp);
     const cplx row[3][2] = {{0.0, 0.0}, {c23, s23 * ep}, {-s23, c23 * ep}};
