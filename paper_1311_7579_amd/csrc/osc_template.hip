@@ -183,92 +183,103 @@ __device__ __forceinline__ void load_block(const double* __restrict__ ws, uint32
     }
 }
 
-// s plus the values first .. min(first + kSumBlock, len) - 1 of ws.
-__device__ __forceinline__ double add_rows(double s, const double* __restrict__ ws, uint32_t first,
-                                           uint32_t len, int lane)
-{
-    const uint32_t end = min(first + kSumBlock, len);
-    double next = first + lane < end ? ws[first + lane] : 0.0;
-#pragma unroll 1
-    for (uint32_t at = first; at < end; at += 64) {
-        const double v = next;
-        const uint32_t i = at + 64 + lane;
-        if (at + 64 < end) next = i < end ? ws[i] : 0.0;
-        s = add_row(s, v);
-    }
-    return s;
-}
-
+// s plus the values of block v that are among the len of its row.  If the
+// block does not stand as a whole, its rows of 64 follow one by one, read back
+// from `rows` (LDS of the wave's own).
 __device__ __forceinline__ double add_block(double s, const double (&v)[kSumRows],
-                                            const double* __restrict__ ws, uint32_t first,
+                                            double* __restrict__ rows, uint32_t first,
                                             uint32_t len, int lane)
 {
     RowSum block(s);
 #pragma unroll
     for (int j = 0; j < kSumRows; ++j) block.add(v[j]);
     double total;
-    return block.finish(total) ? total : add_rows(s, ws, first, len, lane);
+    if (block.finish(total)) return total;
+    if (first >= len) return s;
+#pragma unroll
+    for (int j = 0; j < kSumRows; ++j) rows[j * 64 + lane] = v[j];
+    const uint32_t n = min(kSumBlock, len - first);
+    double next = rows[lane];
+#pragma unroll 1
+    for (uint32_t at = 0; at < n; at += 64) {
+        const double row = next;
+        if (at + 64 < n) next = rows[at + 64 + lane];
+        s = add_row(s, row);
+    }
+    return s;
 }
 
-// Weight sum of every cell.  A workgroup takes 512 cells, a stride apart (the
-// fullest cells are neighbours).  A lane adds a short row by itself; a wave
-// adds a middling one block by block; the workgroup's eight waves add a long
-// one, each forming a block's part of 8192 values at a time from the sum
-// before them (if that does not stand, the waves go on one after the other).
-// The next values are loaded before these are added.  Bound by the memory
-// latency of the fullest cell's chain of loads: 1e7 events in 187200 cells
-// took 5900 us with one thread per cell and 16 loads ahead, 302 us with one
-// wave for each long row, 240 us now; most of that is the first few thousand
-// values of the long rows, where ties are frequent.
+// Weight sum of every cell.  A first kernel has a lane add each short row and
+// lists the longer ones; a second one has a wave add a middling row block by
+// block, and a workgroup's eight waves a long one, each wave forming a block's
+// part of 8192 values at a time from the sum before them (if that does not
+// stand, the waves go on one after the other).  The next values are loaded
+// before these are added.  Bound by the chain of the fullest cells, above all
+// by their first few thousand values, where ties are frequent.  1e7 events in
+// 187200 cells: one thread a cell with 16 loads ahead 5900 us; one kernel whose
+// waves each took the middling rows of their own 64 cells in turn, rows of a
+// block read again from memory, 240; listed and spread over all waves 167;
+// the block's rows kept in LDS 148.  Long rows from 4096, 8192, 16384 or 32768
+// values (the whole build): 673, 644, 654, 671 us.
 constexpr uint32_t kShortRow = 32;
-constexpr uint32_t kLongRow = 16384;
+constexpr uint32_t kLongRow = 8192;
 constexpr int kSumWaves = 8;
-__global__ __launch_bounds__(kSumWaves * 64) void template_sum_kernel(
-    uint32_t n_cells, const uint2* __restrict__ rows, const double* __restrict__ ws,
-    double* __restrict__ T)
+constexpr unsigned kSumBlocks = 512;
+
+// The cells that the first kernel leaves: counts[0] middling ones, counts[1]
+// long ones (both 0 beforehand).
+struct RowLists {
+    uint32_t *counts, *middling, *longs;
+};
+
+__global__ __launch_bounds__(256) void template_short_kernel(uint32_t n_cells,
+                                                             const uint2* __restrict__ rows,
+                                                             const double* __restrict__ ws,
+                                                             double* __restrict__ T,
+                                                             RowLists lists)
 {
-    __shared__ uint3 long_rows[kSumWaves * 64];   // first, length, thread of the cell
-    __shared__ uint32_t n_long;
-    __shared__ double part[kSumWaves];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (threadIdx.x == 0) n_long = 0;
-    __syncthreads();
-    const int64_t cell = int64_t(blockIdx.x) + int64_t(threadIdx.x) * gridDim.x;
+    const uint32_t cell = blockIdx.x * 256u + threadIdx.x;
+    const int lane = threadIdx.x & 63;
     const uint2 row = cell < n_cells ? rows[cell] : uint2{0u, 0u};
     const uint32_t len = row.y - row.x;
+    const auto list = [&](bool mine, uint32_t* count, uint32_t* to) {
+        const uint64_t mask = __ballot(mine);
+        if (!mask) return;
+        const int leader = __builtin_ctzll(mask);
+        uint32_t at = 0;
+        if (lane == leader) at = atomicAdd(count, uint32_t(__builtin_popcountll(mask)));
+        at = __builtin_amdgcn_readlane(at, leader);
+        if (mine) to[at + __builtin_popcountll(mask & ((uint64_t(1) << lane) - 1))] = cell;
+    };
+    list(len > kShortRow && len <= kLongRow, lists.counts, lists.middling);
+    list(len > kLongRow, lists.counts + 1, lists.longs);
+    if (cell >= n_cells || len > kShortRow) return;
     double s = 0.0;
-    if (len <= kShortRow) {
-        uint32_t i = row.x;
-        for (; row.y - i >= 8u; i += 8u) {
-            double v[8];
+    uint32_t i = row.x;
+    for (; row.y - i >= 8u; i += 8u) {
+        double v[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = ws[i + j];
+        for (int j = 0; j < 8; ++j) v[j] = ws[i + j];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) s = s + v[j];
-        }
-        for (; i < row.y; ++i) s = s + ws[i];
-    } else if (len > kLongRow) {
-        long_rows[atomicAdd(&n_long, 1u)] = uint3{row.x, len, threadIdx.x};
+        for (int j = 0; j < 8; ++j) s = s + v[j];
     }
-    for (uint64_t mask = __ballot(len > kShortRow && len <= kLongRow); mask; mask &= mask - 1) {
-        const int l = __builtin_ctzll(mask);
-        const double* w = ws + uint32_t(__builtin_amdgcn_readlane(int(row.x), l));
-        const uint32_t n = __builtin_amdgcn_readlane(int(len), l);
-        double next[kSumRows], v[kSumRows], c = 0.0;
-        load_block(w, 0, n, lane, next);
-        for (uint32_t first = 0; first < n; first += kSumBlock) {
-#pragma unroll
-            for (int j = 0; j < kSumRows; ++j) v[j] = next[j];
-            if (first + kSumBlock < n) load_block(w, first + kSumBlock, n, lane, next);
-            c = add_block(c, v, w, first, n, lane);
-        }
-        if (lane == l) s = c;
-    }
-    __syncthreads();
-    for (uint32_t k = 0; k < n_long; ++k) {
-        const uint3 r = long_rows[k];
-        const double* w = ws + r.x;
-        const uint32_t n = r.y;
+    for (; i < row.y; ++i) s = s + ws[i];
+    T[cell] = s;
+}
+
+__global__ __launch_bounds__(kSumWaves * 64) void template_sum_kernel(
+    const uint2* __restrict__ rows, const double* __restrict__ ws, double* __restrict__ T,
+    RowLists lists)
+{
+    __shared__ double part[kSumWaves], rows_lds[kSumWaves][kSumBlock];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+    const uint32_t n_long = lists.counts[1], n_middling = lists.counts[0];
+    for (uint32_t k = blockIdx.x; k < n_long; k += gridDim.x) {
+        const uint32_t cell = lists.longs[k];
+        const uint2 row = rows[cell];
+        const double* w = ws + row.x;
+        const uint32_t n = row.y - row.x;
         double next[kSumRows], v[kSumRows], c = 0.0;
         load_block(w, wave * kSumBlock, n, lane, next);
         for (uint32_t first = 0; first < n; first += kSumWaves * kSumBlock) {
@@ -295,7 +306,7 @@ __global__ __launch_bounds__(kSumWaves * 64) void template_sum_kernel(
             } else {
                 for (int j = 0; j < kSumWaves; ++j) {
                     if (wave == j) {
-                        c = add_block(c, v, w, mine, n, lane);
+                        c = add_block(c, v, rows_lds[wave], mine, n, lane);
                         if (lane == 0) part[0] = c;
                     }
                     __syncthreads();
@@ -304,9 +315,23 @@ __global__ __launch_bounds__(kSumWaves * 64) void template_sum_kernel(
                 }
             }
         }
-        if (threadIdx.x == r.z) s = c;
+        if (threadIdx.x == 0) T[cell] = c;
     }
-    if (cell < n_cells) T[cell] = s;
+    for (uint32_t k = blockIdx.x * kSumWaves + wave; k < n_middling; k += gridDim.x * kSumWaves) {
+        const uint32_t cell = lists.middling[k];
+        const uint2 row = rows[cell];
+        const double* w = ws + row.x;
+        const uint32_t n = row.y - row.x;
+        double next[kSumRows], v[kSumRows], c = 0.0;
+        load_block(w, 0, n, lane, next);
+        for (uint32_t first = 0; first < n; first += kSumBlock) {
+#pragma unroll
+            for (int j = 0; j < kSumRows; ++j) v[j] = next[j];
+            if (first + kSumBlock < n) load_block(w, first + kSumBlock, n, lane, next);
+            c = add_block(c, v, rows_lds[wave], first, n, lane);
+        }
+        if (lane == 0) T[cell] = c;
+    }
 }
 
 // P of the 18 channels at the centre of every true bin, layout P[c][t].
@@ -468,10 +493,11 @@ osc_status osc_template_create(osc_ctx* ctx, const osc_sample* sample,
                          static_cast<uint32_t*>(nullptr), static_cast<const double*>(nullptr),
                          static_cast<double*>(nullptr), int(n), 0, end_bit, nullptr) != hipSuccess)
             st = OSC_ERR_DEVICE;
-        // one workspace: the cells' rows and the count of used events, the
+        // one workspace: the cells' rows, the count of used events and those
+        // of the listed rows, the
         // keys before and after the sort, the sorted weights, the sort's own
         const auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
-        const size_t rows_b = up(size_t(n_cells) * sizeof(uint2) + sizeof(uint32_t));
+        const size_t rows_b = up(size_t(n_cells) * sizeof(uint2) + 3 * sizeof(uint32_t));
         const size_t keys_b = up(size_t(n) * sizeof(uint32_t));
         const size_t ws_b = up(size_t(n) * sizeof(double));
         osc::host::BuildSpace space;
@@ -502,9 +528,17 @@ osc_status osc_template_create(osc_ctx* ctx, const osc_sample* sample,
                 }
             }
             if (e == hipSuccess) {
-                hipLaunchKernelGGL(osc::template_sum_kernel, dim3(blocks_for(n_cells, osc::kSumWaves * 64)),
-                                   dim3(osc::kSumWaves * 64), 0, s, n_cells, rows, ws, tp->d_T);
+                // the unsorted keys' place holds the lists: every listed row
+                // has more than kShortRow events, a long one more than kLongRow
+                const osc::RowLists lists{d_used + 1, keys, keys + n / osc::kShortRow};
+                hipLaunchKernelGGL(osc::template_short_kernel, dim3(blocks_for(n_cells, 256)),
+                                   dim3(256), 0, s, n_cells, rows, ws, tp->d_T, lists);
                 e = hipGetLastError();
+                if (e == hipSuccess && n > int64_t(osc::kShortRow)) {
+                    hipLaunchKernelGGL(osc::template_sum_kernel, dim3(osc::kSumBlocks),
+                                       dim3(osc::kSumWaves * 64), 0, s, rows, ws, tp->d_T, lists);
+                    e = hipGetLastError();
+                }
             }
             if (e == hipSuccess)
                 e = hipMemcpyAsync(&used, d_used, sizeof used, hipMemcpyDeviceToHost, s);

@@ -234,3 +234,26 @@ def test_contraction_rounds(osc, ctx, nt):
     s.weight[::500] = np.inf
     used, T, P, h = run_bincentre(osc, ctx, s, nt, 0.1, 6.1, 4, 0.0, 5.0)
     np.testing.assert_array_equal(h, oracle.bincentre_contract(T, P))
+
+
+@pytest.mark.parametrize("nt,lengths", [(5, (8191, 8192, 8193, 16385, 0)),
+                                        (530, (8193,)),               # more than the workgroups
+                                        (5000, (33, 0, 32, 64, 1100)),
+                                        (40_000, (1, 31, 0, 34))])
+def test_cells_listed_by_length(osc, ctx, nt, lengths):
+    """Short, middling and long cells next to one another, and more of a kind
+    than there are waves or workgroups to add them: every entry has the bits
+    of adding its weights in event order."""
+    cell = np.repeat(np.arange(nt), np.resize(lengths, nt))
+    rng = np.random.default_rng(nt)
+    rng.shuffle(cell)
+    w = rng.uniform(0.5, 1.5, cell.size)
+    w[::5] = 2.0 ** -40 * (2 * rng.integers(0, 1 << 20, w[::5].size) + 1)   # ties
+    e = 1.0 + (cell + 0.5) / nt
+    flags = workload.make_flags(np.ones(cell.size, int), np.ones(cell.size, int),
+                                np.zeros(cell.size, bool))
+    s = workload.Sample(e, flags, w, e.copy())
+    used, T, P, h = run_bincentre(osc, ctx, s, nt, 1.0, 2.0, 1, 0.0, 3.0)
+    T_o, used_o = oracle.template(s.e_true, s.flags, s.weight, s.e_reco, nt, 1.0, 2.0, 1, 0.0, 3.0)
+    assert used == used_o == cell.size
+    np.testing.assert_array_equal(T, T_o)
