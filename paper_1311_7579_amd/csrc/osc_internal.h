@@ -7,7 +7,7 @@
 namespace osc {
 
 // Reduction contract of the binned PDF: a tile is kTileLanes lanes x
-// kLaneEvents events per lane (one wave64 per tile).
+// kLaneEvents events per lane (one wave64 per tile, or several that share it).
 constexpr int kTileLanes = 64;
 #ifndef OSC_LANE_EVENTS
 #define OSC_LANE_EVENTS 16

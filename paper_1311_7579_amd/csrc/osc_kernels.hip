@@ -1,6 +1,7 @@
 // HIP kernels of libosc for gfx950 (CDNA4, wave64).
 //
-// One wave64 owns one tile of kTileEvents consecutive events.  Lane l of
+// One wave64 owns one tile of kTileEvents consecutive events (four or eight
+// share it where tiles are few).  Lane l of
 // tile t handles events t*T + m*64 + l, m = 0..K-1 (coalesced SoA loads,
 // software-pipelined one group of kGroup events ahead), computes the oscillation
 // probability of each event in FP64 (flavour basis, one amplitude element
