@@ -13,6 +13,7 @@
 // arithmetic as the fused kernel), one wave per reconstructed bin for the
 // contraction (lane-strided sums, then the wave's binary tree).
 #include <hipcub/hipcub.hpp>
+#include <rocprim/rocprim.hpp>
 
 #include <cstdint>
 #include <new>
@@ -441,6 +442,34 @@ bool true_binning_ok(const osc_binning* b)
     return wb > 0.0 && wb < 1e300;
 }
 
+// The stable sort of (cell key, weight) by the lowest end_bit bits of the key;
+// with tmp null only *bytes, the workspace, is set.  hipCUB takes 8 bits of the
+// key in a pass and merge sort up to about 2^20 values; rocPRIM's radix sort
+// underneath it also takes 9 bits, which saves a pass for keys of 17 and 18 (or
+// 25 to 27) bits.  Template builds with hipCUB's choice | 9 bits (us): 18 bits,
+// 1e7 events 623 | 534, 5e6 477 | 423, 2e6 292 | 273; 20 bits, 5e6 501 | 508, 2e6
+// 352 | 378; any width, 1e6 336-393 | 225-306, 4e5 267-292 | 193-232, 2e5 184-219
+// | 171-225, 4e4 141-187 | 148-214.
+using NineBits = rocprim::radix_sort_config<
+    rocprim::default_config, rocprim::default_config,
+    rocprim::radix_sort_onesweep_config<rocprim::kernel_config<512, 8>,
+                                        rocprim::kernel_config<512, 12>, 9,
+                                        rocprim::block_radix_rank_algorithm::match>,
+    0>;
+
+hipError_t sort_cells(void* tmp, size_t* bytes, const uint32_t* keys, uint32_t* keys_out,
+                      const double* weights, double* weights_out, int64_t n, int end_bit,
+                      hipStream_t stream)
+{
+    const bool fewer_passes = (end_bit + 8) / 9 < (end_bit + 7) / 8;
+    if (n > (1 << 18) && (n <= (1 << 20) || fewer_passes))
+        return rocprim::radix_sort_pairs<NineBits>(tmp, *bytes, keys, keys_out, weights,
+                                                   weights_out, size_t(n), 0u, unsigned(end_bit),
+                                                   stream);
+    return hipcub::DeviceRadixSort::SortPairs(tmp, *bytes, keys, keys_out, weights, weights_out,
+                                              int(n), 0, end_bit, stream);
+}
+
 unsigned blocks_for(int64_t n, int threads) { return unsigned((n + threads - 1) / threads); }
 
 }  // namespace
@@ -488,10 +517,8 @@ osc_status osc_template_create(osc_ctx* ctx, const osc_sample* sample,
     uint32_t used = 0;
     if (st == OSC_OK) {
         size_t sort_bytes = 0;
-        if (n > 0 && hipcub::DeviceRadixSort::SortPairs(
-                         nullptr, sort_bytes, static_cast<const uint32_t*>(nullptr),
-                         static_cast<uint32_t*>(nullptr), static_cast<const double*>(nullptr),
-                         static_cast<double*>(nullptr), int(n), 0, end_bit, nullptr) != hipSuccess)
+        if (n > 0 && sort_cells(nullptr, &sort_bytes, nullptr, nullptr, nullptr, nullptr, n, end_bit,
+                                nullptr) != hipSuccess)
             st = OSC_ERR_DEVICE;
         // one workspace: the cells' rows, the count of used events and those
         // of the listed rows, the
@@ -518,9 +545,7 @@ osc_status osc_template_create(osc_ctx* ctx, const osc_sample* sample,
                                    osc::host::bin_consts(reco_binning), n_cells, keys);
                 e = hipGetLastError();
                 if (e == hipSuccess)
-                    e = hipcub::DeviceRadixSort::SortPairs(tmp, sort_bytes, keys, skeys,
-                                                           sample->weight, ws, int(n), 0, end_bit,
-                                                           s);
+                    e = sort_cells(tmp, &sort_bytes, keys, skeys, sample->weight, ws, n, end_bit, s);
                 if (e == hipSuccess) {
                     hipLaunchKernelGGL(osc::template_bounds_kernel, dim3(blocks_for(n, 256)),
                                        dim3(256), 0, s, n, skeys, n_cells, rows, d_used);

@@ -257,3 +257,15 @@ def test_cells_listed_by_length(osc, ctx, nt, lengths):
     T_o, used_o = oracle.template(s.e_true, s.flags, s.weight, s.e_reco, nt, 1.0, 2.0, 1, 0.0, 3.0)
     assert used == used_o == cell.size
     np.testing.assert_array_equal(T, T_o)
+
+
+@pytest.mark.parametrize("nt,nr", [(200, 50), (333, 120)])     # keys of 18 and 20 bits
+@pytest.mark.parametrize("n", [1 << 18, (1 << 18) + 1, 1 << 20, (1 << 20) + 1])
+def test_sorts_by_size_and_key_width(osc, ctx, n, nt, nr):
+    """Both sides of every size at which the sort of the cells changes: the
+    template's bits, event order kept within every cell."""
+    s = mixed_sample(n, 3)
+    used, T, P, h = run_bincentre(osc, ctx, s, nt, 0.1, 6.1, nr, 0.0, 5.0)
+    T_o, used_o = oracle.template(s.e_true, s.flags, s.weight, s.e_reco, nt, 0.1, 6.1, nr, 0.0, 5.0)
+    assert used == used_o
+    np.testing.assert_array_equal(T, T_o)
