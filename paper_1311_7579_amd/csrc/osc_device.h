@@ -863,10 +863,13 @@ __device__ __forceinline__ EventIn load_event(const TileBufs& b, uint32_t l, uin
 {
     EventIn v;
     // a ragged tile's offset goes through the VGPR, which the resource's
-    // bound covers: lanes past the end read 0 without a branch
+    // bound covers: lanes past the end read 0 without a branch.  Their energy
+    // is 1 GeV, as in the batched kernel's load: in the FP32-mixed tier they
+    // take part in the wave's decisions, and so in its bits.
     const uint32_t lv = FULL ? l : l + g0, gs = FULL ? g0 : 0u;
     const uint32_t l8 = lv * 8u, g8 = gs * 8u;
     v.e = buf_load_f64(b.e, l8, g8);
+    if (!FULL && MODE != kHist) v.e = lv < n ? v.e : 1.0;
     v.f = MODE != kHist ? uint32_t(__builtin_amdgcn_raw_buffer_load_b8(b.f, lv, gs, 0)) : 0u;
     v.w = has_hist(MODE) ? buf_load_f64(b.w, l8, g8) : 0.0;
     v.x = has_hist(MODE) && !reads_bins(MODE) ? buf_load_f64(b.x, l8, g8) : 0.0;

@@ -138,3 +138,49 @@ def test_sets_side_by_side(osc, nbins, n_sets, spi):
                     assert_bits_equal(got[k, 0], h.cpu().numpy(), (k, schedule))
         finally:
             batch.close()
+
+
+@pytest.mark.parametrize("tail", [1, 17, 63])
+@pytest.mark.parametrize("rho,ye,e_range,th12", [(1.0, 0.5, (3.0, 30.0), 1e-3),
+                                                 (1.1, 0.5, (3.0, 30.0), 1e-4),
+                                                 (1.0, 0.5, (3.0, 30.0), 0.0),
+                                                 (150.0, 0.67, (0.05, 0.4), 0.307)])
+def test_ragged_wave_decides_alike_in_every_form(osc, rho, ye, e_range, th12, tail):
+    """In the FP32-mixed tier a wave decides as a whole on the roots' second
+    refinement (near a level crossing) and on the FP64 assembly (|A| > 0.01
+    eV^2).  The lanes past the end of a sample count as 1 GeV nu_e -> nu_e
+    events in the plain, binned and batched forms: with parameters and
+    densities where that event alone tips the wave, P has the bits it has in
+    the sample filled up with such events, and all three forms sum that P."""
+    n = 5 * 64 + tail
+    full = 1024
+    p = dict(workload.TABLE1, sin2_th12=th12)
+    with osc.Context(0) as ctx:
+        ctx.osc_set_params([p])
+        for k, L in enumerate((3000.0, 40_000.0, 400_000.0)):
+            s = workload.make_sample(full, 31 + k, L_km=L, rho_gcc=rho, e_range=e_range)
+            s.Ye = ye
+            s.e_true[n:], s.flags[n:] = 1.0, 0
+            filled = osc.DeviceSample.from_host(s)
+            cut = lambda t: t[:n].clone()
+            ds = osc.DeviceSample(cut(filled.e_true), cut(filled.flags), cut(filled.weight),
+                                  cut(filled.e_reco), L, rho, ye)
+            new = lambda m: torch.empty(m, dtype=torch.float64, device="cuda")
+            h, q, want_p = new(NB + 2), new(n), new(full)
+            ctx.osc_fill_pdf(filled, 0, NB, 0.0, HI, h, want_p, precision=osc.OSC_FP32_MIXED)
+            ctx.osc_fill_hist(cut(want_p), ds.weight, ds.e_reco, NB, 0.0, HI, h)
+            want_h, want_p = h.cpu().numpy(), want_p.cpu().numpy()[:n]
+            ctx.osc_fill_pdf(ds, 0, NB, 0.0, HI, h, q, precision=osc.OSC_FP32_MIXED)
+            assert_bits_equal(q.cpu().numpy(), want_p, ("plain P", L))
+            assert_bits_equal(h.cpu().numpy(), want_h, ("plain", L))
+            with ctx.osc_binned_create(ds, NB, 0.0, HI) as binned:
+                ctx.osc_fill_pdf_binned(binned, 0, h, q, precision=osc.OSC_FP32_MIXED)
+            assert_bits_equal(q.cpu().numpy(), want_p, ("binned P", L))
+            assert_bits_equal(h.cpu().numpy(), want_h, ("binned", L))
+            batch = osc.Batch(ctx, [ds], NB, 0.0, HI, osc.OSC_FP32_MIXED, max_sets=2)
+            try:
+                got = batch.run([p, p]).cpu().numpy()
+            finally:
+                batch.close()
+            for j in range(2):
+                assert_bits_equal(got[j, 0], want_h, ("batched", L, j))
