@@ -84,12 +84,12 @@ KERNEL_SOURCES = ("paper_1311_7579_amd/csrc/osc_device.h",
                   "paper_1311_7579_amd/csrc/osc_kernels.hip",
                   "paper_1311_7579_amd/build.py")
 COUNTER_TRAFFIC = {
-    "fetch_kib": 92857.5, "fetch_scale": 2.0,     # copy of 512 MiB: FETCH_SIZE 262157 KiB
-    "write_kib": 82387.3, "write_scale": 1.0,     # copy of 512 MiB: WRITE_SIZE 524288 KiB
-    "valu_per_event": 145.2,
+    "fetch_kib": 92834.1, "fetch_scale": 2.0,     # copy of 512 MiB: FETCH_SIZE 262157 KiB
+    "write_kib": 82451.7, "write_scale": 1.0,     # copy of 512 MiB: WRITE_SIZE 524288 KiB
+    "valu_per_event": 144.8,
     "classes_per_event": {"fp64": 95.9, "fp64_trans": 1.0, "fp32": 19.0, "fp32_trans": 2.0,
-                          "cvt": 3.0, "int32": 6.81, "int64": 0.438, "other": 17.05},
-    "source_sha256": "750297fb0a85c6875090752286c8205e129425cd2182d7fc0506af6959b2902d",
+                          "cvt": 3.0, "int32": 6.38, "int64": 0.438, "other": 17.08},
+    "source_sha256": "920ebacb2c135c66640090d213cde3d3f8597e690dde4b56030512ec445512fd",
 }
 # Issue time of one wave instruction on one SIMD, measured with
 # probe kernels of independent chains (ns): FP64 FMA/MUL/ADD 2.08, FP32
