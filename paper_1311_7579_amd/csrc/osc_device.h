@@ -542,6 +542,7 @@ __device__ __forceinline__ double event_prob_mixed(const SetConsts& sc, const Ti
 // body calls (MIXED selects the FP32-mixed amplitude assembly).
 template <bool MIXED>
 struct ConstDensityProb {
+    static constexpr bool kDecidesByWave = MIXED;   // ballots over the wave's events
     const SetConsts* sc;
     const Tables<MIXED>* tabs;
     double kA, kL;
@@ -704,6 +705,7 @@ __device__ __forceinline__ double event_prob_layered(const SetConsts& sc, const 
 
 // P of one event through a layered path (FP64).
 struct LayeredProb {
+    static constexpr bool kDecidesByWave = false;
     const SetConsts* sc;
     const LayeredTables* tabs;
     const LayerPath* lp;
@@ -857,19 +859,19 @@ __device__ __forceinline__ EventIn load_event(const TilePtrs& b, uint32_t l, uin
 
 // Event g0 + l of a tile (0 <= g0 + l < kTileEvents); n = the tile's events
 // (kTileEvents when FULL).  g0 is the same for the whole wave.
-template <int MODE, bool FULL>
+template <int MODE, bool FULL, bool FILL>
 __device__ __forceinline__ EventIn load_event(const TileBufs& b, uint32_t l, uint32_t g0,
                                               uint32_t n)
 {
     EventIn v;
     // a ragged tile's offset goes through the VGPR, which the resource's
-    // bound covers: lanes past the end read 0 without a branch.  Their energy
-    // is 1 GeV, as in the batched kernel's load: in the FP32-mixed tier they
-    // take part in the wave's decisions, and so in its bits.
+    // bound covers: lanes past the end read 0 without a branch.  Where they
+    // take part in the wave's decisions (FILL), and so in its bits, their energy
+    // is 1 GeV, as in the batched kernel's load.
     const uint32_t lv = FULL ? l : l + g0, gs = FULL ? g0 : 0u;
     const uint32_t l8 = lv * 8u, g8 = gs * 8u;
     v.e = buf_load_f64(b.e, l8, g8);
-    if (!FULL && MODE != kHist) v.e = lv < n ? v.e : 1.0;
+    if (FILL && !FULL && MODE != kHist) v.e = lv < n ? v.e : 1.0;
     v.f = MODE != kHist ? uint32_t(__builtin_amdgcn_raw_buffer_load_b8(b.f, lv, gs, 0)) : 0u;
     v.w = has_hist(MODE) ? buf_load_f64(b.w, l8, g8) : 0.0;
     v.x = has_hist(MODE) && !reads_bins(MODE) ? buf_load_f64(b.x, l8, g8) : 0.0;
@@ -967,17 +969,18 @@ __device__ __forceinline__ void tile_events(const PROB& prob, const BinConsts& b
     constexpr int kGroups = kLaneEvents / kGroup;
     const uint32_t l = uint32_t(lane);
     const TileBufs bufs = tile_bufs<MODE>(n, e_true, flags, weight, e_reco, bins, value, p_out);
+    const auto load = [&](int m) {
+        return load_event<MODE, FULL, PROB::kDecidesByWave>(bufs, l, m * kTileLanes, n);
+    };
     if constexpr (ROLL) {
         EventIn cur[kGroup], nxt[kGroup];
 #pragma unroll
-        for (int j = 0; j < kGroup; ++j)
-            cur[j] = load_event<MODE, FULL>(bufs, l, j * kTileLanes, n);
+        for (int j = 0; j < kGroup; ++j) cur[j] = load(j);
 #pragma unroll 1
         for (int g = 0; g < kGroups; ++g) {
             const int gn = g + 1 < kGroups ? g + 1 : g;   // the last group reloads itself
 #pragma unroll
-            for (int j = 0; j < kGroup; ++j)
-                nxt[j] = load_event<MODE, FULL>(bufs, l, (gn * kGroup + j) * kTileLanes, n);
+            for (int j = 0; j < kGroup; ++j) nxt[j] = load(gn * kGroup + j);
             tile_group<MODE, WRITE_P, FULL>(prob, bc, hist, lane, l, g * kGroup * kTileLanes, n,
                                             cur, bufs);
 #pragma unroll
@@ -986,15 +989,12 @@ __device__ __forceinline__ void tile_events(const PROB& prob, const BinConsts& b
     } else {
         EventIn ev[kGroups][kGroup];
 #pragma unroll
-        for (int j = 0; j < kGroup; ++j)
-            ev[0][j] = load_event<MODE, FULL>(bufs, l, j * kTileLanes, n);
+        for (int j = 0; j < kGroup; ++j) ev[0][j] = load(j);
 #pragma unroll
         for (int g = 0; g < kGroups; ++g) {
             if (g + 1 < kGroups) {
 #pragma unroll
-                for (int j = 0; j < kGroup; ++j)
-                    ev[g + 1][j] = load_event<MODE, FULL>(bufs, l, ((g + 1) * kGroup + j) * kTileLanes,
-                                                          n);
+                for (int j = 0; j < kGroup; ++j) ev[g + 1][j] = load((g + 1) * kGroup + j);
             }
             tile_group<MODE, WRITE_P, FULL>(prob, bc, hist, lane, l, g * kGroup * kTileLanes,
                                             n, ev[g], bufs);
@@ -1055,7 +1055,8 @@ __device__ __forceinline__ void split_tile_events(const PROB& prob, const BinCon
     EventIn ev[kShare];
 #pragma unroll
     for (int j = 0; j < kShare; ++j)
-        ev[j] = load_event<MODE, false>(bufs, l, uint32_t(wave * kShare + j) * kTileLanes, n);
+        ev[j] = load_event<MODE, false, PROB::kDecidesByWave>(
+            bufs, l, uint32_t(wave * kShare + j) * kTileLanes, n);
     double c[kShare];
     int slot[kShare];
 #pragma unroll
