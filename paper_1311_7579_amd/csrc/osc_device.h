@@ -265,8 +265,9 @@ __device__ __forceinline__ double matter_term(double kA, double E, uint32_t f)
 //   X = (M^2 + e M + g) / f'(x)     (the spectral projector of x),
 //   Y = (M - mu)(1 - X) = M - mu - b X.
 // sin psi / del has no singularity as the two eigenvalues close in.  Only
-// the element (beta, alpha) is formed.  1/E, 1/f', del and 1/del share one
-// inverse square root, of disc (E f')^2.
+// the element (beta, alpha) is formed.  1/f', del and 1/del share one inverse
+// square root, of disc f'^2 (with E in it too, for 1/E, E^2 left FP64's range
+// where E does not).
 // Bound by VALU issue: about 125 FP64 issue slots per event and wave (the
 // benchmark step's loop, an FP32 instruction counted as half), against 158
 // with two roots from trigonometric seeds, a Halley step each and the
@@ -291,17 +292,13 @@ __device__ __forceinline__ double event_prob(const SetConsts& sc, const TileTabl
     const double m2im = fma(A, g.b, m2.b);
 
     const Levels v = matter_levels(sc, A);
-    const double u = E * v.fp;
-    const double y = rsqrt_refined(v.disc * (u * u));   // 1 / (sqrt(disc) u)
-    const double yu = y * u;                            // 1 / sqrt(disc)
-    const double sd = v.disc * yu;                      // sqrt(disc)
-    const double iu = y * sd;                           // 1 / u
-    const double inv_fp = E * iu;
-    double invE = v.fp * iu;
-    invE = fma(invE, fma(-E, invE, 1.0), invE);         // the phases take its last bits
-    const double del = sd * inv_fp, inv_del = v.fp * yu;
+    const double y = rsqrt_refined(v.disc * (v.fp * v.fp));   // 1 / (sqrt(disc) f')
+    const double yf = y * v.fp;                               // 1 / sqrt(disc)
+    const double sd = v.disc * yf;                            // sqrt(disc)
+    const double inv_fp = y * sd;
+    const double del = sd * inv_fp, inv_del = v.fp * yf;
     const double b = fma(0.5, v.e, v.x);
-    const double ph = kL * invE;                        // phase per eV^2 in units of pi/32
+    const double ph = kL * recip(E);                          // phase per eV^2 in units of pi/32
 
     const double Xr = fma(v.g, dba, fma(v.e, mre, m2re)) * inv_fp;
     const double Xi = fma(v.e, mim, m2im) * inv_fp;

@@ -279,3 +279,24 @@ def test_mixed_tier_envelope(osc, ctx):
         assert d.max() <= 1.5e-4, (k, p, L, rho, float(d.max()))
         if rho <= 3.0 and L <= 2500.0:
             assert d[e <= 20.0].max() <= 4e-5, (k, p, L, rho, float(d[e <= 20.0].max()))
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_energies_far_from_one(osc, ctx, precision):
+    """Energies whose square is outside FP64: without matter a phase of (next
+    to) zero leaves every flavour as it is, at any energy above, and over no
+    distance at any energy below."""
+    p = [workload.TABLE1, dict(workload.TABLE1, dm2_32=-2.4e-3, delta_cp=1.1)]
+    ctx.osc_set_params(p)
+    for L, e in ((295.0, (1e100, 1e155, 1e200, 1e290)), (0.0, (1e-100, 1e-155, 1e-200, 1e-280))):
+        ev = [(x, a, b, anti) for x in e for a in range(3) for b in range(3) for anti in (0, 1)]
+        e_true = np.array([v[0] for v in ev])
+        a, b, anti = (np.array([v[k] for v in ev]) for k in (1, 2, 3))
+        s = workload.Sample(e_true, workload.make_flags(a, b, anti), np.ones(len(ev)),
+                            np.ones(len(ev)), L_km=L, rho_gcc=0.0, Ye=0.5)
+        ds = osc.DeviceSample.from_host(s)
+        h = torch.empty(3, dtype=torch.float64, device="cuda")
+        out = torch.empty(len(ev), dtype=torch.float64, device="cuda")
+        for k in range(len(p)):
+            ctx.osc_fill_pdf(ds, k, 1, 0.0, 2.0, h, out, precision=precision)
+            assert np.abs(out.cpu().numpy() - (a == b)).max() <= (1e-12, 3e-6)[precision]
