@@ -557,8 +557,13 @@ osc_status osc_create(osc_ctx** out, int device)
     ctx->device = device;
     ctx->noalloc = noalloc_address(device);
     // per-wave histograms: (nbins + 2) x kHistLanes accumulators x 8 B of
-    // dynamic LDS, next to the static tables (channels, flags, sin/cos)
-    const size_t static_lds = sizeof(osc::TileTables);
+    // dynamic LDS, next to the static tables (channels, sin/cos); what they
+    // leave of the reserve stays unused, so that the bin counts accepted do not
+    // follow the tables' layout
+    constexpr size_t static_lds = 3008;
+    static_assert(sizeof(osc::TileTables) <= static_lds &&
+                  sizeof(osc::TileTablesMixed) <= static_lds &&
+                  sizeof(osc::LayeredTables) <= static_lds, "the tables fit the reserve");
     size_t lds = prop.sharedMemPerBlock > static_lds ? prop.sharedMemPerBlock - static_lds : 0;
     if (osc::set_kernel_attributes(lds) != hipSuccess) {
         // keep to the default 64 KiB per workgroup when the larger limit is refused

@@ -743,3 +743,18 @@ def test_validate_sample_counts(osc, ctx, n):
     want_e = int(np.sum(~((e > 0) & np.isfinite(e))))
     valid = (f < 32) & ((f & 3) < 3) & (((f >> 2) & 3) < 3)
     assert (be, bf) == (want_e, int(np.sum(~valid)))
+
+
+def test_bin_counts_accepted(osc, ctx):
+    """gfx950's 160 KB of LDS hold 2513 rows of 8 accumulators next to the 3008
+    bytes kept for the tables: 2511 bins are accepted, 2512 are refused."""
+    assert ctx.max_nbins == (160 * 1024 - 3008) // 64 - 2 == 2511
+    one = torch.ones(100, dtype=torch.float64, device="cuda")
+    for nb in (2511, 2512):
+        h = torch.empty(nb + 2, dtype=torch.float64, device="cuda")
+        if nb == 2511:
+            ctx.osc_fill_hist(one, one, one, nb, 0.0, 2.0, h)
+            assert float(h.sum()) == 100.0
+        else:
+            with pytest.raises(osc.OscError):
+                ctx.osc_fill_hist(one, one, one, nb, 0.0, 2.0, h)
