@@ -285,9 +285,21 @@ namespace {
 // | 11.1, 6e6 36.2 | 35.0 | 46.8, 1e7 57.4 | 57.3 | 81.6; with P written 2e6
 // 17.5 | 17.3 | 19.2, 3e6 22.4 | 22.8 | 26.3; P alone 1e3 8.2 | 4.0 | 4.0,
 // 6e6 31.1 | 30.0 | 32.2; five layers 1e4 33.5 | 13.1 | 10.8, 4e6 99 | 98 | 97.
-int tile_split(int64_t ntiles, int mode, bool write_p)
+//
+// Given values (kHist) have no arithmetic to share, and four waves only pay
+// where one-wave blocks, each with a histogram of its own, would wait for LDS
+// (kHistLdsSplit: five eighths of the chip's 256 x 160 KB).  One wave | four |
+// eight: 1e6 events of 50 bins 7.3 | 7.5 | 7.2, 2e6 11.8 | 12.5 | 13.9, 3e6 of 20
+// bins 15.1 | 16.2 | 16.8, of 200 bins 20.6 | 17.3 | 18.7, 6.2e6 of 100 bins 27.0
+// | 25.6 | 27.5, 4e6 of 600 bins 40.5 | 26.7 | 25.9.
+constexpr int64_t kHistLdsSplit = 26 << 20;
+int tile_split(int64_t ntiles, int mode, bool write_p, size_t hist_bytes)
 {
     if (mode == kReweight) return ntiles <= 6144 ? 4 : 1;
+    if (mode == kHist) {
+        if (ntiles <= 1024) return 8;
+        return ntiles <= 6144 && ntiles * int64_t(hist_bytes) > kHistLdsSplit ? 4 : 1;
+    }
     if (ntiles <= 768) return 8;
     return ntiles <= (write_p ? 2048 : 6144) ? 4 : 1;
 }
@@ -319,7 +331,7 @@ hipError_t launch_tiles(int mode, bool write_p, bool mixed, const SetConsts& sc,
                 partial);
         };
         constexpr int kMode = decltype(m)::value;
-        const int split = tile_split(ntiles, kMode, decltype(w)::value);
+        const int split = tile_split(ntiles, kMode, decltype(w)::value, lds);
         if (split == 4) return with(Int<4>{});
         if constexpr (kMode != kReweight)
             if (split == 8) return with(Int<8>{});

@@ -184,3 +184,21 @@ def test_ragged_wave_decides_alike_in_every_form(osc, rho, ye, e_range, th12, ta
                 batch.close()
             for j in range(2):
                 assert_bits_equal(got[j, 0], want_h, ("batched", L, j))
+
+
+@pytest.mark.parametrize("tiles,nbins", [(768, 20), (769, 20), (1024, 20), (1025, 20),
+                                         (2040, 206), (2050, 206), (2050, 20), (6144, 100),
+                                         (6145, 100)])
+def test_given_values_split(osc, tiles, nbins):
+    """Both sides of every line of the rule for given values (tiles, and tiles
+    times the histogram's LDS), with a ragged last tile: the contract's bits."""
+    n = tiles * TILE - 300
+    rng = np.random.default_rng(tiles)
+    value, w = rng.random(n), rng.uniform(-0.5, 1.5, n)
+    x = rng.uniform(-0.02, 1.02, n)
+    with osc.Context(0) as ctx:
+        d = lambda a: torch.from_numpy(a).cuda()
+        h = torch.empty(nbins + 2, dtype=torch.float64, device="cuda")
+        ctx.osc_fill_hist(d(value), d(w), d(x), nbins, 0.0, 1.0, h)
+        bins = oracle.bin_indices(x, 0.0, 1.0, nbins)
+        assert_bits_equal(h.cpu().numpy(), oracle.hist_contract(w * value, bins, nbins + 2))
