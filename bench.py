@@ -84,12 +84,12 @@ KERNEL_SOURCES = ("paper_1311_7579_amd/csrc/osc_device.h",
                   "paper_1311_7579_amd/csrc/osc_kernels.hip",
                   "paper_1311_7579_amd/build.py")
 COUNTER_TRAFFIC = {
-    "fetch_kib": 92833.0, "fetch_scale": 2.0,     # copy of 512 MiB: FETCH_SIZE 262157 KiB
-    "write_kib": 82447.5, "write_scale": 1.0,     # copy of 512 MiB: WRITE_SIZE 524288 KiB
+    "fetch_kib": 92853.0, "fetch_scale": 2.0,     # copy of 512 MiB: FETCH_SIZE 262157 KiB
+    "write_kib": 82459.4, "write_scale": 1.0,     # copy of 512 MiB: WRITE_SIZE 524288 KiB
     "valu_per_event": 144.2,
     "classes_per_event": {"fp64": 93.9, "fp64_trans": 2.0, "fp32": 19.0, "fp32_trans": 2.0,
                           "cvt": 3.0, "int32": 6.81, "int64": 0.438, "other": 17.05},
-    "source_sha256": "fad2727c995f9496bbe80f44520cc371b26f34c53cbf685d4191ac93ef256d6a",
+    "source_sha256": "af233c3ca9d3e9721c17115aa910d1c98e6828bd9a2db22205cc2d0650d5f90c",
 }
 # Issue time of one wave instruction on one SIMD, measured with
 # probe kernels of independent chains (ns): FP64 FMA/MUL/ADD 2.08, FP32

@@ -43,11 +43,10 @@ constexpr int64_t kMaxEvents = int64_t(1) << 32;
 // a binary tree in registers, and the block's threads meet in a binary tree
 // (the 64 lanes of a wave, then the waves).  The shape of a block changes no
 // bits, so it follows the largest sample's row count (merge_shape).  A chunk
-// is at most 1024 threads x 64 rows; one level serves samples up to 65536
-// tiles (6.7e7 events), a second one the rest.  Rows are stored bin-major
+// is at most 1024 threads x 32 rows; one level serves samples up to 32768
+// tiles (3.4e7 events), a second one the rest.  Rows are stored bin-major
 // within chunks of kLayoutChunk rows (partial_index), so a thread's rows of
 // one bin are contiguous.
-constexpr int64_t kMergeMaxRows = 65536;
 constexpr int kLayoutChunk = 128;
 constexpr int kMaxBatchSamples = 16;
 // Largest number of parameter sets of one batch (the merge grid's z extent).

@@ -378,22 +378,25 @@ hipError_t launch_layered_tiles(int mode, bool write_p, const SetConsts& sc,
     return hipGetLastError();
 }
 
-// A level divides every sample's row count by at most kMergeMaxRows (rounding
-// up), so two levels reduce the largest accepted sample to one row.
-static_assert(kMaxEvents / kTileEvents <= kMergeMaxRows * kMergeMaxRows && kMaxMergeLevels >= 2,
+// A level that is not the last divides every sample's row count by kScratchChunk
+// (rounding up), so two levels reduce the largest accepted sample to one row.
+constexpr int64_t kScratchChunk = 16384;
+static_assert(kMaxEvents / kTileEvents <= kScratchChunk * kScratchChunk && kMaxMergeLevels >= 2,
               "the merge plan's level capacity covers every accepted sample");
 
 namespace {
 
 // Threads and rows per thread of a merge block, for samples of up to `rows`
 // rows: few waves for few rows (most of a large block's threads would only
-// wait for the others), and one launch instead of two up to 65536 rows: at
+// wait for the others), and one launch instead of two up to 32768 rows: at
 // 19532 rows x 52 bins 10.2 us from the per-event kernel's end against 12.9
-// with two levels.  With blocks enough to fill the chip several times
+// with two levels.  Above that one level's 64 rows a thread do not fit the
+// registers of 1024 threads, and two levels are faster: 5e7 given values of 50
+// bins (48829 rows) 252 us with two levels of 16 rows a thread, 256 of 32, 263
+// with one level; 7e7 339, 340 and 353.  With blocks enough to fill the chip several times
 // (`many`) 4097 to 8192 rows take 256 threads of 32 rows too: the 256-set x
 // 4-sample batch (rows 98 to 4883) merges in 297 instead of 388 us with 1024
 // threads of 16.
-constexpr int64_t kScratchChunk = 16384;
 struct MergeShape {
     int waves, rows;
 };
@@ -402,9 +405,8 @@ MergeShape merge_shape(int64_t rows, bool many)
     if (rows <= 1024) return {1, 16};
     if (rows <= 4096) return {4, 16};
     if (many && rows <= 8192) return {4, 32};
-    if (rows <= 16384) return {16, 16};
-    if (rows <= 32768) return {16, 32};
-    return {16, 64};
+    if (rows > 16384 && rows <= 32768) return {16, 32};
+    return {16, 16};
 }
 
 }  // namespace
@@ -506,8 +508,7 @@ hipError_t run_merge(const MergePlan& p, int64_t n_sets, double* scratch, double
         else if (p.waves[l] == 4 && p.thread_rows[l] == 16) launch(Int<4>{}, Int<16>{});
         else if (p.waves[l] == 4) launch(Int<4>{}, Int<32>{});
         else if (p.thread_rows[l] == 16) launch(Int<16>{}, Int<16>{});
-        else if (p.thread_rows[l] == 32) launch(Int<16>{}, Int<32>{});
-        else launch(Int<16>{}, Int<64>{});
+        else launch(Int<16>{}, Int<32>{});
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         in = out;

@@ -37,8 +37,8 @@ hipError_t launch_layered_tiles(int mode, bool write_p, const SetConsts& sc,
 // tiles each (per parameter set, for up to n_sets of them at once), and the
 // scratch strides they need.  A
 // fixed-capacity value: planning a merge allocates nothing.  A sample has
-// at most kMaxEvents / kTileEvents = 2^22 tiles, which two levels of up to
-// kMergeMaxRows = 2^16 rows reduce to one.
+// at most kMaxEvents / kTileEvents = 2^22 tiles, which two levels reduce to
+// one.
 constexpr int kMaxMergeLevels = 3;
 struct MergePlan {
     int nbt = 0;

@@ -202,3 +202,17 @@ def test_given_values_split(osc, tiles, nbins):
         ctx.osc_fill_hist(d(value), d(w), d(x), nbins, 0.0, 1.0, h)
         bins = oracle.bin_indices(x, 0.0, 1.0, nbins)
         assert_bits_equal(h.cpu().numpy(), oracle.hist_contract(w * value, bins, nbins + 2))
+
+
+@pytest.mark.parametrize("tiles", [32767, 32768, 49152])
+def test_merge_lines(osc, tiles):
+    """Up to 32768 tile rows one merge level, above it two: the contract's bits
+    with a ragged last tile."""
+    n = tiles * TILE - 1
+    value = np.tile(np.random.default_rng(tiles).random(1 << 20), -(-n // (1 << 20)))[:n]
+    with osc.Context(0) as ctx:
+        v = torch.from_numpy(value).cuda()
+        h = torch.empty(4, dtype=torch.float64, device="cuda")
+        ctx.osc_fill_hist(v, torch.full_like(v, 1.0 / 3.0), 4.0 * v, 2, 0.0, 3.0, h)
+        bins = oracle.bin_indices(4.0 * value, 0.0, 3.0, 2)
+        assert_bits_equal(h.cpu().numpy(), oracle.hist_contract((1.0 / 3.0) * value, bins, 4))
