@@ -304,7 +304,15 @@ int tile_split(int64_t ntiles, int mode, bool write_p, size_t hist_bytes)
     return ntiles <= (write_p ? 2048 : 6144) ? 4 : 1;
 }
 
-int layered_split(int64_t ntiles) { return ntiles <= 4096 ? 8 : 1; }
+// The same for a layered path: with one layer to solve, the barriers between
+// the waves' additions weigh more against the arithmetic.  One layer, histogram,
+// one wave | eight: 1e6 events 19.9 | 15.7, 1.6e6 25.7 | 24.6, 2e6 26.1 | 28.1,
+// 4.1e6 40.2 | 50.1; two layers that differ 2.5e6 48.3 | 41.8, 4.1e6 62.0 | 63.4;
+// one layer, P alone 2.5e6 23.8 | 20.3, 4.1e6 31.4 | 33.3.
+int layered_split(int64_t ntiles, int mode, const LayerPath& lp)
+{
+    return ntiles <= (lp.n == 1 && mode != kReweight ? 1600 : 4096) ? 8 : 1;
+}
 
 template <int N>
 using Int = std::integral_constant<int, N>;
@@ -369,7 +377,7 @@ hipError_t launch_layered_tiles(int mode, bool write_p, const SetConsts& sc,
                 dim3{unsigned(ntiles)}, dim3{unsigned(kTileLanes * kSplit)}, lds, stream, ev_begin,
                 ev_end, 0, sc, lp, bc, n, e_true, flags, weight, e_reco, p_out, partial);
         };
-        if (layered_split(ntiles) == 8) return with(Int<8>{});
+        if (layered_split(ntiles, decltype(m)::value, lp) == 8) return with(Int<8>{});
         with(Int<1>{});
     };
     if (mode == kReweight) launch(Int<kReweight>{}, std::true_type{});

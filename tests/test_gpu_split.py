@@ -216,3 +216,22 @@ def test_merge_lines(osc, tiles):
         ctx.osc_fill_hist(v, torch.full_like(v, 1.0 / 3.0), 4.0 * v, 2, 0.0, 3.0, h)
         bins = oracle.bin_indices(4.0 * value, 0.0, 3.0, 2)
         assert_bits_equal(h.cpu().numpy(), oracle.hist_contract((1.0 / 3.0) * value, bins, 4))
+
+
+@pytest.mark.parametrize("n", [1600 * TILE, 1600 * TILE + 1])
+@pytest.mark.parametrize("path", [[(1300.0, 3.0, 0.5)], [(650.0, 3.0, 0.5)] * 2])
+def test_one_solved_layer_splits(osc, n, path):
+    """Both sides of the line for paths with one layer to solve: P as without a
+    histogram, and the contract's bits on it."""
+    s = workload.make_sample(n, 8)
+    with osc.Context(0) as ctx:
+        ctx.osc_set_params([workload.TABLE1])
+        ds = osc.DeviceSample.from_host(s)
+        new = lambda m: torch.empty(m, dtype=torch.float64, device="cuda")
+        p0, p1, h = new(n), new(n), new(NB + 2)
+        ctx.osc_reweight_layered(ds, path, 0, p0)
+        ctx.osc_fill_pdf_layered(ds, path, 0, NB, 0.0, HI, h, p1)
+        assert_bits_equal(p1.cpu().numpy(), p0.cpu().numpy())
+        hist_of(s, p0.cpu().numpy(), h)
+        ctx.osc_fill_pdf_layered(ds, path, 0, NB, 0.0, HI, h)
+        hist_of(s, p0.cpu().numpy(), h)
