@@ -127,7 +127,9 @@ __device__ __forceinline__ void tile_sets(const BatchArgs& a, const BatchSampleD
 
 // SETS: parameter sets run side by side on a tile (a group's last odd set
 // runs alone): each event is loaded and decoded once for them, and the
-// arithmetic of the two interleaves.  Bound by VALU issue.
+// arithmetic of the two interleaves.  Bound by VALU issue.  One set at a time
+// fits 20 waves per CU only while its constants stay in SGPRs: from VGPRs, which
+// two sets take them from, 97 registers instead of 91 left 16.
 template <bool MIXED, int SETS>
 __global__ __launch_bounds__(kTileLanes) __attribute__((amdgpu_waves_per_eu(kBatchWavesPerSimd)))
 void batch_kernel(BatchArgs a, const BatchSampleDev* __restrict__ samples,
@@ -214,7 +216,7 @@ struct osc_batch {
     osc_batch_config graph_cfg{};
     osc_batch_config cfg{};
     int num_cus = 0;
-    int occupancy = 1;
+    int occupancy[2] = {1, 1};   // resident waves per CU: one set at a time, two
     std::mutex mu;
 };
 
@@ -270,10 +272,18 @@ using BatchKernel = void (*)(osc::BatchArgs, const osc::BatchSampleDev*, const o
 // while their histograms and tables leave room for 16 waves per CU (256 sets x
 // 4 samples of 50 bins: 9.06 -> 8.75 ms); above that the waves they cost weigh
 // more (100 bins: 535 -> 617 us for 64 sets x 1.6e6 events, 200 bins 651 ->
-// 974).  One in the FP64 tier, which two do not speed up (524 against 535 us).
-int side_by_side(osc_precision precision, int nbt)
+// 974).  One where most sets would run alone all the same, in a kernel that
+// leaves 16 waves per CU instead of 20 (one set per item: 32 sets x 6.6e6 events
+// 1034 us, 1089 in the kernel for two), and for few sets, whose last items leave
+// the chip to few waves (6.6e6 events, as tuned: 3 sets 129 | 135 us, 7 sets 263 |
+// 282, 16 sets 544 | 529, 32 sets 1033 | 1004).  One in the FP64 tier, which two
+// do not speed up (524 against 535 us).
+constexpr int kPairedSets = 16;
+int side_by_side(osc_precision precision, int nbt, int n_sets, int sets_per_item)
 {
-    return precision == OSC_FP32_MIXED && nbt <= 64 ? 2 : 1;
+    return precision == OSC_FP32_MIXED && nbt <= 64 && n_sets >= kPairedSets && sets_per_item > 1
+               ? 2
+               : 1;
 }
 
 struct BatchLaunch {
@@ -281,10 +291,9 @@ struct BatchLaunch {
     size_t lds;
 };
 
-BatchLaunch batch_launch(osc_precision precision, int nbt)
+BatchLaunch batch_launch(osc_precision precision, int nbt, int sets)
 {
     const bool mixed = precision == OSC_FP32_MIXED;
-    const int sets = side_by_side(precision, nbt);
     return {!mixed       ? &osc::batch_kernel<false, 1>
             : sets == 2  ? &osc::batch_kernel<true, 2>
                          : &osc::batch_kernel<true, 1>,
@@ -296,10 +305,11 @@ BatchLaunch batch_launch(osc_precision precision, int nbt)
 hipError_t enqueue(osc_batch* b, int n_sets, const osc_batch_config& c, hipStream_t stream)
 {
     const osc::BatchArgs a = batch_args(b, n_sets, c);
-    const BatchLaunch k = batch_launch(b->precision, a.nbt);
+    const int sets = side_by_side(b->precision, a.nbt, n_sets, a.sets_per_item);
+    const BatchLaunch k = batch_launch(b->precision, a.nbt, sets);
     int64_t grid = a.n_items;
     if (c.schedule != osc::kOnePerBlock) {
-        const int wpc = c.waves_per_cu > 0 ? c.waves_per_cu : b->occupancy;
+        const int wpc = c.waves_per_cu > 0 ? c.waves_per_cu : b->occupancy[sets - 1];
         grid = std::min<int64_t>(a.n_items, int64_t(b->num_cus) * wpc);
     }
     if (a.n_items > 0) {
@@ -459,21 +469,29 @@ osc_status osc_batch_create(osc_ctx* ctx, const osc_sample* samples, int32_t n_s
         hs[size_t(s)].row0 = b->plan.levels[0].in_row0[s];
 
     hipDeviceProp_t prop;
-    int occ = 0;
-    const BatchLaunch k = batch_launch(precision, nbt);
-    const void* kernel = reinterpret_cast<const void*>(k.kernel);
-    const bool ok =
-        hipGetDeviceProperties(&prop, device) == hipSuccess &&
-        hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, int(k.lds)) ==
-            hipSuccess &&
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, osc::kTileLanes, k.lds) ==
-            hipSuccess;
+    bool ok = hipGetDeviceProperties(&prop, device) == hipSuccess;
+    for (int sets = 1; ok && sets <= side_by_side(precision, nbt, max_sets, 2); ++sets) {
+        const BatchLaunch k = batch_launch(precision, nbt, sets);
+        // one set at a time both tiers take the FP64 kernel's count: its larger
+        // tables cost a wave per CU where LDS is the limit, which suits the
+        // mixed kernel too (6e6 events x 8 sets of 200 bins 372 us with 10 waves,
+        // 406 with 11)
+        const BatchKernel counted = sets == 1 ? &osc::batch_kernel<false, 1> : k.kernel;
+        int occ = 0;
+        for (BatchKernel f : {k.kernel, counted})
+            ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(f),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           int(k.lds)) == hipSuccess;
+        ok = ok && hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                       &occ, reinterpret_cast<const void*>(counted), osc::kTileLanes, k.lds) ==
+                       hipSuccess;
+        b->occupancy[sets - 1] = std::max(1, occ);
+    }
     if (!ok) {
         free_batch(b);
         return OSC_ERR_DEVICE;
     }
     b->num_cus = prop.multiProcessorCount;
-    b->occupancy = std::max(1, occ);
     b->cfg = osc_batch_config{8, osc::kDynamic, 0, 1};
     // the persistent schedules must be able to run every set count up to
     // max_sets with one set per item

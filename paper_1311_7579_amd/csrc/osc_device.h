@@ -345,8 +345,9 @@ struct MixedRoots {
 };
 
 // Constants of a set that the batched kernel keeps in VGPRs over its events
-// (second constant operands of an FMA, which it otherwise copied there for
-// every event): the 256-set x 4-sample batch 8.83 -> 8.69 ms.
+// where it runs two sets side by side (second constant operands of an FMA,
+// which it otherwise copied there for every event): the 256-set x 4-sample
+// batch 8.83 -> 8.69 ms.
 struct MixedRegs {
     double C0, QH1, QH0;
     static __device__ __forceinline__ MixedRegs of(const SetConsts& sc)
@@ -1012,7 +1013,8 @@ __device__ __forceinline__ void tile_events_sets(const SetConsts* const (&sc)[NS
     EventIn cur = load_event<kPdfBinned, FULL>(arr, l, 0, n);
     MixedRegs regs[NS];
 #pragma unroll
-    for (int k = 0; k < NS; ++k) regs[k] = MixedRegs::in_vgprs(*sc[k]);
+    for (int k = 0; k < NS; ++k)
+        regs[k] = NS > 1 ? MixedRegs::in_vgprs(*sc[k]) : MixedRegs::of(*sc[k]);
 #pragma unroll 1
     for (int m = 0; m < kLaneEvents; ++m) {
         const uint32_t next = uint32_t(m + 1 < kLaneEvents ? m + 1 : m) * kTileLanes;

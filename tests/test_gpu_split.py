@@ -235,3 +235,29 @@ def test_one_solved_layer_splits(osc, n, path):
         hist_of(s, p0.cpu().numpy(), h)
         ctx.osc_fill_pdf_layered(ds, path, 0, NB, 0.0, HI, h)
         hist_of(s, p0.cpu().numpy(), h)
+
+
+@pytest.mark.parametrize("n_sets,spi", [(15, 8), (16, 1), (16, 2), (17, 2), (17, 8), (19, 3)])
+def test_paired_sets_from_sixteen(osc, n_sets, spi):
+    """The FP32-mixed batch pairs sets from 16 sets on, with more than one set
+    per item: whole groups, odd groups and a short last one have the plain
+    call's bits, with level crossings and large matter terms in some sets."""
+    n = 5 * TILE + 333
+    s = workload.make_sample(n, 8, L_km=2500.0, rho_gcc=11.0, e_range=(0.1, 60.0))
+    sets = workload.make_param_sets(n_sets, 9)
+    for k in range(1, n_sets, 3):
+        sets[k]["sin2_th13"] = 0.0
+    with osc.Context(0) as ctx:
+        ds = osc.DeviceSample.from_host(s)
+        batch = osc.Batch(ctx, [ds], NB, 0.0, 20.0, osc.OSC_FP32_MIXED, max_sets=n_sets)
+        ctx.osc_set_params(sets)
+        try:
+            for schedule in (0, 1, 2):
+                batch.config = dict(sets_per_item=spi, schedule=schedule)
+                got = batch.run(sets).cpu().numpy()
+                for k in range(n_sets):
+                    h = torch.empty(NB + 2, dtype=torch.float64, device="cuda")
+                    ctx.osc_fill_pdf(ds, k, NB, 0.0, 20.0, h, precision=osc.OSC_FP32_MIXED)
+                    assert_bits_equal(got[k, 0], h.cpu().numpy(), (k, schedule))
+        finally:
+            batch.close()
