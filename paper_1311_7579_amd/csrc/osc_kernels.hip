@@ -159,8 +159,8 @@ __device__ __forceinline__ void serve_finish(const ServeFinish& f, int nbt, int 
 
 // The final merge level of a served request (one set, one sample).  The block
 // that finishes last (each block stores its total before it takes a ticket)
-// ends the request, so that a request takes two launches and neither a copy
-// nor a callback.
+// ends the request, so that a request of up to 4096 tiles takes two launches and
+// neither a copy nor a callback.
 template <int WAVES, int ROWS>
 __global__ __launch_bounds__(WAVES * 64) void merge_serve_kernel(MergeLevel L,
                                                                  const double* __restrict__ in,
@@ -485,15 +485,25 @@ size_t merge_scratch_bytes(const MergePlan& p, int64_t n_sets)
     return size_t(n_sets) * size_t(p.tile_set_stride + 2 * p.level_set_stride) * sizeof(double);
 }
 
+hipError_t launch_serve_finish(const ServeFinish& finish, int nbt, hipStream_t stream)
+{
+    hipLaunchKernelGGL(serve_finish_kernel, dim3(1), dim3(64), 0, stream, finish, nbt);
+    return hipGetLastError();
+}
+
 namespace {
 
 // Runs the merge levels with the final one writing hist_out, or, with
-// `finish`, ending a served request.
+// `finish`, ending a served request.  Blocks of 16 waves leave that end to a
+// kernel of its own: the likelihood in it takes 208 registers, which capped at
+// the 128 of a 1024-thread block spilled 48, and a block needed a CU to itself
+// among the other requests' waves.
 hipError_t run_merge(const MergePlan& p, int64_t n_sets, double* scratch, double* hist_out,
                      const ServeFinish* finish, hipStream_t stream)
 {
     double* bufs[2] = {scratch + n_sets * p.tile_set_stride,
                        scratch + n_sets * (p.tile_set_stride + p.level_set_stride)};
+    if (finish) hist_out = finish->hist;
     const double* in = scratch;
     for (int l = 0; l < p.n_levels; ++l) {
         const MergeLevel& L = p.levels[l];
@@ -502,10 +512,14 @@ hipError_t run_merge(const MergePlan& p, int64_t n_sets, double* scratch, double
         double* out = final_level ? hist_out : bufs[l % 2];
         const auto launch = [&](auto waves, auto rows) {
             constexpr int W = decltype(waves)::value, R = decltype(rows)::value;
-            if (final_level && finish)
-                hipLaunchKernelGGL((merge_serve_kernel<W, R>), grid, dim3(W * 64), 0, stream, L, in,
-                                   *finish);
-            else if (final_level)
+            if constexpr (W < 16 && R == 16)
+                if (final_level && finish) {
+                    hipLaunchKernelGGL((merge_serve_kernel<W, R>), grid, dim3(W * 64), 0, stream,
+                                       L, in, *finish);
+                    finish = nullptr;
+                    return;
+                }
+            if (final_level)
                 hipLaunchKernelGGL((merge_level_kernel<true, W, R>), grid, dim3(W * 64), 0, stream,
                                    L, in, out);
             else
@@ -521,7 +535,7 @@ hipError_t run_merge(const MergePlan& p, int64_t n_sets, double* scratch, double
         if (e != hipSuccess) return e;
         in = out;
     }
-    return hipSuccess;
+    return finish ? launch_serve_finish(*finish, p.nbt, stream) : hipSuccess;
 }
 
 }  // namespace
@@ -536,12 +550,6 @@ hipError_t launch_merge_serve(const MergePlan& p, double* scratch, const ServeFi
                               hipStream_t stream)
 {
     return run_merge(p, 1, scratch, nullptr, &finish, stream);
-}
-
-hipError_t launch_serve_finish(const ServeFinish& finish, int nbt, hipStream_t stream)
-{
-    hipLaunchKernelGGL(serve_finish_kernel, dim3(1), dim3(64), 0, stream, finish, nbt);
-    return hipGetLastError();
 }
 
 hipError_t occupancy(int mode, int nbins, int* blocks_per_cu)

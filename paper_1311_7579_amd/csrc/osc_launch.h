@@ -60,7 +60,7 @@ size_t merge_scratch_bytes(const MergePlan& p, int64_t n_sets);
 hipError_t launch_merge(const MergePlan& p, int64_t n_sets, double* scratch, double* hist_out,
                         hipStream_t stream);
 
-// The merge of one histogram whose last block ends a served request, and the
+// The merge of one histogram and the end of a served request after it, and the
 // end alone, for a histogram that is finished (a single tile's).
 hipError_t launch_merge_serve(const MergePlan& p, double* scratch, const ServeFinish& finish,
                               hipStream_t stream);
