@@ -67,6 +67,7 @@ struct Slot {
     uint64_t ticket = 0;
     size_t off = 0, bytes = 0;
     double t_query = 0.0;       // when to ask the runtime about an overdue request
+    bool lost = false;          // a lost request may have left the block counter above 0
 
     bool arrived() const { return __atomic_load_n(flag, __ATOMIC_ACQUIRE) == seq; }
 };
@@ -156,6 +157,11 @@ osc_status launch(osc_server* sv, Slot& slot, Request& r)
 {
     const osc::SetConsts sc = osc::host::set_consts(r.params);
     double* scratch = reinterpret_cast<double*>(sv->arena_mem + slot.off);
+    if (slot.lost) {
+        if (hipMemsetAsync(slot.d_hist + sv->nbt, 0, sizeof(double), slot.stream) != hipSuccess)
+            return OSC_ERR_DEVICE;
+        slot.lost = false;
+    }
     r.with_nll = sv->has_data;
     osc::ServeFinish finish{};
     finish.ticket = reinterpret_cast<unsigned*>(slot.d_hist + sv->nbt);
@@ -203,6 +209,7 @@ void dispatch_loop(osc_server* sv)
                 slot.t_query = now_s() + kOverdueS;
                 if (hipStreamQuery(slot.stream) == hipErrorNotReady || slot.arrived()) continue;
                 st = OSC_ERR_DEVICE;
+                slot.lost = true;
             }
             Request& r = sv->reqs[slot.ticket];
             if (st == OSC_OK) {
@@ -251,6 +258,7 @@ void dispatch_loop(osc_server* sv)
                 // enqueued before the failure may still use the scratch, so
                 // the slot's stream drains first
                 (void)hipStreamSynchronize(free_slot->stream);
+                free_slot->lost = true;
                 retire(sv, *free_slot, r, st);
                 sv->cv_done.notify_all();
             }
