@@ -39,9 +39,10 @@ double now_s()
 }
 
 constexpr size_t kArenaAlign = 256;
-// How long the dispatcher watches the flags before it sleeps between looks (a
-// sleep of 20 us lasts 70 and more; the small requests end within 40), and
-// when a request without its flag is asked after.
+// How long after the last admission or completion the dispatcher watches the
+// flags without a pause; from then on it sleeps between looks (a sleep of 20 us
+// lasts 70 and more; the small requests end within 40), so that a long request
+// does not hold a host core.  And when a request without its flag is asked after.
 constexpr double kSpinS = 100e-6;
 constexpr double kOverdueS = 0.1;
 
@@ -196,6 +197,7 @@ void dispatch_loop(osc_server* sv)
 {
     (void)hipSetDevice(sv->device);
     std::unique_lock<std::mutex> lock(sv->mu);
+    double watch_until = 0.0;
     while (!sv->stop) {
         // retire finished slots
         bool retired = false;
@@ -219,7 +221,10 @@ void dispatch_loop(osc_server* sv)
             retire(sv, slot, r, st);
             retired = true;
         }
-        if (retired) sv->cv_done.notify_all();
+        if (retired) {
+            sv->cv_done.notify_all();
+            watch_until = now_s() + kSpinS;
+        }
         // admit from the head of the queue while a slot and the budget allow
         while (!sv->pending.empty()) {
             Slot* free_slot = nullptr;
@@ -247,6 +252,7 @@ void dispatch_loop(osc_server* sv)
             free_slot->bytes = bytes;
             r.t_admit = now_s();
             free_slot->t_query = r.t_admit + kOverdueS;
+            watch_until = r.t_admit + kSpinS;
             ++sv->stats.admitted;
             ++sv->stats.in_flight;
             sv->stats.max_in_flight = std::max(sv->stats.max_in_flight, sv->stats.in_flight);
@@ -269,13 +275,13 @@ void dispatch_loop(osc_server* sv)
             sv->cv_dispatch.wait_for(lock, std::chrono::microseconds(2000));
             continue;
         }
-        // completions arrive without a notification: watch the flags for
-        // kSpinS with the lock open, then sleep between looks
+        // completions arrive without a notification: watch the flags until
+        // watch_until with the lock open, then sleep between looks
         const uint64_t calls = sv->calls.load(std::memory_order_relaxed);
-        lock.unlock();
-        const double until = now_s() + kSpinS;
         bool arrived = false;
-        while (!arrived && now_s() < until && sv->calls.load(std::memory_order_relaxed) == calls)
+        lock.unlock();
+        while (!arrived && now_s() < watch_until &&
+               sv->calls.load(std::memory_order_relaxed) == calls)
             for (const Slot& slot : sv->slots) arrived |= slot.busy && slot.arrived();
         lock.lock();
         if (!arrived && sv->calls.load(std::memory_order_relaxed) == calls)

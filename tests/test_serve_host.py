@@ -1,5 +1,6 @@
 """The serving form's host side against a pretended device (no GPU): a lost
-request leaves its slot usable."""
+request leaves its slot usable, and a request in flight does not hold a host
+core."""
 import os
 import subprocess
 
@@ -25,3 +26,11 @@ def test_slot_of_a_lost_request(program):
     first, lost, *after = program("lost")
     assert first == "0" and lost == "3"          # OSC_OK, OSC_ERR_DEVICE
     assert after == ["0 0 1 2 3 4 5 6 7"] * 2
+
+
+def test_cpu_time_while_a_request_runs(program):
+    """Half a second of one request in flight costs the process well under half
+    of a core (0.2 with sleeps of 20 us; 0.64 where it also watches between
+    them)."""
+    status, share = program("idle")[0].split()
+    assert status == "0" and float(share) < 0.4
