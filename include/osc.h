@@ -314,7 +314,11 @@ typedef struct osc_template osc_template;
  * osc_fill_pdf (e_scale applies; under/overflow rows kept).  Synchronous:
  * waits for all earlier work on the device, returns once the template is
  * built, after which the sample arrays are no
- * longer read; the path (L, rho, Ye) is taken from `sample`.  *n_used
+ * longer read; the path (L, rho, Ye) is taken from `sample`.  Builds on one
+ * context run one at a time, and the context keeps their device workspace (up
+ * to 512 MiB, about 28 bytes per event and 8 per cell) for the next one until
+ * osc_destroy, or until an allocation of this library on that device would
+ * fail without it.  *n_used
  * (may be NULL) receives the number of events in the template.  The
  * template holds (nbins_reco + 2) * 18 * nbins_true FP64 values of device
  * memory and belongs to ctx. */

@@ -222,6 +222,8 @@ struct osc_batch {
 
 namespace {
 
+using osc::host::device_malloc;
+
 bool same_cfg(const osc_batch_config& a, const osc_batch_config& b)
 {
     return a.sets_per_item == b.sets_per_item && a.schedule == b.schedule &&
@@ -505,7 +507,7 @@ osc_status osc_batch_create(osc_ctx* ctx, const osc_sample* samples, int32_t n_s
     // histogram slot is cached once, here.
     int64_t events = 0;
     for (int s = 0; s < n_samples; ++s) events += samples[s].n;
-    if (events > 0 && hipMalloc(&b->d_bins, size_t(events) * sizeof(uint16_t)) != hipSuccess) {
+    if (events > 0 && device_malloc(&b->d_bins, size_t(events) * sizeof(uint16_t)) != hipSuccess) {
         free_batch(b);
         return OSC_ERR_OUT_OF_MEMORY;
     }
@@ -525,11 +527,11 @@ osc_status osc_batch_create(osc_ctx* ctx, const osc_sample* samples, int32_t n_s
 
     const size_t scratch = osc::merge_scratch_bytes(b->plan, max_sets);
     const size_t hist_bytes = size_t(max_sets) * n_samples * nbt * sizeof(double);
-    if (hipMalloc(&b->d_samples, hs.size() * sizeof(osc::BatchSampleDev)) != hipSuccess ||
-        hipMalloc(&b->d_sets, size_t(max_sets) * sizeof(osc::SetConsts)) != hipSuccess ||
-        hipMalloc(&b->d_scratch, scratch) != hipSuccess ||
-        hipMalloc(&b->d_queue, osc::kQueueBytes) != hipSuccess ||
-        hipMalloc(&b->d_hist, hist_bytes) != hipSuccess ||
+    if (device_malloc(&b->d_samples, hs.size() * sizeof(osc::BatchSampleDev)) != hipSuccess ||
+        device_malloc(&b->d_sets, size_t(max_sets) * sizeof(osc::SetConsts)) != hipSuccess ||
+        device_malloc(&b->d_scratch, scratch) != hipSuccess ||
+        device_malloc(&b->d_queue, osc::kQueueBytes) != hipSuccess ||
+        device_malloc(&b->d_hist, hist_bytes) != hipSuccess ||
         hipHostMalloc(&b->h_sets, size_t(max_sets) * sizeof(osc::SetConsts), hipHostMallocDefault) !=
             hipSuccess) {
         free_batch(b);

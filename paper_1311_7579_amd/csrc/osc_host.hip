@@ -230,9 +230,12 @@ struct osc_ctx {
     void* build_ptr = nullptr;
     size_t build_cap = 0;
     hipStream_t build_stream = nullptr;
+    osc_ctx* next = nullptr;        // list of the live contexts
 };
 
 namespace {
+
+using osc::host::device_malloc;
 
 osc_status device_status(hipError_t e) { return e == hipSuccess ? OSC_OK : OSC_ERR_DEVICE; }
 
@@ -311,10 +314,7 @@ osc_status acquire_scratch(osc_ctx* ctx, size_t bytes, hipStream_t stream, Scrat
             s.cap = 0;
         }
         const size_t want = (bytes + (size_t(1) << 20) - 1) & ~((size_t(1) << 20) - 1);
-        if (hipMalloc(&s.ptr, want) != hipSuccess) {
-            s.ptr = nullptr;
-            return OSC_ERR_OUT_OF_MEMORY;
-        }
+        if (device_malloc(&s.ptr, want) != hipSuccess) return OSC_ERR_OUT_OF_MEMORY;
         s.cap = want;
         s.recorded = false;
     } else if (s.recorded && s.last != stream) {
@@ -336,7 +336,45 @@ osc_status release_scratch(osc_ctx* ctx, Scratch* s, hipStream_t stream)
 }  // namespace
 
 namespace {
+
 constexpr size_t kBuildKeepBytes = size_t(512) << 20;
+
+// The live contexts, for device_malloc.  Taken before a context's build_mu is
+// tried, never the other way round with a wait.
+std::mutex g_contexts_mu;
+osc_ctx* g_contexts = nullptr;
+
+void free_build_space(osc_ctx* ctx)
+{
+    if (ctx->build_ptr) (void)hipFree(ctx->build_ptr);
+    ctx->build_ptr = nullptr;
+    ctx->build_cap = 0;
+}
+
+}  // namespace
+
+hipError_t osc::host::device_malloc(void** p, size_t bytes, const osc_ctx* building)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipSuccess) return e;
+    (void)hipGetLastError();   // or the next launch's check would find it
+    int device = -1;
+    if (hipGetDevice(&device) == hipSuccess) {
+        bool freed = false;
+        std::lock_guard<std::mutex> lock(g_contexts_mu);
+        for (osc_ctx* c = g_contexts; c; c = c->next) {
+            if (c == building || c->device != device || !c->build_mu.try_lock()) continue;
+            freed = freed || c->build_ptr;
+            free_build_space(c);
+            c->build_mu.unlock();
+        }
+        if (freed) e = hipMalloc(p, bytes);
+    }
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        *p = nullptr;
+    }
+    return e;
 }
 
 osc_status osc::host::BuildSpace::acquire(osc_ctx* ctx, size_t bytes)
@@ -347,13 +385,8 @@ osc_status osc::host::BuildSpace::acquire(osc_ctx* ctx, size_t bytes)
         hipStreamCreateWithFlags(&ctx->build_stream, hipStreamNonBlocking) != hipSuccess)
         return OSC_ERR_DEVICE;
     if (ctx->build_cap >= bytes) return OSC_OK;
-    if (ctx->build_ptr) (void)hipFree(ctx->build_ptr);
-    ctx->build_ptr = nullptr;
-    ctx->build_cap = 0;
-    if (hipMalloc(&ctx->build_ptr, bytes) != hipSuccess) {
-        ctx->build_ptr = nullptr;
-        return OSC_ERR_OUT_OF_MEMORY;
-    }
+    free_build_space(ctx);
+    if (device_malloc(&ctx->build_ptr, bytes, ctx) != hipSuccess) return OSC_ERR_OUT_OF_MEMORY;
     ctx->build_cap = bytes;
     return OSC_OK;
 }
@@ -361,11 +394,7 @@ osc_status osc::host::BuildSpace::acquire(osc_ctx* ctx, size_t bytes)
 osc::host::BuildSpace::~BuildSpace()
 {
     if (!ctx_) return;
-    if (ctx_->build_cap > kBuildKeepBytes) {
-        (void)hipFree(ctx_->build_ptr);
-        ctx_->build_ptr = nullptr;
-        ctx_->build_cap = 0;
-    }
+    if (ctx_->build_cap > kBuildKeepBytes) free_build_space(ctx_);
     ctx_->build_mu.unlock();
 }
 
@@ -577,6 +606,11 @@ osc_status osc_create(osc_ctx** out, int device)
         delete ctx;
         return OSC_ERR_DEVICE;
     }
+    {
+        std::lock_guard<std::mutex> lock(g_contexts_mu);
+        ctx->next = g_contexts;
+        g_contexts = ctx;
+    }
     *out = ctx;
     return OSC_OK;
 }
@@ -585,6 +619,12 @@ osc_status osc_destroy(osc_ctx* ctx)
 {
     if (!ctx) return OSC_OK;
     osc_status st = OSC_OK;
+    {
+        std::lock_guard<std::mutex> lock(g_contexts_mu);
+        osc_ctx** at = &g_contexts;
+        while (*at && *at != ctx) at = &(*at)->next;
+        if (*at) *at = ctx->next;
+    }
     (void)hipSetDevice(ctx->device);
     drop_profile(ctx);
     // one stream: it may have been destroyed since its last call, so wait
@@ -706,7 +746,7 @@ osc_status osc_binned_create(osc_ctx* ctx, const osc_sample* sample, const osc_b
     b->sample = *sample;
     b->binning = *binning;
     if (sample->n > 0 &&
-        hipMalloc(&b->slots, size_t(sample->n) * sizeof(uint16_t)) != hipSuccess) {
+        device_malloc(&b->slots, size_t(sample->n) * sizeof(uint16_t)) != hipSuccess) {
         delete b;
         return OSC_ERR_OUT_OF_MEMORY;
     }
@@ -911,7 +951,7 @@ osc_status osc_validate_sample(osc_ctx* ctx, const osc_sample* sample, int64_t* 
     const hipStream_t hs = static_cast<hipStream_t>(stream);
     unsigned long long* d = nullptr;
     unsigned long long h[2] = {0, 0};
-    if (hipMalloc(&d, sizeof h) != hipSuccess) return OSC_ERR_OUT_OF_MEMORY;
+    if (device_malloc(&d, sizeof h) != hipSuccess) return OSC_ERR_OUT_OF_MEMORY;
     hipError_t e = hipMemsetAsync(d, 0, sizeof h, hs);
     if (e == hipSuccess)
         e = osc::launch_validate_sample(sample->n, sample->e_true, sample->flags, d, hs);

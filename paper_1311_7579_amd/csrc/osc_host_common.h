@@ -35,12 +35,24 @@ hipError_t enqueue_served(const SetConsts& sc, const osc_sample* sample, const u
 hipError_t enqueue_bin_slots(const osc_sample* sample, const osc_binning* binning,
                              uint16_t* bins, hipStream_t stream);
 
+// hipMalloc on the current device.  Where it fails, the workspaces that the
+// contexts on that device keep between builds (BuildSpace) are given back and
+// it is tried once more, so that they never cost an allocation of the library.
+// `building`: the context whose workspace the calling thread holds, if any.
+hipError_t device_malloc(void** p, size_t bytes, const osc_ctx* building = nullptr);
+template <class T>
+hipError_t device_malloc(T** p, size_t bytes)
+{
+    return device_malloc(reinterpret_cast<void**>(p), bytes);
+}
+
 // The context's device workspace and stream for one-time builds (templates).
 // A build holds them from acquire() to the end of the object's life, so
 // builds on one context run one at a time, and has to wait for its stream
 // before that end.  The workspace stays with the context for the next build
-// (allocating and freeing 300 MB costs 0.3 ms each time), unless it is larger
-// than 512 MiB: then it is freed at once.
+// (allocating and freeing 300 MB costs 0.3 ms each time) until device_malloc
+// needs it or the context ends, unless it is larger than 512 MiB: then it is
+// freed at once.
 class BuildSpace {
 public:
     BuildSpace() = default;

@@ -32,6 +32,8 @@
 
 namespace {
 
+using osc::host::device_malloc;
+
 double now_s()
 {
     using clock = std::chrono::steady_clock;
@@ -337,7 +339,7 @@ osc_status osc_server_create(osc_ctx* ctx, const osc_sample* samples, int32_t n_
         sv->need.push_back(osc::host::fill_scratch_bytes(s.n, binning->nbins));
     sv->slots = std::vector<Slot>(size_t(cfg->slots));
     const size_t budget = size_t(cfg->scratch_budget_bytes) & ~(kArenaAlign - 1);
-    bool ok = budget > 0 && hipMalloc(&sv->arena_mem, budget) == hipSuccess;
+    bool ok = budget > 0 && device_malloc(&sv->arena_mem, budget) == hipSuccess;
     // the reco-energy bins of a resident sample do not change from request
     // to request: cache each event's histogram slot once
     sv->bins.assign(sv->samples.size(), nullptr);
@@ -345,13 +347,13 @@ osc_status osc_server_create(osc_ctx* ctx, const osc_sample* samples, int32_t n_
     for (size_t k = 0; ok && k < sv->samples.size(); ++k) {
         const osc_sample& smp = sv->samples[k];
         if (smp.n == 0) continue;
-        ok = hipMalloc(&sv->bins[k], size_t(smp.n) * sizeof(uint16_t)) == hipSuccess &&
+        ok = device_malloc(&sv->bins[k], size_t(smp.n) * sizeof(uint16_t)) == hipSuccess &&
              osc::host::enqueue_bin_slots(&smp, binning, sv->bins[k], nullptr) == hipSuccess;
     }
     ok = ok && hipDeviceSynchronize() == hipSuccess;
     for (Slot& slot : sv->slots) {
         ok = ok && hipStreamCreateWithFlags(&slot.stream, hipStreamNonBlocking) == hipSuccess &&
-             hipMalloc(&slot.d_hist, size_t(sv->nbt + 1) * sizeof(double)) == hipSuccess &&
+             device_malloc(&slot.d_hist, size_t(sv->nbt + 1) * sizeof(double)) == hipSuccess &&
              hipMemset(slot.d_hist, 0, size_t(sv->nbt + 1) * sizeof(double)) == hipSuccess &&
              hipHostMalloc(&slot.h_hist, size_t(sv->nbt + 2) * sizeof(double),
                            hipHostMallocCoherent) == hipSuccess;
@@ -433,7 +435,7 @@ osc_status osc_server_set_data(osc_server* sv, const double* data, double mu_sca
     }
     const size_t bytes = sv->samples.size() * size_t(sv->binning.nbins) * sizeof(double);
     if (hipSetDevice(sv->device) != hipSuccess) return OSC_ERR_DEVICE;
-    if (!sv->d_data && hipMalloc(&sv->d_data, bytes) != hipSuccess) return OSC_ERR_OUT_OF_MEMORY;
+    if (!sv->d_data && device_malloc(&sv->d_data, bytes) != hipSuccess) return OSC_ERR_OUT_OF_MEMORY;
     if (hipMemcpy(sv->d_data, data, bytes, hipMemcpyHostToDevice) != hipSuccess)
         return OSC_ERR_DEVICE;
     sv->mu_scale = mu_scale;

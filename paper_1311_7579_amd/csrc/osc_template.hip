@@ -433,6 +433,8 @@ struct osc_template {
 
 namespace {
 
+using osc::host::device_malloc;
+
 bool true_binning_ok(const osc_binning* b)
 {
     if (!b || b->nbins < 1 || b->nbins > 65536) return false;
@@ -503,8 +505,8 @@ osc_status osc_template_create(osc_ctx* ctx, const osc_sample* sample,
                            true_binning->nbins};
     tp->nr = reco_binning->nbins;
     tp->pc = osc::host::path_consts(sample);
-    if (hipMalloc(&tp->d_T, size_t(cells) * sizeof(double)) != hipSuccess ||
-        hipMalloc(&tp->d_P, size_t(osc::kTemplateChannels * nt) * sizeof(double)) != hipSuccess) {
+    if (device_malloc(&tp->d_T, size_t(cells) * sizeof(double)) != hipSuccess ||
+        device_malloc(&tp->d_P, size_t(osc::kTemplateChannels * nt) * sizeof(double)) != hipSuccess) {
         osc_template_destroy(tp);
         return OSC_ERR_OUT_OF_MEMORY;
     }

@@ -74,6 +74,7 @@ osc_status osc_validate_params(const osc_params*, int32_t) { return OSC_OK; }
 
 namespace osc {
 namespace host {
+hipError_t device_malloc(void** p, size_t n, const osc_ctx*) { return hipMalloc(p, n); }
 SetConsts set_consts(const osc_params& p)
 {
     SetConsts s{};
