@@ -310,8 +310,12 @@ def _stream(stream):
         torch = _torch or _load_torch()
         if torch.cuda.is_initialized():
             # the same handle as torch.cuda.current_stream().cuda_stream,
-            # without the 3 us it takes to build the stream object
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            # without the 3 us it takes to build the stream object; private
+            # names, so a torch without them takes the public way
+            try:
+                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            except AttributeError:
+                pass
         stream = torch.cuda.current_stream()
     return int(getattr(stream, "cuda_stream", stream))
 

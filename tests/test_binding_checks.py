@@ -2,6 +2,8 @@
 that a kernel would read or write out of bounds (wrong dtype, wrong length,
 not contiguous, not in GPU memory) are refused with ValueError before
 anything reaches the library.  Runs without a GPU."""
+from types import SimpleNamespace
+
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -72,3 +74,14 @@ def test_context_wrappers_refuse_before_the_library():
     with pytest.raises(ValueError, match="reads weight and e_reco"):
         sample.weight = None
         ctx.osc_fill_pdf(sample, 0, 50, 0.0, 3.0, f64(52))
+
+
+@pytest.mark.parametrize("gone", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_current_stream_without_torchs_private_names(monkeypatch, gone):
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=0x1234))
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda d: 0x77, raising=False)
+    assert osc._stream(None) == 0x77
+    monkeypatch.delattr(torch._C, gone)
+    assert osc._stream(None) == 0x1234
