@@ -269,3 +269,20 @@ def test_sorts_by_size_and_key_width(osc, ctx, n, nt, nr):
     T_o, used_o = oracle.template(s.e_true, s.flags, s.weight, s.e_reco, nt, 0.1, 6.1, nr, 0.0, 5.0)
     assert used == used_o
     np.testing.assert_array_equal(T, T_o)
+
+
+@pytest.mark.parametrize("nt,nr,bits", [(1, 20, 9), (20_000, 90, 25), (20_000, 100, 26),
+                                        (40_000, 100, 27)])
+def test_sorts_of_every_key_width_that_saves_a_pass(osc, ctx, nt, nr, bits):
+    """Above 2^20 events keys of 9, and of 25 to 27 bits, also take 9 bits a
+    pass: the template's bits, event order kept within every cell."""
+    assert ((nr + 2) * 18 * nt).bit_length() == bits
+    s = mixed_sample((1 << 20) + 1, 3)
+    tp = osc.Template(ctx, osc.DeviceSample.from_host(s), nt, 0.1, 6.1, nr, 0.0, 5.0)
+    try:
+        T, used = host(tp.copy()), tp.n_used
+    finally:
+        tp.close()
+    T_o, used_o = oracle.template(s.e_true, s.flags, s.weight, s.e_reco, nt, 0.1, 6.1, nr, 0.0, 5.0)
+    assert used == used_o
+    assert np.array_equal(T.reshape(-1), T_o.reshape(-1))
