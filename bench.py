@@ -84,12 +84,12 @@ KERNEL_SOURCES = ("paper_1311_7579_amd/csrc/osc_device.h",
                   "paper_1311_7579_amd/csrc/osc_kernels.hip",
                   "paper_1311_7579_amd/build.py")
 COUNTER_TRAFFIC = {
-    "fetch_kib": 92853.3, "fetch_scale": 2.0,     # copy of 512 MiB: FETCH_SIZE 262157 KiB
-    "write_kib": 82419.3, "write_scale": 1.0,     # copy of 512 MiB: WRITE_SIZE 524288 KiB
+    "fetch_kib": 92838.9, "fetch_scale": 2.0,     # copy of 512 MiB: FETCH_SIZE 262157 KiB
+    "write_kib": 82430.0, "write_scale": 1.0,     # copy of 512 MiB: WRITE_SIZE 524288 KiB
     "valu_per_event": 144.2,
     "classes_per_event": {"fp64": 93.9, "fp64_trans": 2.0, "fp32": 19.0, "fp32_trans": 2.0,
                           "cvt": 3.0, "int32": 6.81, "int64": 0.438, "other": 17.05},
-    "source_sha256": "aaa3fcc7664771d4f69be4bfe312e1f19685c6eee4dad109ce4f42ba6d9a4f37",
+    "source_sha256": "362ee3c2202d622b415eafffdedf64bf86b0069586d43ac95b16abaee12b5a40",
 }
 # Issue time of one wave instruction on one SIMD, measured with
 # probe kernels of independent chains (ns): FP64 FMA/MUL/ADD 2.08, FP32

@@ -50,7 +50,6 @@ struct BatchArgs {
     int64_t groups;        // ceil(n_sets / sets_per_item)
     int64_t n_items;       // total tiles x groups
     int64_t set_stride;    // tile-result elements per set
-    BinConsts bc;
 };
 
 enum Schedule { kDynamic = 0, kStatic = 1, kOnePerBlock = 2 };
@@ -249,7 +248,6 @@ osc::BatchArgs batch_args(const osc_batch* b, int n_sets, const osc_batch_config
     for (int64_t t : b->tiles) total_tiles += t;
     a.n_items = total_tiles * a.groups;
     a.set_stride = b->plan.tile_set_stride;
-    a.bc = osc::host::bin_consts(&b->binning);
     return a;
 }
 

@@ -16,7 +16,6 @@
 
 #include <algorithm>
 #include <type_traits>
-#include <vector>
 
 #include "osc_device.h"
 #include "osc_host_common.h"
@@ -563,26 +562,11 @@ hipError_t occupancy(int mode, int nbins, int* blocks_per_cu)
 
 namespace {
 
-// The kernels that keep histograms in dynamic LDS, with SPLIT waves a tile.
-template <int SPLIT>
-hipError_t raise_lds_limit(int bytes)
+// Raises the limit of kernels that keep histograms in dynamic LDS.
+template <class... F>
+hipError_t raise_lds_limit(int bytes, F... kernels)
 {
-    std::vector<const void*> fns{
-        reinterpret_cast<const void*>(&tile_kernel<kPdf, true, false, SPLIT>),
-        reinterpret_cast<const void*>(&tile_kernel<kPdf, false, false, SPLIT>),
-        reinterpret_cast<const void*>(&tile_kernel<kPdf, true, true, SPLIT>),
-        reinterpret_cast<const void*>(&tile_kernel<kPdf, false, true, SPLIT>),
-        reinterpret_cast<const void*>(&tile_kernel<kHist, false, false, SPLIT>),
-        reinterpret_cast<const void*>(&tile_kernel<kPdfBinned, true, false, SPLIT>),
-        reinterpret_cast<const void*>(&tile_kernel<kPdfBinned, false, false, SPLIT>),
-        reinterpret_cast<const void*>(&tile_kernel<kPdfBinned, true, true, SPLIT>),
-        reinterpret_cast<const void*>(&tile_kernel<kPdfBinned, false, true, SPLIT>),
-    };
-    if constexpr (SPLIT != 4) {
-        fns.push_back(reinterpret_cast<const void*>(&layered_tile_kernel<kPdf, true, SPLIT>));
-        fns.push_back(reinterpret_cast<const void*>(&layered_tile_kernel<kPdf, false, SPLIT>));
-    }
-    for (const void* f : fns) {
+    for (const void* f : {reinterpret_cast<const void*>(kernels)...}) {
         const hipError_t e =
             hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
         if (e != hipSuccess) return e;
@@ -590,13 +574,35 @@ hipError_t raise_lds_limit(int bytes)
     return hipSuccess;
 }
 
+// Those with SPLIT waves a tile.
+template <int SPLIT>
+hipError_t raise_tile_limits(int bytes)
+{
+    return raise_lds_limit(
+        bytes, &tile_kernel<kPdf, true, false, SPLIT>, &tile_kernel<kPdf, false, false, SPLIT>,
+        &tile_kernel<kPdf, true, true, SPLIT>, &tile_kernel<kPdf, false, true, SPLIT>,
+        &tile_kernel<kHist, false, false, SPLIT>, &tile_kernel<kPdfBinned, true, false, SPLIT>,
+        &tile_kernel<kPdfBinned, false, false, SPLIT>,
+        &tile_kernel<kPdfBinned, true, true, SPLIT>, &tile_kernel<kPdfBinned, false, true, SPLIT>);
+}
+
+template <int SPLIT>
+hipError_t raise_layered_limits(int bytes)
+{
+    return raise_lds_limit(bytes, &layered_tile_kernel<kPdf, true, SPLIT>,
+                           &layered_tile_kernel<kPdf, false, SPLIT>);
+}
+
 }  // namespace
 
 hipError_t set_kernel_attributes(size_t max_dyn_lds)
 {
-    hipError_t e = raise_lds_limit<1>(int(max_dyn_lds));
-    if (e == hipSuccess) e = raise_lds_limit<4>(int(max_dyn_lds));
-    if (e == hipSuccess) e = raise_lds_limit<8>(int(max_dyn_lds));
+    const int bytes = int(max_dyn_lds);
+    hipError_t e = raise_tile_limits<1>(bytes);
+    if (e == hipSuccess) e = raise_tile_limits<4>(bytes);
+    if (e == hipSuccess) e = raise_tile_limits<8>(bytes);
+    if (e == hipSuccess) e = raise_layered_limits<1>(bytes);
+    if (e == hipSuccess) e = raise_layered_limits<8>(bytes);
     return e;
 }
 

@@ -569,7 +569,9 @@ osc_status osc_template_create(osc_ctx* ctx, const osc_sample* sample,
             }
             if (e == hipSuccess)
                 e = hipMemcpyAsync(&used, d_used, sizeof used, hipMemcpyDeviceToHost, s);
-            if (e == hipSuccess) e = hipStreamSynchronize(s);
+            // also after an error: the workspace is the next build's from here on
+            const hipError_t done = hipStreamSynchronize(s);
+            if (e == hipSuccess) e = done;
             if (e != hipSuccess) st = OSC_ERR_DEVICE;
         }
     }
