@@ -38,15 +38,15 @@ BYTES_PER_EVENT_COMPUTED_BINS = 33
 HBM_PEAK_GBS = 8000.0
 SETTLE_S = 0.1   # untimed load before the warm-up steps (clock settle)
 # Algorithmic FP64 flops per event of the formulation the kernel follows
-# (an FMA counts two, an inverse square root estimate one): matter term and
-# amplitude inputs 9, coefficients of the cubic and its discriminant 13 (the
-# seed of the isolated root is FP32), two chord steps 14, sum and product of
-# the other two roots and f' 6, 1/E, 1/f', del and 1/del from one inverse
-# square root 23, root difference and phase scale 3, the projector element X
-# 8 and Y 7, two sines and cosines of the phases 52 (the phase products sit
-# inside their reduction FMAs), amplitude sum and |S|^2 17, weighted add 2
-# (w * P and the add into the histogram).  Computing the bin per call adds 4
-# (scale, offset, quotient, floor).
+# (an FMA counts two, a reciprocal or inverse square root estimate one):
+# matter term and amplitude inputs 9, coefficients of the cubic and its
+# discriminant 13 (the seed of the isolated root is FP32), two chord steps 14,
+# sum and product of the other two roots and f' 6, 1/f', del and 1/del from
+# one inverse square root 16, 1/E 7, root difference and phase scale 3, the
+# projector element X 8 and Y 7, two sines and cosines of the phases 52 (the
+# phase products sit inside their reduction FMAs), amplitude sum and |S|^2 17,
+# weighted add 2 (w * P and the add into the histogram).  Computing the bin
+# per call adds 4 (scale, offset, quotient, floor).
 FLOPS_PER_EVENT = 154
 FLOPS_PER_EVENT_COMPUTED_BINS = 158
 # Layered path, per layer solved: matter term 1, the isolated root and the
@@ -84,12 +84,12 @@ KERNEL_SOURCES = ("paper_1311_7579_amd/csrc/osc_device.h",
                   "paper_1311_7579_amd/csrc/osc_kernels.hip",
                   "paper_1311_7579_amd/build.py")
 COUNTER_TRAFFIC = {
-    "fetch_kib": 92838.9, "fetch_scale": 2.0,     # copy of 512 MiB: FETCH_SIZE 262157 KiB
-    "write_kib": 82430.0, "write_scale": 1.0,     # copy of 512 MiB: WRITE_SIZE 524288 KiB
+    "fetch_kib": 92833.0, "fetch_scale": 2.0,     # copy of 512 MiB: FETCH_SIZE 262157 KiB
+    "write_kib": 82325.2, "write_scale": 1.0,     # copy of 512 MiB: WRITE_SIZE 524288 KiB
     "valu_per_event": 144.2,
     "classes_per_event": {"fp64": 93.9, "fp64_trans": 2.0, "fp32": 19.0, "fp32_trans": 2.0,
                           "cvt": 3.0, "int32": 6.81, "int64": 0.438, "other": 17.05},
-    "source_sha256": "362ee3c2202d622b415eafffdedf64bf86b0069586d43ac95b16abaee12b5a40",
+    "source_sha256": "435d7df5f0968fab746ac82fca1b3335d4bfbd73b8293861d536ae93ea84ca26",
 }
 # Issue time of one wave instruction on one SIMD, measured with
 # probe kernels of independent chains (ns): FP64 FMA/MUL/ADD 2.08, FP32

@@ -271,7 +271,8 @@ osc_status osc_profile_read(osc_ctx* ctx, double* event_kernel_ms, int64_t* even
  * operator of Sec. 1.1 for its own density and length:
  *   S = S_{n-1} ... S_1 S_0,  P(alpha -> beta) = |S_{beta alpha}|^2,
  * layer 0 crossed first.  Computed in FP64 by propagating column alpha
- * through the layers. */
+ * through the layers; for a path that reads the same from both ends, columns
+ * alpha and beta through its first half. */
 typedef struct {
     double L_km;     /* layer length, >= 0 */
     double rho_gcc;  /* density, >= 0      */
@@ -421,7 +422,10 @@ osc_status osc_batch_tune(osc_batch* batch, const osc_params* sets, int32_t n_se
  * one resident sample in one precision tier.  Requests are queued first in,
  * first out; a dispatcher thread admits the head of the queue when one of
  * `slots` HIP streams is free and the request's device scratch fits in the
- * remaining budget; admitted requests run concurrently.  A request's
+ * remaining budget; admitted requests run concurrently.  Until 100 us after
+ * the last admission or completion the dispatcher watches for results without
+ * a pause, so that a stream of short requests keeps one host core busy; with
+ * only longer ones in flight it looks every 20 us or so.  A request's
  * histogram is the same, bit for bit, as osc_fill_pdf of the same set,
  * sample and tier, alone or in any mix. */
 typedef struct osc_server osc_server;

@@ -176,9 +176,14 @@ struct PolyRegs {
 // The other two roots are not solved for: their sum is tr - x = -e, their
 // product g = c1 - x (tr - x), f'(x) = (x - l1)(x - l2), and half their
 // distance is del = sqrt(disc) / f'(x) with disc a quarter of the
-// discriminant, a quartic in A with host coefficients.  That keeps del
-// accurate to a few ulp of itself also where the two are close (a solution
-// of the cubic for both roots leaves an ulp of the largest root there).
+// discriminant, a quartic in A with host coefficients.  Near a level crossing
+// of a small mixing angle the quartic cancels, so that del errs by about
+// 2^-53 (spread / gap)^2 of itself (in 2^-53: 6 at the atmospheric resonance of
+// Table 1, 150 with sin2_th13 = 1e-3, 2e4 with 1e-5); psi, del times L/2E, is
+// then as far off as an ulp of the largest phase times spread / gap, as with
+// both roots solved for: P was compared with 64-bit-mantissa references at gaps
+// from 8e-4 of the spread and 300 to 12000 km, and its error is the same or
+// smaller than theirs.
 struct Levels {
     double x;     // the isolated eigenvalue
     double e;     // x - tr: minus the sum of the other two
@@ -268,13 +273,15 @@ __device__ __forceinline__ double matter_term(double kA, double E, uint32_t f)
 // the element (beta, alpha) is formed.  1/f', del and 1/del share one inverse
 // square root, of disc f'^2 (with E in it too, for 1/E, E^2 left FP64's range
 // where E does not).
-// Bound by VALU issue: about 125 FP64 issue slots per event and wave (the
+// Bound by VALU issue: about 126 FP64 issue slots per event and wave (the
 // benchmark step's loop, an FP32 instruction counted as half), against 158
 // with two roots from trigonometric seeds, a Halley step each and the
 // projectors of two roots.  1e7 events: P alone 59.5 -> 49.7 us, the step on
-// binned events with P written 71.1 -> 59.9 us; the error against
-// 64-bit references fell (1.1e-15 -> 6.5e-16 relative on uniform energies)
-// or stayed.
+// binned events with P written 71.1 -> 59.9 us.  1/f' of the chord steps and
+// the seed are FP32, which steer an FP64 iteration.  The rms error of P against
+// 50-digit values, before -> now in 1e-16: 295 km E log-uniform 10.3 -> 3.8,
+// uniform 2.3 -> 0.8; 810 km 13.1 -> 10.9, 3.2 -> 1.7; 1300 km 17.0 -> 18.3,
+// 23.9 -> 6.9; 2500 km 21.2 -> 21.5, 7.2 -> 11.5 (one event of 1 MeV).
 __device__ __forceinline__ double event_prob(const SetConsts& sc, const TileTables& T, double kA,
                                              double kL, double E, uint32_t f,
                                              const PolyRegs& pr = PolyRegs{})
@@ -325,8 +332,8 @@ __device__ __forceinline__ double event_prob(const SetConsts& sc, const TileTabl
 // cubically, so the roots are then within about (2^-12)^3 ~ 1.5e-11 of that
 // distance, far below what the FP32 amplitude assembly resolves, and the
 // phases stay within ~1e-8 rad up to 1e3 rad.  (The FP64 tier's isolated
-// root would be cheaper here too, but every P of this tier would change in
-// its FP32 roundings.)
+// root and amplitude together moved P of this tier by up to 2e-7; its root alone
+// in front of this amplitude has not been measured.)
 constexpr double kHalleyOnly = 0x1p-12;
 // Waves with a matter term above this (eV^2, about 4 times the largest
 // vacuum splitting) assemble the amplitude in FP64.

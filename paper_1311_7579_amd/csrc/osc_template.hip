@@ -447,8 +447,8 @@ bool true_binning_ok(const osc_binning* b)
 // The stable sort of (cell key, weight) by the lowest end_bit bits of the key;
 // with tmp null only *bytes, the workspace, is set.  hipCUB takes 8 bits of the
 // key in a pass and merge sort up to about 2^20 values; rocPRIM's radix sort
-// underneath it also takes 9 bits, which saves a pass for keys of 17 and 18 (or
-// 25 to 27) bits.  Template builds with hipCUB's choice | 9 bits (us): 18 bits,
+// underneath it also takes 9 bits, which saves a pass for keys of 9, 17 and 18
+// (or 25 to 27) bits.  Template builds with hipCUB's choice | 9 bits (us): 18 bits,
 // 1e7 events 623 | 534, 5e6 477 | 423, 2e6 292 | 273; 20 bits, 5e6 501 | 508, 2e6
 // 352 | 378; any width, 1e6 336-393 | 225-306, 4e5 267-292 | 193-232, 2e5 184-219
 // | 171-225, 4e4 141-187 | 148-214.
