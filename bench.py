@@ -41,23 +41,24 @@ SETTLE_S = 0.1   # untimed load before the warm-up steps (clock settle)
 # (an FMA counts two, a reciprocal or inverse square root estimate one):
 # matter term and amplitude inputs 9, coefficients of the cubic and its
 # discriminant 13 (the seed of the isolated root is FP32), two chord steps 14,
-# sum and product of the other two roots and f' 6, 1/f', del and 1/del from
-# one inverse square root 16, 1/E 7, root difference and phase scale 3, the
-# projector element X 8 and Y 7, two sines and cosines of the phases 52 (the
-# phase products sit inside their reduction FMAs), amplitude sum and |S|^2 17,
+# sum and product of the other two roots and f' 6, 1/E and 1/f' from one
+# reciprocal estimate 16, the inverse square root of the discriminant, del and
+# 1/del 12, root difference with its rounding and phase scale 8, the projector
+# element X 8 and Y 7, two sines and cosines of the phases 52 (the phase
+# products sit inside their reduction FMAs), amplitude sum and |S|^2 17,
 # weighted add 2 (w * P and the add into the histogram).  Computing the bin
 # per call adds 4 (scale, offset, quotient, floor).
-FLOPS_PER_EVENT = 154
-FLOPS_PER_EVENT_COMPUTED_BINS = 158
+FLOPS_PER_EVENT = 164
+FLOPS_PER_EVENT_COMPUTED_BINS = 168
 # Layered path, per layer solved: matter term 1, the isolated root and the
-# discriminant 33 (as above), 1/f', del and 1/del 15, root difference and
+# discriminant 33 (as above), 1/f' and del 18, root difference and
 # phase scale 3, two sines and cosines 52, the operator's coefficients 18;
 # per vector taken through a layer: y = N v 22, t = kappa y - i s v 30, c0 v
 # 18, N t 28; per event 1/E 7, u . v 24, |S|^2 3 and the weighted add 2.  A
 # path that reads the same from both ends solves its first half only and takes
 # two vectors through each of its layers by the operator's elements: N^2 10,
 # real parts 9, imaginary parts 19, and 66 a vector.
-LAYER_SOLVE_FLOPS = 122
+LAYER_SOLVE_FLOPS = 125
 LAYER_VECTOR_FLOPS = 98
 LAYER_PAIR_FLOPS = 170
 
@@ -84,12 +85,12 @@ KERNEL_SOURCES = ("paper_1311_7579_amd/csrc/osc_device.h",
                   "paper_1311_7579_amd/csrc/osc_kernels.hip",
                   "paper_1311_7579_amd/build.py")
 COUNTER_TRAFFIC = {
-    "fetch_kib": 92833.0, "fetch_scale": 2.0,     # copy of 512 MiB: FETCH_SIZE 262157 KiB
-    "write_kib": 82325.2, "write_scale": 1.0,     # copy of 512 MiB: WRITE_SIZE 524288 KiB
-    "valu_per_event": 144.2,
-    "classes_per_event": {"fp64": 93.9, "fp64_trans": 2.0, "fp32": 19.0, "fp32_trans": 2.0,
+    "fetch_kib": 92838.3, "fetch_scale": 2.0,     # copy of 512 MiB: FETCH_SIZE 262157 KiB
+    "write_kib": 82473.3, "write_scale": 1.0,     # copy of 512 MiB: WRITE_SIZE 524288 KiB
+    "valu_per_event": 149.2,
+    "classes_per_event": {"fp64": 98.9, "fp64_trans": 2.0, "fp32": 19.0, "fp32_trans": 2.0,
                           "cvt": 3.0, "int32": 6.81, "int64": 0.438, "other": 17.05},
-    "source_sha256": "435d7df5f0968fab746ac82fca1b3335d4bfbd73b8293861d536ae93ea84ca26",
+    "source_sha256": "91efb28a43dc5141fe58816f8e510d6003ac41abc7a01d67b9cc262b6e949410",
 }
 # Issue time of one wave instruction on one SIMD, measured with
 # probe kernels of independent chains (ns): FP64 FMA/MUL/ADD 2.08, FP32

@@ -48,17 +48,27 @@ __device__ __forceinline__ double flip_sign(double v, uint32_t sign_bit)
     return __hiloint2double(__double2hiint(v) ^ int(sign_bit), __double2loint(v));
 }
 
-// p7 and q6 are kP7 and kQ6; a caller that evaluates many phases passes
-// them from VGPRs (see PolyRegs), so that each polynomial step reads at most
-// one constant from an SGPR pair (the VALU reads one per instruction).
-__device__ __forceinline__ void phase_sincos(double a, double b, const SinCos* __restrict__ table,
-                                             double& sn, double& cs, double p7 = kP7,
-                                             double q6 = kQ6)
+struct Phase {
+    double u;     // the phase less n
+    int anchor;   // n mod 64
+};
+
+__device__ __forceinline__ Phase reduce_phase(double a, double b)
 {
     const double t = __builtin_fma(a, b, kRoundMagic);
     const double n = t - kRoundMagic;
-    const double u = __builtin_fma(a, b, -n);
-    const SinCos k = table[__double2loint(t) & 63];
+    return {__builtin_fma(a, b, -n), __double2loint(t) & 63};
+}
+
+// p7 and q6 are kP7 and kQ6; a caller that evaluates many phases passes
+// them from VGPRs (see PolyRegs), so that each polynomial step reads at most
+// one constant from an SGPR pair (the VALU reads one per instruction).
+__device__ __forceinline__ void phase_sincos(const Phase& ph, const SinCos* __restrict__ table,
+                                             double& sn, double& cs, double p7 = kP7,
+                                             double q6 = kQ6)
+{
+    const double u = ph.u;
+    const SinCos k = table[ph.anchor];
     const double z = u * u;
     const double s = u * __builtin_fma(z, __builtin_fma(z, __builtin_fma(z, p7, kP5), kP3), kStep);
     const double cm = z * __builtin_fma(z, __builtin_fma(z, q6, kQ4), kQ2);
@@ -270,18 +280,21 @@ __device__ __forceinline__ double matter_term(double kA, double E, uint32_t f)
 //   X = (M^2 + e M + g) / f'(x)     (the spectral projector of x),
 //   Y = (M - mu)(1 - X) = M - mu - b X.
 // sin psi / del has no singularity as the two eigenvalues close in.  Only
-// the element (beta, alpha) is formed.  1/f', del and 1/del share one inverse
-// square root, of disc f'^2 (with E in it too, for 1/E, E^2 left FP64's range
-// where E does not).
-// Bound by VALU issue: about 126 FP64 issue slots per event and wave (the
+// the element (beta, alpha) is formed.
+// What P's error is made of, at large phases: the roundings of x, tr and b, of
+// 1/E and of X's factor 1/f'.  So 1/E and 1/f' share one reciprocal estimate, of
+// E f', but each is corrected with its own residual, and b's rounding (b_lo)
+// enters theta after its reduction.  del needs fewer bits.  Mean ratio of the
+// rms error to that of two solved roots, over 400 sets at 295 to 2500 km: 0.89
+// for E log-uniform on 0.1-10 GeV (1.27 with both inverses from one inverse
+// square root; 1.00 without b_lo), 0.62 for uniform E.
+// Bound by VALU issue: about 128 FP64 issue slots per event and wave (the
 // benchmark step's loop, an FP32 instruction counted as half), against 158
 // with two roots from trigonometric seeds, a Halley step each and the
-// projectors of two roots.  1e7 events: P alone 59.5 -> 49.7 us, the step on
-// binned events with P written 71.1 -> 59.9 us.  1/f' of the chord steps and
-// the seed are FP32, which steer an FP64 iteration.  The rms error of P against
-// 50-digit values, before -> now in 1e-16: 295 km E log-uniform 10.3 -> 3.8,
-// uniform 2.3 -> 0.8; 810 km 13.1 -> 10.9, 3.2 -> 1.7; 1300 km 17.0 -> 18.3,
-// 23.9 -> 6.9; 2500 km 21.2 -> 21.5, 7.2 -> 11.5 (one event of 1 MeV).
+// projectors of two roots: 1e7 events, P alone 59.5 -> 51 us, the step on
+// binned events with P written 71.1 -> 61.5 us.  (b_lo costs 2.5 % of the
+// kernel.)  1/f' of the chord steps and the seed are FP32, which steer an FP64
+// iteration.
 __device__ __forceinline__ double event_prob(const SetConsts& sc, const TileTables& T, double kA,
                                              double kL, double E, uint32_t f,
                                              const PolyRegs& pr = PolyRegs{})
@@ -299,21 +312,26 @@ __device__ __forceinline__ double event_prob(const SetConsts& sc, const TileTabl
     const double m2im = fma(A, g.b, m2.b);
 
     const Levels v = matter_levels(sc, A);
-    const double y = rsqrt_refined(v.disc * (v.fp * v.fp));   // 1 / (sqrt(disc) f')
-    const double yf = y * v.fp;                               // 1 / sqrt(disc)
-    const double sd = v.disc * yf;                            // sqrt(disc)
-    const double inv_fp = y * sd;
-    const double del = sd * inv_fp, inv_del = v.fp * yf;
-    const double b = fma(0.5, v.e, v.x);
-    const double ph = kL * recip(E);                          // phase per eV^2 in units of pi/32
+    // 1/E and 1/f' from one reciprocal, each with its own last bits
+    const double r = __builtin_amdgcn_rcp(E * v.fp);
+    const double rE = v.fp * r, rf = E * r;
+    const double eE = fma(-E, rE, 1.0), ef = fma(-v.fp, rf, 1.0);
+    const double invE = fma(rE, fma(eE, eE, eE), rE);
+    const double inv_fp = fma(rf, fma(ef, ef, ef), rf);
+    const double y = rsqrt_refined(v.disc);             // 1 / sqrt(disc)
+    const double del = (v.disc * y) * inv_fp, inv_del = v.fp * y;
+    const double b = fma(0.5, v.e, v.x), b_lo = fma(0.5, v.e, v.x - b);
+    const double ph = kL * invE;                        // phase per eV^2 in units of pi/32
 
     const double Xr = fma(v.g, dba, fma(v.e, mre, m2re)) * inv_fp;
     const double Xi = fma(v.e, mim, m2im) * inv_fp;
     const double Yr = fma(-b, Xr, fma(v.e, 0.5 * dba, mre));
     const double Yi = fma(-b, Xi, mim);
     double s1, c1, s2, c2;
-    phase_sincos(b, ph, T.sct, s1, c1, pr.p7, pr.q6);     // theta
-    phase_sincos(del, ph, T.sct, s2, c2, pr.p7, pr.q6);   // psi
+    Phase theta = reduce_phase(b, ph);
+    theta.u = fma(b_lo, ph, theta.u);
+    phase_sincos(theta, T.sct, s1, c1, pr.p7, pr.q6);
+    phase_sincos(reduce_phase(del, ph), T.sct, s2, c2, pr.p7, pr.q6);   // psi
     const double sg = s2 * inv_del, w = c1 - c2;
     const double zr = fma(sg, Yi, fma(s1, Xi, fma(w, Xr, dba * c2)));
     const double zi = fma(-sg, Yr, fma(-s1, Xr, w * Xi));
@@ -580,7 +598,7 @@ struct ConstDensityProb {
 // half's operator: S_beta,alpha = (T beta) . (S_mid T alpha).  Both vectors go
 // through each layer of the first half with one set of coefficients.
 //
-// Bound by VALU issue: about 95 FP64 issue slots for a layer's coefficients
+// Bound by VALU issue: about 97 FP64 issue slots for a layer's coefficients
 // and 58 for a vector through it, or 96 for two (by the operator's elements:
 // 24 to form them, 36 a vector; two times 58 took 3 % longer over five layers
 // and 8 % over 12 and 31).  With complex 3x3 products in the flavour basis and
@@ -672,18 +690,16 @@ __device__ __forceinline__ double event_prob_layered(const SetConsts& sc, const 
         const PathConsts pc = lp.layer[k];
         const double A = matter_term(pc.kA, E, f);
         const Levels lv = matter_levels(sc, A);
-        const double y = rsqrt_refined(lv.disc * (lv.fp * lv.fp));   // 1 / (sqrt(disc) f')
-        const double yf = y * lv.fp;                                 // 1 / sqrt(disc)
-        const double sd = lv.disc * yf;
-        const double inv_fp = y * sd;
-        const double del = sd * inv_fp;
+        const double y = rsqrt_refined(lv.disc);   // 1 / sqrt(disc)
+        const double inv_fp = recip(lv.fp);
+        const double del = (lv.disc * y) * inv_fp;
         const double b = fma(0.5, lv.e, lv.x);
         const double ph = pc.kL * invE;
         double s1, c1, s2, c2;
-        phase_sincos(b, ph, T.sct, s1, c1);     // theta
-        phase_sincos(del, ph, T.sct, s2, c2);   // psi
+        phase_sincos(reduce_phase(b, ph), T.sct, s1, c1);     // theta
+        phase_sincos(reduce_phase(del, ph), T.sct, s2, c2);   // psi
         LayerOp o;
-        o.s = s2 * (lv.fp * yf);
+        o.s = s2 * (lv.fp * y);
         o.kr = (c1 - c2) * inv_fp;
         o.ki = fma(o.s, b, -s1) * inv_fp;
         const double del2 = del * del;

@@ -3,7 +3,6 @@
 // on the CPU and ships them to the GPU), device scratch, kernel launches.
 #include <algorithm>
 #include <cmath>
-#include <complex>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -14,8 +13,6 @@
 #include "osc_launch.h"
 
 namespace {
-
-using cplx = std::complex<double>;
 
 // hbar*c = 197.3269804 MeV fm; N_A = 6.02214076e23 / mol (CODATA 2018);
 // G_F / (hbar c)^3 = 1.1663787e-5 GeV^-2.
@@ -56,24 +53,32 @@ bool params_ok(const osc_params& p)
     return true;
 }
 
-// Mixing matrix (PDG form), rows = flavour (e, mu, tau), columns = mass.
-void mixing_matrix(const osc_params& p, cplx U[3][3])
-{
-    const double s12 = std::sqrt(p.sin2_th12), c12 = std::sqrt(1.0 - p.sin2_th12);
-    const double s23 = std::sqrt(p.sin2_th23), c23 = std::sqrt(1.0 - p.sin2_th23);
-    const double s13 = std::sqrt(p.sin2_th13), c13 = std::sqrt(1.0 - p.sin2_th13);
-    const cplx ep = std::polar(1.0, p.delta_cp);     // e^{+i delta}
-    const cplx em = std::conj(ep);
-    U[0][0] = c12 * c13;
-    U[0][1] = s12 * c13;
-    U[0][2] = s13 * em;
-    U[1][0] = -s12 * c23 - c12 * s23 * s13 * ep;
-    U[1][1] = c12 * c23 - s12 * s23 * s13 * ep;
-    U[1][2] = s23 * c13;
-    U[2][0] = s12 * s23 - c12 * c23 * s13 * ep;
-    U[2][1] = -c12 * s23 - s12 * c23 * s13 * ep;
-    U[2][2] = c23 * c13;
-}
+// The parameter-only quantities are formed in extended precision and rounded
+// once: their errors are the same for every event of a set and for every layer
+// of a path, so they add up where the events' own do not.  rms error of P at
+// 295, 810 and 1300 km, E log-uniform on 0.1-10 GeV, in 1e-16: 3.2, 7.9 and
+// 12.4 with these in double, 2.7, 6.9 and 11.3 so; 0.14 -> 0.32 us a set.
+using Ext = long double;
+struct Cx {
+    Ext re, im;
+};
+Cx operator+(Cx a, Cx b) { return {a.re + b.re, a.im + b.im}; }
+Cx operator*(Ext a, Cx b) { return {a * b.re, a * b.im}; }
+Cx times_conj(Cx a, Cx b) { return {a.re * b.re + a.im * b.im, a.im * b.re - a.re * b.im}; }
+
+struct Mixing {
+    Ext s12, c12, s23, c23, s13, c13;
+    Cx ep;           // e^{i delta}
+    Ext dm21, dm31;
+    explicit Mixing(const osc_params& p)
+        : s12(std::sqrt(Ext(p.sin2_th12))), c12(std::sqrt(1.0L - p.sin2_th12)),
+          s23(std::sqrt(Ext(p.sin2_th23))), c23(std::sqrt(1.0L - p.sin2_th23)),
+          s13(std::sqrt(Ext(p.sin2_th13))), c13(std::sqrt(1.0L - p.sin2_th13)),
+          ep{std::cos(p.delta_cp), std::sin(p.delta_cp)}, dm21(p.dm2_21),
+          dm31(Ext(p.dm2_32) + p.dm2_21)
+    {
+    }
+};
 
 // The eigenvalue solver's constants (see SetConsts) from T0, C0, CA and DA,
 // in extended precision: their sums cancel.
@@ -109,37 +114,29 @@ void seed_consts(osc::SetConsts& sc)
 // H0 in the layered path's real tridiagonal basis (see Tridiagonal).
 void tridiagonal_consts(const osc_params& p, osc::Tridiagonal& t)
 {
-    const double s12 = std::sqrt(p.sin2_th12), c12 = std::sqrt(1.0 - p.sin2_th12);
-    const double s23 = std::sqrt(p.sin2_th23), c23 = std::sqrt(1.0 - p.sin2_th23);
-    const double s13 = std::sqrt(p.sin2_th13), c13 = std::sqrt(1.0 - p.sin2_th13);
-    // O = R13 R12, K = O diag(0, dm21, dm31) O^T
-    const double O[3][3] = {{c13 * c12, c13 * s12, s13},
-                            {-s12, c12, 0.0},
-                            {-s13 * c12, -s13 * s12, c13}};
-    const double lv[3] = {0.0, p.dm2_21, p.dm2_32 + p.dm2_21};
-    double K[3][3];
-    for (int i = 0; i < 3; ++i)
-        for (int j = 0; j < 3; ++j) {
-            K[i][j] = 0.0;
-            for (int k = 1; k < 3; ++k) K[i][j] += lv[k] * O[i][k] * O[j][k];
-        }
-    // rotate axes 1 and 2 so that K[0][2] vanishes
-    const double h = std::hypot(K[0][1], K[0][2]);
-    const double c = h > 0.0 ? K[0][1] / h : 1.0, s = h > 0.0 ? K[0][2] / h : 0.0;
-    t.a0 = K[0][0];
-    t.b0 = h;
-    t.a1 = c * c * K[1][1] + 2.0 * c * s * K[1][2] + s * s * K[2][2];
-    t.a2 = s * s * K[1][1] - 2.0 * c * s * K[1][2] + c * c * K[2][2];
-    t.b1 = (c * c - s * s) * K[1][2] + c * s * (K[2][2] - K[1][1]);
+    const Mixing m(p);
+    // columns 1 and 2 of O = R13 R12, K = O diag(0, dm21, dm31) O^T
+    const Ext O1[3] = {m.c13 * m.s12, m.c12, -m.s13 * m.s12}, O2[3] = {m.s13, 0.0L, m.c13};
+    const auto K = [&](int i, int j) { return m.dm21 * O1[i] * O1[j] + m.dm31 * O2[i] * O2[j]; };
+    // rotate axes 1 and 2 so that K(0, 2) vanishes
+    const Ext k01 = K(0, 1), k02 = K(0, 2), k11 = K(1, 1), k12 = K(1, 2), k22 = K(2, 2);
+    const Ext h = std::hypot(k01, k02);
+    const Ext c = h > 0.0L ? k01 / h : 1.0L, s = h > 0.0L ? k02 / h : 0.0L;
+    t.a0 = double(K(0, 0));
+    t.b0 = double(h);
+    t.a1 = double(c * c * k11 + 2.0L * c * s * k12 + s * s * k22);
+    t.a2 = double(s * s * k11 - 2.0L * c * s * k12 + c * c * k22);
+    t.b1 = double((c * c - s * s) * k12 + c * s * (k22 - k11));
     t.b00 = t.b0 * t.b0;
     t.b01 = t.b0 * t.b1;
     t.b11 = t.b1 * t.b1;
-    // rows of R23 diag(1, 1, e^{i delta}) times that rotation
-    const cplx ep = std::polar(1.0, p.delta_cp);
-    const cplx row[3][2] = {{0.0, 0.0}, {c23, s23 * ep}, {-s23, c23 * ep}};
+    // rows of R23 diag(1, 1, e^{i delta}) times that rotation: x on axis 1, y
+    // e^{i delta} on axis 2
+    const Ext x[3] = {0.0L, m.c23, -m.s23}, y[3] = {0.0L, m.s23, m.c23};
     for (int f = 0; f < 3; ++f) {
-        const cplx w1 = c * row[f][0] + s * row[f][1], w2 = c * row[f][1] - s * row[f][0];
-        const double w[5] = {f == 0 ? 1.0 : 0.0, w1.real(), w1.imag(), w2.real(), w2.imag()};
+        const Cx z = y[f] * m.ep;
+        const double w[5] = {f == 0 ? 1.0 : 0.0, double(c * x[f] + s * z.re), double(s * z.im),
+                             double(c * z.re - s * x[f]), double(c * z.im)};
         std::copy(w, w + 5, t.w[f]);
     }
 }
@@ -149,29 +146,33 @@ void tridiagonal_consts(const osc_params& p, osc::Tridiagonal& t)
 // Parameter-only quantities of one set for the kernels.
 osc::SetConsts osc::host::set_consts(const osc_params& p)
 {
-    cplx U[3][3];
-    mixing_matrix(p, U);
-    const double dm21 = p.dm2_21, dm31 = p.dm2_32 + p.dm2_21;
-    const double lv[3] = {0.0, dm21, dm31};
+    const Mixing m(p);
+    const Ext dm21 = m.dm21, dm31 = m.dm31;
+    // columns 1 and 2 of the mixing matrix (PDG form; the level of column 0 is
+    // 0), rows = flavour (e, mu, tau)
+    const Cx U1[3] = {{m.s12 * m.c13, 0.0L},
+                      Cx{m.c12 * m.c23, 0.0L} + (-m.s12 * m.s23 * m.s13) * m.ep,
+                      Cx{-m.c12 * m.s23, 0.0L} + (-m.s12 * m.c23 * m.s13) * m.ep};
+    const Cx U2[3] = {{m.s13 * m.ep.re, -m.s13 * m.ep.im},
+                      {m.s23 * m.c13, 0.0L},
+                      {m.c23 * m.c13, 0.0L}};
 
-    cplx H[3][3], H2[3][3];   // U diag(lv) U^+ and U diag(lv^2) U^+
+    Cx H[3][3], H2[3][3];   // U diag(lv) U^+ and U diag(lv^2) U^+
     for (int b = 0; b < 3; ++b)
-        for (int a = 0; a < 3; ++a) {
-            cplx h = 0.0, h2 = 0.0;
-            for (int i = 0; i < 3; ++i) {
-                const cplx t = U[b][i] * std::conj(U[a][i]);
-                h += lv[i] * t;
-                h2 += lv[i] * lv[i] * t;
-            }
-            H[b][a] = h;
-            H2[b][a] = h2;
+        for (int a = 0; a <= b; ++a) {
+            const Cx h1 = dm21 * times_conj(U1[b], U1[a]), h2 = dm31 * times_conj(U2[b], U2[a]);
+            H[b][a] = h1 + h2;
+            H2[b][a] = dm21 * h1 + dm31 * h2;
+            H[a][b] = {H[b][a].re, -H[b][a].im};
+            H2[a][b] = {H2[b][a].re, -H2[b][a].im};
         }
 
     osc::SetConsts sc{};
-    sc.T0 = dm21 + dm31;                        // trace of H
-    sc.C0 = dm21 * dm31;                        // sum of principal 2x2 minors of H
-    sc.CA = H[1][1].real() + H[2][2].real();    // d c1 / dA
-    sc.DA = dm21 * dm31 * std::norm(U[0][0]);   // d det / dA = cofactor_ee(H)
+    const Ext Ue0 = m.c12 * m.c13;
+    sc.T0 = double(dm21 + dm31);                 // trace of H
+    sc.C0 = double(dm21 * dm31);                 // sum of principal 2x2 minors of H
+    sc.CA = double(H[1][1].re + H[2][2].re);     // d c1 / dA
+    sc.DA = double(dm21 * dm31 * Ue0 * Ue0);     // d det / dA = cofactor_ee(H)
     // q/2 = tr^3 - 4.5 tr c1 + 13.5 det as a cubic in A
     sc.QH2 = 3.0 * sc.T0 - 4.5 * sc.CA;
     sc.QH1 = 3.0 * sc.T0 * sc.T0 - 4.5 * (sc.C0 + sc.T0 * sc.CA) + 13.5 * sc.DA;
@@ -179,11 +180,12 @@ osc::SetConsts osc::host::set_consts(const osc_params& p)
     seed_consts(sc);
     for (int b = 0; b < 3; ++b)
         for (int a = 0; a < 3; ++a) {
-            cplx g = 0.0;
-            if (b == 0) g += H[0][a];
-            if (a == 0) g += H[b][0];
-            sc.ch[3 * b + a] = osc::Chan{H[b][a].real(), H[b][a].imag(), H2[b][a].real(),
-                                         H2[b][a].imag(), g.real(),          g.imag(),
+            Cx g{0.0L, 0.0L};
+            if (b == 0) g = g + H[0][a];
+            if (a == 0) g = g + H[b][0];
+            sc.ch[3 * b + a] = osc::Chan{double(H[b][a].re),  double(H[b][a].im),
+                                         double(H2[b][a].re), double(H2[b][a].im),
+                                         double(g.re),        double(g.im),
                                          (a == 0 && b == 0) ? 1.0 : 0.0};
         }
     return sc;
