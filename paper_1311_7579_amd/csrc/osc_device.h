@@ -288,13 +288,13 @@ __device__ __forceinline__ double matter_term(double kA, double E, uint32_t f)
 // rms error to that of two solved roots, over 400 sets at 295 to 2500 km: 0.89
 // for E log-uniform on 0.1-10 GeV (1.27 with both inverses from one inverse
 // square root; 1.00 without b_lo), 0.62 for uniform E.
-// Bound by VALU issue: about 128 FP64 issue slots per event and wave (the
+// Bound by VALU issue: about 131 FP64 issue slots per event and wave (the
 // benchmark step's loop, an FP32 instruction counted as half), against 158
 // with two roots from trigonometric seeds, a Halley step each and the
-// projectors of two roots: 1e7 events, P alone 59.5 -> 51 us, the step on
-// binned events with P written 71.1 -> 61.5 us.  (b_lo costs 2.5 % of the
-// kernel.)  1/f' of the chord steps and the seed are FP32, which steer an FP64
-// iteration.
+// projectors of two roots: 1e7 events, P alone 61.7 -> 54.7 us a call, the
+// step on binned events with P written 76.7 -> 68.9 us (52.4 and 67.3 with both
+// inverses from one inverse square root and without b_lo).  1/f' of the chord
+// steps and the seed are FP32, which steer an FP64 iteration.
 __device__ __forceinline__ double event_prob(const SetConsts& sc, const TileTables& T, double kA,
                                              double kL, double E, uint32_t f,
                                              const PolyRegs& pr = PolyRegs{})
