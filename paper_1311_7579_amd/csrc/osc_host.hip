@@ -55,27 +55,31 @@ bool params_ok(const osc_params& p)
 
 // The parameter-only quantities are formed in extended precision and rounded
 // once: their errors are the same for every event of a set and for every layer
-// of a path, so they add up where the events' own do not.  rms error of P at
-// 295, 810 and 1300 km, E log-uniform on 0.1-10 GeV, in 1e-16: 3.2, 7.9 and
-// 12.4 with these in double, 2.7, 6.9 and 11.3 so; 0.14 -> 0.32 us a set.
+// of a path, so they add up where the events' own do not, and event_prob's Y
+// cancels the matrix elements down to the half distance of two levels.  rms
+// error of P at 295, 810 and 1300 km, E log-uniform on 0.1-10 GeV, in 1e-16:
+// 3.2, 7.9 and 12.4 with these in double, 2.9, 7.6 and 12.2 with only the cubic's
+// so, 2.7, 6.9 and 11.3 with all; 0.14 -> 0.17 us a set (0.32 with the smaller
+// term of the matrix elements in extended precision too, for the same errors).
 using Ext = long double;
-struct Cx {
-    Ext re, im;
-};
-Cx operator+(Cx a, Cx b) { return {a.re + b.re, a.im + b.im}; }
-Cx operator*(Ext a, Cx b) { return {a * b.re, a * b.im}; }
-Cx times_conj(Cx a, Cx b) { return {a.re * b.re + a.im * b.im, a.im * b.re - a.re * b.im}; }
+
+// Square root: a Newton correction of the one in double (18 -> 5 ns).
+Ext root(Ext y)
+{
+    const double s = std::sqrt(double(y));
+    return s > 0.0 ? s + (y - Ext(s) * s) * (0.5 / s) : 0.0L;
+}
 
 struct Mixing {
-    Ext s12, c12, s23, c23, s13, c13;
-    Cx ep;           // e^{i delta}
+    Ext S12, C12, S23, C23, S13, C13;   // squared sines and cosines
+    Ext s23, c23, s13, c13;
+    double cd, sd;                      // cos and sin of delta
     Ext dm21, dm31;
     explicit Mixing(const osc_params& p)
-        : s12(std::sqrt(Ext(p.sin2_th12))), c12(std::sqrt(1.0L - p.sin2_th12)),
-          s23(std::sqrt(Ext(p.sin2_th23))), c23(std::sqrt(1.0L - p.sin2_th23)),
-          s13(std::sqrt(Ext(p.sin2_th13))), c13(std::sqrt(1.0L - p.sin2_th13)),
-          ep{std::cos(p.delta_cp), std::sin(p.delta_cp)}, dm21(p.dm2_21),
-          dm31(Ext(p.dm2_32) + p.dm2_21)
+        : S12(p.sin2_th12), C12(1.0L - S12), S23(p.sin2_th23), C23(1.0L - S23), S13(p.sin2_th13),
+          C13(1.0L - S13), s23(root(S23)), c23(root(C23)), s13(root(S13)), c13(root(C13)),
+          cd(std::cos(p.delta_cp)),
+          sd(std::sin(p.delta_cp)), dm21(p.dm2_21), dm31(Ext(p.dm2_32) + p.dm2_21)
     {
     }
 };
@@ -115,14 +119,16 @@ void seed_consts(osc::SetConsts& sc)
 void tridiagonal_consts(const osc_params& p, osc::Tridiagonal& t)
 {
     const Mixing m(p);
-    // columns 1 and 2 of O = R13 R12, K = O diag(0, dm21, dm31) O^T
-    const Ext O1[3] = {m.c13 * m.s12, m.c12, -m.s13 * m.s12}, O2[3] = {m.s13, 0.0L, m.c13};
-    const auto K = [&](int i, int j) { return m.dm21 * O1[i] * O1[j] + m.dm31 * O2[i] * O2[j]; };
+    const Ext sc12 = root(m.S12 * m.C12);
+    // K = O diag(0, dm21, dm31) O^T, O = R13 R12
+    const Ext k00 = m.dm21 * m.S12 * m.C13 + m.dm31 * m.S13, k01 = m.dm21 * sc12 * m.c13,
+              k02 = m.s13 * m.c13 * (m.dm31 - m.dm21 * m.S12), k11 = m.dm21 * m.C12,
+              k12 = -m.dm21 * sc12 * m.s13,
+              k22 = m.dm21 * m.S12 * m.S13 + m.dm31 * m.C13;
     // rotate axes 1 and 2 so that K(0, 2) vanishes
-    const Ext k01 = K(0, 1), k02 = K(0, 2), k11 = K(1, 1), k12 = K(1, 2), k22 = K(2, 2);
     const Ext h = std::hypot(k01, k02);
     const Ext c = h > 0.0L ? k01 / h : 1.0L, s = h > 0.0L ? k02 / h : 0.0L;
-    t.a0 = double(K(0, 0));
+    t.a0 = double(k00);
     t.b0 = double(h);
     t.a1 = double(c * c * k11 + 2.0L * c * s * k12 + s * s * k22);
     t.a2 = double(s * s * k11 - 2.0L * c * s * k12 + c * c * k22);
@@ -134,9 +140,9 @@ void tridiagonal_consts(const osc_params& p, osc::Tridiagonal& t)
     // e^{i delta} on axis 2
     const Ext x[3] = {0.0L, m.c23, -m.s23}, y[3] = {0.0L, m.s23, m.c23};
     for (int f = 0; f < 3; ++f) {
-        const Cx z = y[f] * m.ep;
-        const double w[5] = {f == 0 ? 1.0 : 0.0, double(c * x[f] + s * z.re), double(s * z.im),
-                             double(c * z.re - s * x[f]), double(c * z.im)};
+        const Ext re = y[f] * m.cd, im = y[f] * m.sd;
+        const double w[5] = {f == 0 ? 1.0 : 0.0, double(c * x[f] + s * re), double(s * im),
+                             double(c * re - s * x[f]), double(c * im)};
         std::copy(w, w + 5, t.w[f]);
     }
 }
@@ -147,47 +153,51 @@ void tridiagonal_consts(const osc_params& p, osc::Tridiagonal& t)
 osc::SetConsts osc::host::set_consts(const osc_params& p)
 {
     const Mixing m(p);
-    const Ext dm21 = m.dm21, dm31 = m.dm31;
-    // columns 1 and 2 of the mixing matrix (PDG form; the level of column 0 is
-    // 0), rows = flavour (e, mu, tau)
-    const Cx U1[3] = {{m.s12 * m.c13, 0.0L},
-                      Cx{m.c12 * m.c23, 0.0L} + (-m.s12 * m.s23 * m.s13) * m.ep,
-                      Cx{-m.c12 * m.s23, 0.0L} + (-m.s12 * m.c23 * m.s13) * m.ep};
-    const Cx U2[3] = {{m.s13 * m.ep.re, -m.s13 * m.ep.im},
-                      {m.s23 * m.c13, 0.0L},
-                      {m.c23 * m.c13, 0.0L}};
-
-    Cx H[3][3], H2[3][3];   // U diag(lv) U^+ and U diag(lv^2) U^+
-    for (int b = 0; b < 3; ++b)
-        for (int a = 0; a <= b; ++a) {
-            const Cx h1 = dm21 * times_conj(U1[b], U1[a]), h2 = dm31 * times_conj(U2[b], U2[a]);
-            H[b][a] = h1 + h2;
-            H2[b][a] = dm21 * h1 + dm31 * h2;
-            H[a][b] = {H[b][a].re, -H[b][a].im};
-            H2[a][b] = {H2[b][a].re, -H2[b][a].im};
-        }
-
     osc::SetConsts sc{};
-    const Ext Ue0 = m.c12 * m.c13;
-    sc.T0 = double(dm21 + dm31);                 // trace of H
-    sc.C0 = double(dm21 * dm31);                 // sum of principal 2x2 minors of H
-    sc.CA = double(H[1][1].re + H[2][2].re);     // d c1 / dA
-    sc.DA = double(dm21 * dm31 * Ue0 * Ue0);     // d det / dA = cofactor_ee(H)
+    sc.T0 = double(m.dm21 + m.dm31);   // trace of H
+    sc.C0 = double(m.dm21 * m.dm31);   // sum of principal 2x2 minors of H
+    // d c1 / dA = H_mm + H_tt and d det / dA = cofactor_ee(H)
+    sc.CA = double(m.dm21 * (1.0L - m.S12 * m.C13) + m.dm31 * m.C13);
+    sc.DA = double(m.dm21 * m.dm31 * m.C12 * m.C13);
+
+    // Elements ee, me, mm, te, tm, tt of dm31 U_b2 U_a2^* (PDG form; without
+    // e^{i delta}, which me and te carry) and of dm21 U_b1 U_a1^*, the smaller
+    // term of the two, in double.
+    const Ext ls = m.dm31 * m.s13 * m.c13, lc = m.dm31 * m.C13;
+    const Ext l2[6] = {m.dm31 * m.S13, m.s23 * ls, m.S23 * lc, m.c23 * ls, m.s23 * m.c23 * lc,
+                       m.C23 * lc};
+    const double d = p.dm2_21, S12 = p.sin2_th12, S23 = p.sin2_th23, S13 = p.sin2_th13,
+                 C12 = double(m.C12), C23 = double(m.C23), C13 = double(m.C13),
+                 s23 = double(m.s23), c23 = double(m.c23), c13 = double(m.c13),
+                 sc12 = std::sqrt(S12 * C12), sc23 = s23 * c23, w = sc12 * double(m.s13),
+                 u = S12 * double(m.s13) * c13, t = 2.0 * sc23 * w * m.cd;
+    const double re1[6] = {d * (S12 * C13),
+                           d * (sc12 * c13 * c23 - u * s23 * m.cd),
+                           d * (C12 * C23 + S12 * S23 * S13 - t),
+                           -d * (sc12 * c13 * s23 + u * c23 * m.cd),
+                           d * (sc23 * (S12 * S13 - C12) + w * m.cd * (S23 - C23)),
+                           d * (C12 * S23 + S12 * C23 * S13 + t)};
+    const double im1[6] = {0.0, -d * u * s23 * m.sd, 0.0, -d * u * c23 * m.sd, -d * w * m.sd, 0.0};
+    for (int b = 0, k = 0; b < 3; ++b)
+        for (int a = 0; a <= b; ++a, ++k) {
+            const bool phase = a == 0 && b > 0;
+            const Ext r2 = phase ? l2[k] * m.cd : l2[k], i2 = phase ? l2[k] * m.sd : 0.0L;
+            osc::Chan c{};
+            c.m_re = double(r2 + re1[k]);
+            c.m_im = double(i2 + im1[k]);
+            c.m2_re = double(m.dm31 * r2 + d * re1[k]);
+            c.m2_im = double(m.dm31 * i2 + d * im1[k]);
+            if (a == 0) c.g_re = (b == 0 ? 2.0 : 1.0) * c.m_re, c.g_im = c.m_im;
+            c.dee = b == 0 ? 1.0 : 0.0;
+            sc.ch[3 * b + a] = c;
+            c.m_im = -c.m_im, c.m2_im = -c.m2_im, c.g_im = -c.g_im;
+            if (a < b) sc.ch[3 * a + b] = c;
+        }
     // q/2 = tr^3 - 4.5 tr c1 + 13.5 det as a cubic in A
     sc.QH2 = 3.0 * sc.T0 - 4.5 * sc.CA;
     sc.QH1 = 3.0 * sc.T0 * sc.T0 - 4.5 * (sc.C0 + sc.T0 * sc.CA) + 13.5 * sc.DA;
     sc.QH0 = sc.T0 * (sc.T0 * sc.T0 - 4.5 * sc.C0);
     seed_consts(sc);
-    for (int b = 0; b < 3; ++b)
-        for (int a = 0; a < 3; ++a) {
-            Cx g{0.0L, 0.0L};
-            if (b == 0) g = g + H[0][a];
-            if (a == 0) g = g + H[b][0];
-            sc.ch[3 * b + a] = osc::Chan{double(H[b][a].re),  double(H[b][a].im),
-                                         double(H2[b][a].re), double(H2[b][a].im),
-                                         double(g.re),        double(g.im),
-                                         (a == 0 && b == 0) ? 1.0 : 0.0};
-        }
     return sc;
 }
 
